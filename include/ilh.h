@@ -420,6 +420,15 @@ int ilh_set_apply_rows(ilh_ctx* ctx, int rows);
  * has fewer than 1,024 waves (one per SIMD), else 1.  FP64 actions always use one wave.  The
  * result does not depend on it beyond the order of FP additions.  Other values: ILH_EINVAL. */
 int ilh_set_apply_waves(ilh_ctx* ctx, int waves);
+/* The Gram-Schmidt part of an Arnoldi step runs as one launch, whose work-groups meet once inside
+ * it, where the basis vectors fit the registers of one work-group per compute unit (up to 14 basis
+ * vectors), else as three launches.  us bounds the time the work-groups wait for one another
+ * (default 5,000 microseconds): a step whose work-groups could not all be placed in that time
+ * (other work holds the device) is given up on the device without a store, the solver repeats
+ * the cycle with the three launches and the context keeps to them.  us < 0 takes the three
+ * launches from the start; us = 0 gives every such step up (the fallback's test).  The result does
+ * not depend on it beyond the order of FP additions.  us above 1e6 or NaN: ILH_EINVAL. */
+int ilh_set_step_wait(ilh_ctx* ctx, double us);
 int ilh_timing_enable(ilh_ctx* ctx, int on);
 int ilh_timing_read(ilh_ctx* ctx, double* ms, int64_t* launches);
 

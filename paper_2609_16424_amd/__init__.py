@@ -322,6 +322,11 @@ class Hydro:
         mesh size."""
         self._check(self.lib.ilh_set_apply_waves(self.ctx, int(waves)))
 
+    def set_step_wait(self, us):
+        """Longest wait, in microseconds, of the work-groups of a one-launch Arnoldi step for one
+        another; negative: three launches instead."""
+        self._check(self.lib.ilh_set_step_wait(self.ctx, float(us)))
+
     def timing(self, on=True):
         self._check(self.lib.ilh_timing_enable(self.ctx, int(bool(on))))
 

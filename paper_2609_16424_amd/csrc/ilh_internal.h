@@ -136,6 +136,9 @@ struct ilh_ctx {
                                 // {h_j+1,j, tag} at [4j, 4j + 4); [256, 258) a pair of norms
   double* hest_dev = nullptr;   // its device (mapped) address
   double est_tag = 0.0;         // tag of the current FGMRES cycle (host counter)
+  unsigned* gs_words = nullptr;  // arrival words of the one-launch Arnoldi steps, zeroed by each cycle's start
+  int gs_cus = 0;                // compute units of the device (bounds the work-groups that meet in a launch)
+  double gs_wait_us = 5000.0;    // longest wait of those work-groups; < 0: three launches instead; 0: always given up
   double* gmd = nullptr;        // device Givens state of FGMRES: H [64][64], cs, sn [64], g [65]
   hipStream_t capstream = nullptr;         // stream the Arnoldi-step graphs are captured on
   std::vector<hipGraphExec_t> gexec;       // captured Arnoldi step per basis index
@@ -281,6 +284,8 @@ constexpr int HDEV_LGSE = 770;
 // 771: |r|^2 of a restart residual, formed on the device and read by the next cycle's scaling
 constexpr int HDEV_RBETA2 = 771;
 constexpr int HDEV_LEN = 776;
+// hest[HEST_ABORT, +2): {step, tag} of a cycle whose one-launch step was given up
+constexpr int HEST_ABORT = 260;
 // y = H(0:n, 0:n)^-1 g
 int launch_trisolve(ilh_ctx* c, const double* G, int m, int n, double* y);
 // x += Z y with y = H(0:jn, 0:jn)^-1 g, one launch (accumulate = false: x = Z y, x need not be
@@ -358,7 +363,17 @@ int lgs_final(ilh_ctx* c, const double* part, int np, int j, int m, int has_w, d
 template <typename TV>
 int lgs_update(ilh_ctx* c, TV* V, int64_t ldv, int j, const double* h, TV* z, float* z32, TV* zero_v, int probe,
                int coupled, const double* tau_dev, double* hest, const double* end);
+// The same step j (<= lgs_step_max_j()) as one launch, np node pairs per thread (ilh_gs.hip);
+// lgs_step_pairs: the np that fits this context, 0 where the three launches are taken.
+// Arrival words: GS_STEP_WORDS per step, for GS_STEPS steps.
+constexpr int GS_STEP_WORDS = 1024, GS_STEPS = 15;
+int lgs_step_pairs(const ilh_ctx* c, bool f32);
+int lgs_step_max_j();
+template <typename TV>
+int lgs_step(ilh_ctx* c, int np, TV* V, int64_t ldv, int j, int m, double* h, double* G, TV* z, float* z32,
+             TV* zero_v, int probe, int coupled, double* part, double* hest);
 // (skip nullable: the kernel returns at once when *skip is nonzero)
+int launch_jvp2d_q_f64(ilh_ctx* c, const double* dk, double* out, const double* tau_dev, const double* skip = nullptr);
 int launch_jvp2d_q_f32to64(ilh_ctx* c, const float* dk, double* out, const double* tau_dev,
                            const double* skip = nullptr);
 int launch_jvp2d_q_f32to32(ilh_ctx* c, const float* dk, float* out, const double* tau_dev,

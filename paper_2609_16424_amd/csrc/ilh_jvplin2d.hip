@@ -657,6 +657,13 @@ int launch_jvp2d_q_f32to32(ilh_ctx* c, const float* dk, float* out, const double
   return dispatch_apply<float, float>(c, dk, (const float*)c->qd[0], out, tau_dev, skip);
 }
 
+// FP64 action, tau and the skip flag from the device (same contract)
+int launch_jvp2d_q_f64(ilh_ctx* c, const double* dk, double* out, const double* tau_dev, const double* skip) {
+  if (!lin2d_supported(c)) return ILH_EINVAL;
+  if (!c->qd[1] || !c->qd_ok[1]) return fail(c, ILH_EINVAL, "linearised Jacobian action before its linearisation");
+  return dispatch_apply<double, double>(c, dk, (const double*)c->qd[1], out, tau_dev, skip);
+}
+
 bool lin2d_available(const ilh_ctx* c) { return lin2d_supported(c); }
 
 int64_t lin2d_coef_bytes(const ilh_ctx* c, int prec) {

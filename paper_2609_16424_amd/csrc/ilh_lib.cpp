@@ -325,6 +325,7 @@ void ilh_destroy(ilh_ctx* c) {
   if (c->capstream) (void)hipStreamDestroy(c->capstream);
   if (c->red_host) (void)hipHostFree(c->red_host);
   if (c->hest) (void)hipHostFree(c->hest);
+  if (c->gs_words) (void)hipFree(c->gs_words);
   delete c;
 }
 
@@ -1148,9 +1149,10 @@ static int read_pair(ilh_ctx* c, double* a, double* b) {
 // kernels read
 // (beta2 nullable: beta = sqrt(*beta2), the norm of a restart residual formed on the device; a
 // zero norm gives a zero basis vector, whose cycle then ends at its first column)
+// words: the arrival words of the cycle's one-launch steps, zeroed
 template <typename TV>
 __global__ void k_scale_copy(TV* y, const double* x, double beta_h, int64_t n, double* h, double target,
-                             double tag, double tau, const double* beta2) {
+                             double tag, double tau, const double* beta2, unsigned* words) {
   const double beta = beta2 ? sqrt(*beta2) : beta_h;
   const double f = beta > 0.0 ? 1.0 / beta : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1163,6 +1165,8 @@ __global__ void k_scale_copy(TV* y, const double* x, double beta_h, int64_t n, d
   }
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = (TV)(x[i] * f);
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < GS_STEPS * GS_STEP_WORDS; i += gridDim.x * blockDim.x)
+    words[i] = 0u;
 }
 
 // Exact diagonal blocks of the Jacobian at the current linearisation point, read off by FP32
@@ -1234,17 +1238,19 @@ struct Solver {
 
   const TV* z32_of = nullptr;  // FP64 basis: the vector whose FP32 copy is in kry32 (written by precond)
   const TV* zeroed_v = nullptr;  // the basis vector whose velocity rows precond zeroed
+  int pairs = 0;  // node pairs per thread of the one-launch Arnoldi step (0: three launches)
   bool took_direct = false;  // an action took the direct FP32 path (tau read from the device)
 
-  // FP32 linearised 2D actions write the FP64 Krylov vector directly
-  bool direct64() const { return o->jvp_prec == 32 && c->jvp_variant == 0 && lin2d_available(c); }
+  // linearised 2D actions write the Krylov vector directly (the FP32 action an FP64 vector too)
+  bool direct() const { return c->jvp_variant == 0 && lin2d_available(c); }
+  bool direct64() const { return o->jvp_prec == 32 && direct(); }
 
   int precond_body(const TV* r, TV* z, TV* next_out, const double* rs, const GivensJob* job) {
     const int64_t nh1 = c->nh1;
     int st;
     z32_of = nullptr;
     zeroed_v = nullptr;
-    TV* zv = (next_out && direct64()) ? next_out + nh1 : nullptr;
+    TV* zv = (next_out && direct()) ? next_out + nh1 : nullptr;
     const double* tdev = c->hdev + 250;  // tau on the device (set at the start of each solve)
     if (o->prec_probe) {
       float* z32 = (o->jvp_prec == 32 && !F32) ? c->kry32 : nullptr;
@@ -1372,6 +1378,26 @@ struct Solver {
       if ((st = ilh_jvp_lin(c, 32, x32, y32))) return st;
       return launch_cast_f2d(c, y, y32, c->nblock);
     }
+    if constexpr (!F32) {
+      const bool zeroed = (const void*)y == (const void*)zeroed_v;
+      zeroed_v = nullptr;
+      if (zeroed && direct()) {  // the velocity rows of y are zero already: no fill ahead of the action
+        if (!c->qd_ok[1]) {
+          const int ls = tstart_k(c, 5);
+          st = launch_lin2d(c, 64);
+          tstop_k(c, ls);
+          if (st) return st;
+          c->qd_ok[1] = true;
+        }
+        const int slot = tstart_k(c, 0);
+        st = launch_jvp2d_q_f64(c, x, y, c->hdev + 250, skip);
+        tstop_k(c, slot);
+        skippable = skip != nullptr;
+        skip_slot = slot;
+        skip_gen = c->tgen;
+        return st;
+      }
+    }
     return ilh_jvp_lin(c, 64, x, y);
   }
 
@@ -1432,12 +1458,25 @@ struct Solver {
     if (full && (st = apply_basis(Z + (int64_t)j * n, w, skip))) return st;
     const int slot = tstart(c, 3);
     int np = 0;
+    if (full && pairs > 0 && j <= lgs_step_max_j()) {
+      const bool next = j + 1 < L;  // step j + 1 applies J to z_{j+1}
+      TV* zn = next ? Z + (int64_t)(j + 1) * n : nullptr;
+      TV* out = (next && direct()) ? V + (int64_t)(j + 2) * n : nullptr;
+      float* z32 = (next && o->jvp_prec == 32 && !F32) ? c->kry32 : nullptr;
+      if ((st = lgs_step<TV>(c, pairs, V, n, j, m, hd, c->gmd, zn, z32, out, o->prec_probe, o->prec_coupled, c->gsp,
+                             c->hest_dev)))
+        return st;
+      z32_of = z32 ? zn : nullptr;
+      zeroed_v = out;
+      tstop(c, slot);
+      return ILH_OK;
+    }
     if ((st = lgs_dots<TV>(c, V, n, j, V + (int64_t)j * n, w, n, c->gsp, &np, skip))) return st;
     if ((st = lgs_final(c, c->gsp, np, j, m, full ? 1 : 0, hd, c->gmd, c->hest_dev, skip))) return st;
     if (full) {
       const bool next = j + 1 < L;  // step j + 1 applies J to z_{j+1}
       TV* zn = next ? Z + (int64_t)(j + 1) * n : nullptr;
-      TV* out = (next && direct64()) ? V + (int64_t)(j + 2) * n : nullptr;
+      TV* out = (next && direct()) ? V + (int64_t)(j + 2) * n : nullptr;
       float* z32 = (next && o->jvp_prec == 32 && !F32) ? c->kry32 : nullptr;
       if ((st = lgs_update<TV>(c, V, n, j, hd, zn, z32, out, o->prec_probe, o->prec_coupled, hd + 250, c->hest_dev,
                                hd + HDEV_LGSE)))
@@ -1467,6 +1506,8 @@ struct Solver {
     mix((uint64_t)c->apply_waves);
     mix((uint64_t)c->nblock);
     mix((uint64_t)lagged());
+    mix((uint64_t)pairs);
+    mix((uint64_t)(int64_t)c->gs_wait_us);
     return k;
   }
 
@@ -1546,6 +1587,7 @@ struct Solver {
     const double* rhs = b;
     double* rbuf = c->nwt + 3 * n;  // tmp vector
     int total = 0;
+    pairs = lagged() ? lgs_step_pairs(c, F32) : 0;
     const bool use_graph = graphable();
     if (use_graph && !c->qd_ok[0]) {  // the linearisation stays outside the captured steps
       if ((st = launch_lin2d(c, 32))) return st;
@@ -1555,8 +1597,10 @@ struct Solver {
       // V0 = r / beta (beta, the target and the cycle's tag to the device), z_0 = P V0
       const double tag = (c->est_tag += 1.0);
       hipLaunchKernelGGL(k_scale_copy<TV>, dim3(1024), dim3(256), 0, c->stream, V, rhs, beta, n, hd, target, tag,
-                         tau, beta2_dev);
+                         tau, beta2_dev, c->gs_words);
       if ((st = precond(V, Z, V + n))) return st;
+      const int calls0 = jvp_calls, total0 = total;
+      bool given_up = false;  // a one-launch step of this cycle was given up on the device
       int j_end = 0;
       bool stop = false;  // converged or out of iterations
       bool dev_end = false;  // the step's end flag is set on the device
@@ -1569,6 +1613,10 @@ struct Solver {
         auto arrived = [&]() { return est[4 * jj + 1] == tag && est[4 * jj + 3] == tag; };
         for (unsigned spins = 1; !arrived(); ++spins) {
           __builtin_ia32_pause();
+          if (est[HEST_ABORT + 1] == tag) {
+            given_up = true;
+            return ILH_OK;
+          }
           if ((spins & 1023) == 0) {
             const hipError_t q = hipStreamQuery(c->stream);
             if (q != hipSuccess && q != hipErrorNotReady) ILH_HIP(c, q);
@@ -1641,6 +1689,7 @@ struct Solver {
             ++next;
           }
           if ((st = check(col, end))) return st;
+          if (given_up) break;
           ++col;
           if (end) {
             // step col's final block ended the cycle at column col - 1; the full steps enqueued
@@ -1658,6 +1707,16 @@ struct Solver {
             break;
           }
         }
+      }
+      if (given_up) {
+        // the work-groups of a one-launch step could not meet in time (other work held the device):
+        // the launches behind it returned at once, x is as the cycle found it, and the cycle is
+        // repeated with the three launches, which this context then keeps
+        c->gs_wait_us = -1.0;
+        pairs = 0;
+        total = total0;
+        jvp_calls = calls0;
+        continue;
       }
       for (int j = 0; j < m && !end && !lagged(); ++j) {
         // step j - 1 is the last one the iteration limit allows: step j is not enqueued
@@ -1739,6 +1798,13 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
     ILH_HIP(c, hipHostGetDevicePointer((void**)&c->hest_dev, c->hest, 0));
   }
   if (!c->gmd && (st = dalloc(c, &c->gmd, 64 * 64 + 3 * 65))) return st;
+  if (!c->gs_words) {
+    int dev = 0, cus = 0;
+    ILH_HIP(c, hipGetDevice(&dev));
+    ILH_HIP(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    c->gs_cus = cus;
+    if ((st = dalloc(c, &c->gs_words, GS_STEPS * GS_STEP_WORDS))) return st;
+  }
   // The iterate k is only read: every Newton update writes a trial buffer (kA or kB), which then
   // becomes the iterate; the guess and the zero vector serve as iterates without a copy.
   double* kA = c->nwt;
@@ -1969,6 +2035,15 @@ int ilh_set_apply_waves(ilh_ctx* c, int waves) {
   if (!c) return ILH_EINVAL;
   if (waves < 0 || waves > 2) return fail(c, ILH_EINVAL, "apply waves must be 0, 1 or 2");
   c->apply_waves = waves;
+  return ILH_OK;
+  ILH_CATCH(c)
+}
+
+int ilh_set_step_wait(ilh_ctx* c, double us) {
+  ILH_TRY
+  if (!c) return ILH_EINVAL;
+  if (!(us <= 1e6)) return fail(c, ILH_EINVAL, "step wait must be at most one second");
+  c->gs_wait_us = us;
   return ILH_OK;
   ILH_CATCH(c)
 }

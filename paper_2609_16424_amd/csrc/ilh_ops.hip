@@ -11,6 +11,7 @@
 #include "ilh_internal.h"
 #include "ilh_pointwise.h"
 #include "ilh_lin.h"
+#include "ilh_lgs.h"
 
 namespace ilh {
 
@@ -404,40 +405,6 @@ __device__ __forceinline__ void tile_load(const TV* __restrict__ x, const int64_
   for (int u = 0; u < KU; ++u) v[u] = in[u] ? t[u] : 0.0;
 }
 
-// Sums of K values (K a power of two, at most 64) over the 64 lanes of a wave.  Each exchange
-// pairs lane l with l ^ mask and halves the values a lane holds (it keeps one half, adds the
-// partner's copy of that half): K - 1 + (6 - log2 K) shuffles instead of 6 K.  Afterwards every
-// lane holds in acc[0] the complete sum of the value index returned (the lanes that differ only
-// in their low 6 - log2 K bits hold the same one).
-template <int CNT, int MASK, int K>
-__device__ __forceinline__ void wave_sums_r(double (&acc)[K], int lane, int& v) {
-  if constexpr (MASK >= 1) {
-    const bool hi = (lane & MASK) != 0;
-    if constexpr (CNT > 1) {
-      constexpr int HALF = CNT / 2;
-#pragma unroll
-      for (int i = 0; i < HALF; ++i) {
-        const double send = hi ? acc[i] : acc[i + HALF];
-        const double keep = hi ? acc[i + HALF] : acc[i];
-        acc[i] = keep + __shfl_xor(send, MASK, 64);
-      }
-      if (hi) v += HALF;
-      wave_sums_r<HALF, MASK / 2, K>(acc, lane, v);
-    } else {
-      acc[0] += __shfl_xor(acc[0], MASK, 64);
-      wave_sums_r<1, MASK / 2, K>(acc, lane, v);
-    }
-  }
-}
-
-template <int K>
-__device__ __forceinline__ int wave_sums(double (&acc)[K]) {
-  static_assert(K >= 1 && K <= 64 && (K & (K - 1)) == 0, "K: a power of two up to 64");
-  int v = 0;
-  wave_sums_r<K, 32, K>(acc, (int)(threadIdx.x & 63), v);
-  return v;
-}
-
 // part[(j0 + jj) * gridDim.x + blockIdx.x] = block sum of acc[jj], jj < jn
 template <int JC>
 __device__ __forceinline__ void store_block_sums(double (&acc)[JC], int j0, int jn, double* part) {
@@ -598,16 +565,6 @@ int maxpy_multidot(ilh_ctx* c, TV* w, const TV* V, int64_t ldv, int m, const dou
 
 __device__ void givens_update(double* h, double* G, int j, int m, const double* csl, const double* snl,
                               const double* coll);
-
-// The residual estimate and h_{j+1,j} of column j to host memory (mapped, coherent) as two 16-byte
-// records {estimate, tag} and {h_{j+1,j}, tag}: each record is one store, so the host never pairs
-// a new tag with an old value whatever order the two stores become visible in
-__device__ __forceinline__ void publish_estimate(double* hest, int j, double est, double hn, double tag) {
-  double2* rec = reinterpret_cast<double2*>(hest + 4 * j);
-  rec[0] = make_double2(est, tag);
-  rec[1] = make_double2(hn, tag);
-  __threadfence_system();
-}
 
 // final sum of the norm partials into h[144], the Givens update of Arnoldi step j, and the
 // scale of the next basis vector, h[256 + j + 1] = 1 / |w| (1 for a zero or non-finite norm:
@@ -1028,8 +985,8 @@ __global__ void __launch_bounds__(LGS_FT) k_lgs_final(const double* __restrict__
   const int ns = 2 * (j + 1) + (has_w ? 1 : 0);
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   constexpr int NW = LGS_FT / 64;
-  double* cs = G + 64 * 64;
-  double* g = cs + 128;
+  const double* cs = G + 64 * 64;
+  const double* g = cs + 128;
   // every scalar the serial part needs is staged into LDS first, by other threads, so that its
   // chain reads no global memory.  The staged values are loaded by every lane of waves 0, 2 and 3
   // (two loads each, addresses chosen per lane, a harmless address elsewhere) before the partial
@@ -1097,62 +1054,8 @@ __global__ void __launch_bounds__(LGS_FT) k_lgs_final(const double* __restrict__
   if (t >= 192 && t < 198) sc[q] = ((q == 0 && j < 1) || (q == 5 && !skip)) ? 0.0 : va;
   __syncthreads();
   if (sc[5] != 0.0 || t != 0) return;
-  double aa = 0.0, ab = 0.0;
-  for (int k = 0; k < j; ++k) {
-    aa += S[2 * k] * S[2 * k];
-    ab += S[2 * k] * S[2 * k + 1];
-  }
-  double rho = 1.0, flag = 0.0;
-  if (j > 0) {
-    const double r2 = S[2 * j] - aa;
-    rho = (r2 == r2) ? sqrt(fmax(r2, 0.0)) : r2;
-    const double gs = sc[4];  // 1 / s_j
-    for (int k = 0; k < j; ++k) coll[k] = pl[k] + S[2 * k] * gs;
-    const double hn = rho * gs;
-    // Givens update of column jc = j - 1 (as givens_col, every operand from LDS)
-    const int jc = j - 1;
-    double* Hm = G;
-    double cur = coll[0];
-    for (int i = 0; i < jc; ++i) {
-      const double nx = coll[i + 1];
-      Hm[i * 64 + jc] = csl[i] * cur + snl[i] * nx;
-      cur = -snl[i] * cur + csl[i] * nx;
-    }
-    const double den = hypot(cur, hn);
-    const double c_ = den > 0 ? cur / den : 1.0, s_ = den > 0 ? hn / den : 0.0;
-    cs[jc] = c_;
-    cs[64 + jc] = s_;
-    Hm[jc * 64 + jc] = den;
-    const double gj = jc == 0 ? sc[1] : sc[0];
-    if (jc == 0)
-      for (int i = 2; i <= m; ++i) g[i] = 0.0;
-    g[jc] = c_ * gj;
-    g[jc + 1] = -s_ * gj;
-    const double est = fabs(s_ * gj);
-    h[352 + 2 * jc] = est;
-    h[353 + 2 * jc] = hn;
-    flag = (est <= sc[2] || hn == 0.0) ? 1.0 : 0.0;
-    if (hest && !has_w) {  // a full step's update sweep publishes it (first block)
-      publish_estimate(hest, jc, est, hn, sc[3]);
-    }
-  }
-  if (flag != 0.0) h[HDEV_LGSE] = j + 1;
-  if (!has_w) return;
-  const double rinv = (rho > 0.0 && rho <= 1.7e308) ? 1.0 / rho : 0.0;
-  const double d = j > 0 ? (S[2 * j + 1] - ab) * rinv : S[1];
-  double* p = h + HDEV_LGSP;
-  for (int k = 0; k < j; ++k) {
-    h[k] = S[2 * k];
-    h[72 + k] = S[2 * k + 1];
-    p[k] = S[2 * k + 1];
-  }
-  p[j] = d;
-  const double wn = sqrt(fmax(S[2 * j + 2], 0.0));
-  const bool ok = wn > 0.0 && wn <= 1.7e308;
-  p[65] = ok ? wn : 1.0;
-  h[144] = j > 0 ? rinv : 1.0;
-  h[145] = d;
-  h[146] = ok ? 1.0 / wn : 1.0;
+  // (a full step's update sweep publishes the estimate, from its first block)
+  lgs_column(S, j, m, has_w, csl, snl, coll, pl, sc, h, G, hest, !has_w);
 }
 
 // A[r] = sum_{k < m} a_k V_k[rows[r]], B[r] likewise with b (FP64 sums of the stored basis)
@@ -1204,20 +1107,6 @@ __device__ __forceinline__ void combo_ab_n(const TV* __restrict__ V, int64_t ldv
       B[r] += cb * (double)v[k][r];
     }
   }
-}
-
-// one row of the update from its loaded u_j and w: v_j (stored back when j > 0) and u_{j+1}
-// (scaled by sg, stored over w); returns the stored u_{j+1}
-template <typename TV>
-__device__ __forceinline__ double lgs_row(TV* uj, TV* w, int64_t row, bool in, int j, double uv, double wv, double A,
-                                          double B, double rinv, double d, double sg) {
-  const TV vj = j > 0 ? (TV)((uv - A) * rinv) : (TV)uv;
-  const TV un = (TV)(sg * (wv - B - d * (double)vj));
-  if (in) {
-    if (j > 0) uj[row] = vj;
-    w[row] = un;
-  }
-  return (double)un;
 }
 
 static constexpr int LGS_NU = 2;  // node pairs (position row, velocity row) per thread
