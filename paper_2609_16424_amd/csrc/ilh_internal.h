@@ -123,7 +123,13 @@ struct ilh_ctx {
   double* pgb = nullptr;        // plain-guess fallback: candidate and residual [2][nblock] (first use)
   double* pdv = nullptr;        // probed diagonal of the velocity block [nh1]
   double* peinv = nullptr;      // inverted probed energy blocks [Ne][Nl][Nl]
-  double* rkw = nullptr;        // explicit RK2-average workspace [2 nblock] (allocated on first use)
+  double* rkw = nullptr;        // explicit RK2-average workspace [4 nblock] (allocated on first use)
+  bool rkw_zero = false;        // its zero block is filled and the velocity rows of its residual are zero
+  double rj0_one = 0.0;         // rho0 |J0| when every element has the same (affine initial mesh), else 0
+  double* tm_w[3][2] = {};      // 1D inverse mass bands: per direction, without and with held ends (first use)
+  int tm_bw[3][2] = {};         // and their half bandwidths
+  double* tm_tmp = nullptr;     // [2][nh1] vectors between the passes of the direct mass solve
+  bool tm_ok = false;
   double* sdk = nullptr;        // SDIRK stage rates and stage base [4][nblock] (allocated on first use)
   double* nwt = nullptr;        // Newton vectors: k, r, dk, tmp, zero, w [6][nblock]
   float* kry32 = nullptr;       // z32, w32 [2][nblock]
@@ -252,7 +258,6 @@ int launch_cast_f2d(ilh_ctx* c, double* y, const float* x, int64_t n);
 int launch_mass_v(ilh_ctx* c, const double* x, double* y, int zero_first);
 int launch_mass_e_inv(ilh_ctx* c, const double* b, double* x);
 int launch_jacobi(ilh_ctx* c, const double* r, double* z);   // z = r / Mdiag
-int launch_scale_free(ilh_ctx* c, double* y, double a, const double* x);  // H1: y = a x, constrained rows 0
 // reductions: dot products of n-length vectors, result on host (synchronizes)
 int dot_host(ilh_ctx* c, const double* x, const double* y, int64_t n, double* out);
 // device-side dot into d_out (no sync)
@@ -402,6 +407,30 @@ int init_state_dev(ilh_ctx* c, double* u, const double* rhs_l2);
 // residual is tested on the host every `check` iterations.
 int pcg_mass_v(ilh_ctx* c, const double* b, double* x, double rtol, int maxit, int check,
                int* iters, double* relres);
+
+// Direct solve of the velocity-mass system where rho0 |J0| is one number (ilh_tensor.hip):
+// a = sign Mhat^-1 b on free rows and cons b on constrained ones, to a (nullable); zero (nullable)
+// is cleared entry by entry; with v, vm = v + dv a, xo = x + dx vm and, with vo, vo = v + dvo a (vo may
+// be v and xo may be x).  b is read again for constrained rows by the last pass: it is not a and not
+// zero unless cons = 0.
+struct MassOut {
+  const double* b = nullptr;
+  double sign = 1.0, cons = 1.0;
+  double* a = nullptr;
+  double* zero = nullptr;
+  const double* v = nullptr;
+  double* vm = nullptr;
+  double dv = 0.0;
+  const double* x = nullptr;
+  double* xo = nullptr;
+  double dx = 0.0;
+  double* vo = nullptr;
+  double dvo = 0.0;
+};
+bool tensor_mass_available(const ilh_ctx* c);
+int tensor_mass_solve(ilh_ctx* c, const MassOut& mo);
+// y = s M_E^-1 b, added to x when x is given (y may be x)
+int launch_mass_e_axpy(ilh_ctx* c, const double* b, const double* x, double s, double* y);
 
 // MLP and guess (ilh_mlp.hip)
 int guess_features(ilh_ctx* c, const double* u, double vs, double es, double xs, float* f, int nin);

@@ -139,29 +139,6 @@ int launch_cast_d2f(ilh_ctx* c, float* y, const double* x, int64_t n, double* z,
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
-// y = a x on the free rows of an H1 vector, 0 on the constrained (wall) rows
-__global__ void k_scale_free(double* y, double a, const double* x, KParams P) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.dim * P.N) return;
-  const int c = (int)(i / P.N);
-  int64_t node = i - (int64_t)c * P.N;
-  int64_t g = node % P.ng[0];
-  if (c >= 1) {
-    node /= P.ng[0];
-    g = node % P.ng[1];
-  }
-  if (c == 2) g = node / P.ng[1];
-  const bool cons = on_wall(P.walls, c, g, P.ng[c]);
-  y[i] = cons ? 0.0 : a * x[i];
-}
-
-int launch_scale_free(ilh_ctx* c, double* y, double a, const double* x) {
-  const int64_t n = c->nh1;
-  hipLaunchKernelGGL(k_scale_free, dim3(nblk(n)), dim3(TPB), 0, c->stream, y, a, x, c->kp);
-  ILH_HIP(c, hipGetLastError());
-  return ILH_OK;
-}
-
 int launch_cast_f2d(ilh_ctx* c, double* y, const float* x, int64_t n) {
   if (n <= 0) return ILH_OK;
   hipLaunchKernelGGL(k_f2d, dim3(nblk(n)), dim3(TPB), 0, c->stream, y, x, n);
@@ -1834,8 +1811,9 @@ int launch_mass_v(ilh_ctx* c, const double* x, double* y, int bc) { return mass_
 // x_e = scale_e Minv_e b_e with Minv_e = Minv + e * stride (stride 0: one reference inverse for
 // every element of an affine initial mesh, scaled by 1 / (rho0 |J0|)_e; stride Nl^2: per-element
 // inverses of a curved initial mesh, scale nullptr)
+// (a: the result times a; base nullable: added to it)
 __global__ void k_me_inv(const double* Minv, int64_t stride, const double* scale, const double* b, double* x,
-                         int64_t Ne, int Nl) {
+                         int64_t Ne, int Nl, double a, const double* base) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= Ne * Nl) return;
   const int64_t e = i / Nl;
@@ -1843,16 +1821,18 @@ __global__ void k_me_inv(const double* Minv, int64_t stride, const double* scale
   const double* Me = Minv + e * stride;
   double acc = 0;
   for (int j = 0; j < Nl; ++j) acc += Me[r * Nl + j] * b[e * Nl + j];
-  x[i] = scale ? scale[e] * acc : acc;
+  if (scale) acc *= scale[e];
+  x[i] = base ? base[i] + a * acc : a * acc;
 }
-int launch_mass_e_inv(ilh_ctx* c, const double* b, double* x) {
+int launch_mass_e_axpy(ilh_ctx* c, const double* b, const double* x, double s, double* y) {
   const int64_t n = c->Ne * c->Nl;
   if (n == 0) return ILH_OK;
   hipLaunchKernelGGL(k_me_inv, dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, c->stream, c->MEinv,
-                     c->me_stride, c->me_scale, b, x, c->Ne, c->Nl);
+                     c->me_stride, c->me_scale, b, y, c->Ne, c->Nl, s, x);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
+int launch_mass_e_inv(ilh_ctx* c, const double* b, double* x) { return launch_mass_e_axpy(c, b, nullptr, 1.0, x); }
 
 // ------------------------------------------------------------------ device-scalar PCG
 // scalars s[0] = rz, s[1] = pAp, s[2] = rz_new, s[3] = bb, s[4] = rr

@@ -1,0 +1,241 @@
+// Direct velocity-mass solve on an affine initial mesh with one density.
+//
+// With rho0 |J0| the same in every element, M_V is (rho0 |J0|) times the tensor product of the 1D mass
+// matrices of the directions, and the eliminated operator Mhat = P_u M_V P_u + P_c keeps that form per
+// component: component c is held on wall faces normal to direction c, whole lines of its nodes, so
+// the 1D matrix of direction c loses those end rows and the others none.  Its inverse is the tensor
+// product of the 1D inverses.  A 1D inverse is dense, but its entries fall off exponentially (the 1D
+// condition number is 4 to 16): beyond 29 to 68 nodes (k = 1 to 4) they are below 1e-17 of the largest,
+// less than the rounding of the result.  So the solve is one banded product along each direction,
+// exact to rounding, where conjugate gradients took some 20 iterations of nine launches.
+//
+// The product along a direction is a band matrix times the matrix of all lines, so it runs on the FP64
+// matrix instructions: a wave makes a tile of 16 nodes by 16 lines from (16 + 2 bw) / 4 multiplies of
+// 16x16x4, its weights packed in the operand's lane order.  What bounds it: on small meshes the
+// launches and the round trips to memory (all of a tile's operands are requested 16 multiplies ahead;
+// a first form with one lane per node, weights and lines through the caches and LDS, took 13 us a pass at
+// 49 x 49 nodes against 5 and 8 now), on large ones the multiplies, about 2 (16 + 2 bw) flop per node and
+// direction against 16 bytes moved.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+#include "ilh_internal.h"
+
+namespace ilh {
+
+static constexpr int TM_W = 4;   // waves per work-group
+static constexpr int TM_U = 16;  // multiplies whose operands are in flight together
+
+// The 1D inverse mass matrix on the n k + 1 nodes of a direction, scaled by `scale`, as rows of
+// 2 bw + 1 band entries (row i, offset o: column i + o - bw); with lo / hi, the end node is held (its
+// row and column zero).  Banded Cholesky (half bandwidth k) in extended precision, so that the weights
+// are the inverse's entries rounded once, then every column by substitution over
+// a window wide enough that what it leaves out is below 1e-25.
+static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool hi, double scale, int* bw_out) {
+  const int k = c->k, n1 = n * k + 1, D1D = k + 1, Q1D = 2 * k;
+  std::vector<long double> m(D1D * D1D, 0.0L), A((size_t)n1 * D1D, 0.0L);  // A[i][k + j - i], j <= i
+  for (int a = 0; a < D1D; ++a)
+    for (int b = 0; b < D1D; ++b)
+      for (int q = 0; q < Q1D; ++q) m[a * D1D + b] += (long double)c->h_w1[q] * c->h_B[q * D1D + a] * c->h_B[q * D1D + b];
+  for (int e = 0; e < n; ++e)
+    for (int a = 0; a < D1D; ++a)
+      for (int b = 0; b <= a; ++b) A[(size_t)(e * k + a) * D1D + k + b - a] += m[a * D1D + b];
+  auto hold = [&](int i) {
+    for (int o = 0; o < k; ++o) A[(size_t)i * D1D + o] = 0.0;
+    A[(size_t)i * D1D + k] = 1.0;
+    for (int j = i + 1; j <= std::min(n1 - 1, i + k); ++j) A[(size_t)j * D1D + k + i - j] = 0.0;
+  };
+  if (lo) hold(0);
+  if (hi) hold(n1 - 1);
+  for (int i = 0; i < n1; ++i)  // A = L L^T in place
+    for (int j = std::max(0, i - k); j <= i; ++j) {
+      long double s = A[(size_t)i * D1D + k + j - i];
+      for (int p = std::max(0, i - k); p < j; ++p)
+        if (j - p <= k) s -= A[(size_t)i * D1D + k + p - i] * A[(size_t)j * D1D + k + p - j];
+      A[(size_t)i * D1D + k + j - i] = j == i ? std::sqrt(s) : s / A[(size_t)j * D1D + k];
+    }
+  const int win = 160;
+  std::vector<double> B((size_t)n1 * (2 * win + 1), 0.0);
+  std::vector<long double> y(n1, 0.0L);
+  const int far = win + 64;  // beyond it from both ends the columns repeat with the elements' period k
+  for (int j = 0; j < n1; ++j) {
+    const int i0 = std::max(0, j - win), i1 = std::min(n1 - 1, j + win);
+    if (j >= far + k && j < n1 - far) {
+      for (int i = i0; i <= i1; ++i)
+        B[(size_t)i * (2 * win + 1) + win + j - i] = B[(size_t)(i - k) * (2 * win + 1) + win + j - i];
+      continue;
+    }
+    for (int i = j; i <= i1; ++i) {
+      long double s = i == j ? 1.0L : 0.0L;
+      for (int p = std::max(j, i - k); p < i; ++p) s -= A[(size_t)i * D1D + k + p - i] * y[p];
+      y[i] = s / A[(size_t)i * D1D + k];
+    }
+    for (int i = i1; i >= i0; --i) {
+      long double s = i >= j ? y[i] : 0.0L;
+      for (int p = i + 1; p <= std::min(i1, i + k); ++p) s -= A[(size_t)p * D1D + k + i - p] * y[p];
+      y[i] = s / A[(size_t)i * D1D + k];
+    }
+    const bool held = (lo && j == 0) || (hi && j == n1 - 1);
+    for (int i = i0; i <= i1; ++i) B[(size_t)i * (2 * win + 1) + win + j - i] = held ? 0.0 : (double)(scale * y[i]);
+  }
+  double top = 0.0;
+  for (double v : B) top = std::max(top, std::fabs(v));
+  int bw = 0;
+  for (int i = 0; i < n1; ++i)
+    for (int o = 0; o <= 2 * win; ++o)
+      if (std::fabs(B[(size_t)i * (2 * win + 1) + o]) > 1e-18 * top) bw = std::max(bw, std::abs(o - win));
+  std::vector<double> W((size_t)n1 * (2 * bw + 1));
+  for (int i = 0; i < n1; ++i)
+    for (int o = 0; o <= 2 * bw; ++o) W[(size_t)i * (2 * bw + 1) + o] = B[(size_t)i * (2 * win + 1) + win - bw + o];
+  *bw_out = bw;
+  return W;
+}
+
+// (the extent keeps the weights' set-up small and the grids within their limits)
+bool tensor_mass_available(const ilh_ctx* c) {
+  if (!(c->rj0_one > 0.0)) return false;
+  for (int d = 0; d < c->dim; ++d)
+    if (c->ng[d] > 16384) return false;
+  return c->dim == 2 || (int64_t)((c->ng[1] + 15) / 16) * c->ng[2] <= 65535;
+}
+
+// The weights on the device, on first use: per direction, without and with held ends, row tile by row
+// tile in the order of the multiplies' first operand: lane l of multiply t of tile i0 / 16 holds row
+// i0 + l mod 16, column i0 - bw + 4 t + l / 16 (zero outside the band and the matrix).
+// 1 / (rho0 |J0|) is folded into direction 0.
+static int tensor_setup(ilh_ctx* c) {
+  if (c->tm_ok) return ILH_OK;
+  for (int d = 0; d < c->dim; ++d)
+    for (int held = 0; held < 2; ++held) {
+      const bool lo = held && ((c->kp.walls >> (2 * d)) & 1), hi = held && ((c->kp.walls >> (2 * d + 1)) & 1);
+      int bw = 0;
+      const std::vector<double> W = inverse_band(c, c->n[d], lo, hi, d == 0 ? 1.0 / c->rj0_one : 1.0, &bw);
+      const int n1 = c->ng[d], nb = 2 * bw + 1, tiles = (n1 + 15) / 16, nt = (16 + 2 * bw + 3) / 4;
+      std::vector<double> P((size_t)tiles * nt * 64, 0.0);
+      for (int b = 0; b < tiles; ++b)
+        for (int t = 0; t < nt; ++t)
+          for (int l = 0; l < 64; ++l) {
+            const int i = 16 * b + l % 16, col = 16 * b - bw + 4 * t + l / 16, o = col - i + bw;
+            if (i < n1 && col >= 0 && col < n1 && o >= 0 && o < nb)
+              P[((size_t)b * nt + t) * 64 + l] = W[(size_t)i * nb + o];
+          }
+      double*& dst = c->tm_w[d][held];
+      if (!dst) ILH_HIP(c, hipMalloc((void**)&dst, P.size() * sizeof(double)));
+      ILH_HIP(c, hipMemcpy(dst, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice));
+      c->tm_bw[d][held] = bw;
+    }
+  if (!c->tm_tmp) ILH_HIP(c, hipMalloc((void**)&c->tm_tmp, 2 * (size_t)c->nh1 * sizeof(double)));
+  c->tm_ok = true;
+  return ILH_OK;
+}
+
+struct TensorW {
+  const double* w[3];  // per component
+  int bw[3];
+};
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// One direction (n1 nodes at stride sn) of every component (grid.z): lines at stride 1 within
+// `inner` of them (direction d >= 1, outer blocks of n1 * inner entries), or at stride n1 (FIRST:
+// direction 0).  A wave takes 16 nodes (row tile) of 16 lines; the waves of a group take
+// neighbouring row tiles of the same lines (FIRST: a line's entries are read by all of them) or
+// neighbouring lines of one row tile (the weights are).  LAST: the solution's entries go through the
+// epilogue of MassOut instead of to out.
+template <bool FIRST, bool LAST>
+__global__ void __launch_bounds__(64 * TM_W) k_tensor(const double* __restrict__ in, double* __restrict__ out,
+                                                      const TensorW tw, int n1, int64_t lines, int64_t N,
+                                                      const KParams P, const MassOut mo) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int tiles = (n1 + 15) / 16, c = blockIdx.z, bw = tw.bw[c], nt = (16 + 2 * bw + 3) / 4;
+  int tile, ot = 0;
+  int64_t l0;
+  if constexpr (FIRST) {
+    tile = blockIdx.y * TM_W + wid;
+    l0 = (int64_t)blockIdx.x * 16;
+  } else {
+    ot = blockIdx.y / tiles;
+    tile = blockIdx.y - ot * tiles;
+    l0 = ((int64_t)blockIdx.x * TM_W + wid) * 16;
+  }
+  if (tile >= tiles || l0 >= lines) return;
+  const int i0 = 16 * tile, ln = lane & 15, lk = lane >> 4;
+  const bool have = l0 + ln < lines;
+  const int64_t line = have ? l0 + ln : lines - 1;
+  const int64_t sn = FIRST ? 1 : lines;
+  const int64_t base = c * N + (FIRST ? line * n1 : (int64_t)ot * n1 * lines + line);
+  const double* w = tw.w[c] + (int64_t)tile * nt * 64 + lane;
+  const int r0 = i0 - bw + lk;
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int t0 = 0; t0 < nt; t0 += TM_U) {
+    double a[TM_U], b[TM_U];
+#pragma unroll
+    for (int q = 0; q < TM_U; ++q) {
+      const int t = min(t0 + q, nt - 1);
+      a[q] = w[t * 64];
+      b[q] = in[base + (int64_t)min(max(r0 + 4 * t, 0), n1 - 1) * sn];
+    }
+#pragma unroll
+    for (int q = 0; q < TM_U; ++q)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t0 + q < nt ? a[q] : 0.0, b[q], acc, 0, 0, 0);
+  }
+  if (!have) return;
+  // grid index of the line along direction c of the last pass (c below the pass's direction)
+  const uint32_t l32 = (uint32_t)line, ng0 = P.ng[0];
+  const int gl = P.dim == 2 ? (int)l32 : c == 0 ? (int)(l32 % ng0) : (int)(l32 / ng0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {  // lane l holds rows l / 16 + 4 q of line l mod 16
+    const int j = i0 + lk + 4 * q;
+    if (j >= n1) break;
+    const int64_t g = base + (int64_t)j * sn;
+    if constexpr (!LAST) {
+      out[g] = acc[q];
+    } else {
+      const bool cons = on_wall(P.walls, c, c == P.dim - 1 ? j : gl, P.ng[c]);
+      const double s = !cons ? mo.sign * acc[q] : mo.cons != 0.0 ? mo.cons * mo.b[g] : 0.0;
+      if (mo.a) mo.a[g] = s;
+      if (mo.zero) mo.zero[g] = 0.0;
+      if (mo.v) {
+        const double v = mo.v[g], vm = v + mo.dv * s;
+        mo.vm[g] = vm;
+        mo.xo[g] = mo.x[g] + mo.dx * vm;
+        if (mo.vo) mo.vo[g] = v + mo.dvo * s;
+      }
+    }
+  }
+}
+
+int tensor_mass_solve(ilh_ctx* c, const MassOut& mo) {
+  int st = tensor_setup(c);
+  if (st) return st;
+  const int D = c->dim;
+  const double* src = mo.b;
+  for (int d = 0; d < D; ++d) {
+    TensorW tw{};
+    for (int k = 0; k < D; ++k) {
+      tw.w[k] = c->tm_w[d][k == d ? 1 : 0];
+      tw.bw[k] = c->tm_bw[d][k == d ? 1 : 0];
+    }
+    const int n1 = c->ng[d];
+    const unsigned tiles = (n1 + 15) / 16;
+    double* dst = c->tm_tmp + (int64_t)(d & 1) * c->nh1;
+    if (d == 0) {
+      const int64_t lines = c->N / n1;
+      hipLaunchKernelGGL((k_tensor<true, false>), dim3((unsigned)((lines + 15) / 16), (tiles + TM_W - 1) / TM_W, D),
+                         dim3(64 * TM_W), 0, c->stream, src, dst, tw, n1, lines, c->N, c->kp, mo);
+    } else {
+      const int64_t inner = d == 1 ? c->ng[0] : (int64_t)c->ng[0] * c->ng[1], outer = c->N / (inner * n1);
+      const dim3 grid((unsigned)((inner + 16 * TM_W - 1) / (16 * TM_W)), (unsigned)(tiles * outer), D);
+      auto f = d == D - 1 ? k_tensor<false, true> : k_tensor<false, false>;
+      hipLaunchKernelGGL(f, grid, dim3(64 * TM_W), 0, c->stream, src, dst, tw, n1, inner, c->N, c->kp, mo);
+    }
+    src = dst;
+  }
+  ILH_HIP(c, hipGetLastError());
+  return ILH_OK;
+}
+
+}  // namespace ilh
