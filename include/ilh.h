@@ -134,7 +134,7 @@ int ilh_force_jvp(ilh_ctx* ctx, int prec, const double* w, const void* dw, void*
  *   R_x = k_x - w_v
  *   R_v = M_V k_v + F(w) 1          (constrained rows: R_v = k_v)
  *   R_e = M_E k_e - F(w)^T w_v - b(w_x)   (b: TG energy source, else 0).
- * 2D (k = 2, 3) and 3D (k = 2, no TG source): strip kernels on the lane maps of the linearised
+ * 2D (k = 1 to 4) and 3D (k = 2, no TG source): strip kernels on the lane maps of the linearised
  * kernels (unless kernel variant 1 is selected); otherwise the generic element kernel. */
 int ilh_residual(ilh_ctx* ctx, const double* k, const double* u, double tau, double* r);
 
@@ -152,7 +152,7 @@ int ilh_linearize(ilh_ctx* ctx, const double* k, const double* u, double tau);
  * linearised variant applies FP64-evaluated coefficients rounded to FP32; the recomputing
  * variants read positions in FP64 and make them element-relative before rounding).  The first
  * call of a precision after ilh_linearize evaluates and stores that precision's tangent
- * coefficients (linearised variant: 2D, k = 2, 3, 12 to 18 values per quadrature point;
+ * coefficients (linearised variant: 2D, 12 to 18 values per quadrature point;
  * 3D, k = 2, 20 or 29; allocated on first use and kept until ilh_destroy). */
 int ilh_jvp_lin(ilh_ctx* ctx, int prec, const void* dk, void* jdk);
 
@@ -396,7 +396,7 @@ int ilh_set_viscosity_scale(ilh_ctx* ctx, int mode, double width);
  * time in milliseconds and the number of timed launches (host arrays of ILH_TIMING_CLASSES). */
 #define ILH_TIMING_CLASSES 7
 /* Select the Jacobian-action kernels (all compute the same operator, for cross-checking):
- *   0 (default) linearised: where one exists (2D, k = 2, 3; 3D, k = 2 without the TG
+ *   0 (default) linearised: where one exists (2D; 3D, k = 2 without the TG
  *     source), the tangent coefficients of every quadrature point are evaluated once per
  *     linearisation point and precision (FP64 arithmetic, stored in the precision of the
  *     action) and each action applies them;

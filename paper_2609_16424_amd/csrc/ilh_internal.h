@@ -228,7 +228,7 @@ inline void klaunch(ilh_ctx* c, F kernel, dim3 grid, dim3 block, uint32_t shm, A
 int launch_elem(ilh_ctx* c, int mode, int prec, const EArgs<double>* a64, const EArgs<float>* a32);
 // register-resident 2D Jacobian action (k = 2, 3); ILH_EINVAL when not specialised
 int launch_jvp2d(ilh_ctx* c, int prec, const EArgs<double>* a64, const EArgs<float>* a32);
-// linearised 2D Jacobian action (k = 2, 3): coefficients at (w64, lin_tau), then apply
+// linearised 2D Jacobian action : coefficients at (w64, lin_tau), then apply
 bool lin2d_available(const ilh_ctx* c);
 int launch_lin2d(ilh_ctx* c, int prec);
 int launch_jvp2d_q(ilh_ctx* c, int prec, const void* dk, void* out);
@@ -383,7 +383,7 @@ int launch_jvp2d_q_f32to64(ilh_ctx* c, const float* dk, double* out, const doubl
                            const double* skip = nullptr);
 int launch_jvp2d_q_f32to32(ilh_ctx* c, const float* dk, float* out, const double* tau_dev,
                            const double* skip = nullptr);
-// Stage residual on the strip lane maps (2D k = 2, 3; 3D k = 2 without the TG source):
+// Stage residual on the strip lane maps (2D; 3D k = 2 without the TG source):
 // r = R(k; u, tau), the velocity rows of r zero on entry
 bool res2d_available(const ilh_ctx* c);
 // dmin (nullable, res2d_groups(c) entries): each work-group's smallest det J over its quadrature

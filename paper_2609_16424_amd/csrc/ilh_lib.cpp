@@ -905,14 +905,24 @@ int ilh_jvp_noalloc(ilh_ctx* c, int prec, const double* k, const double* u, doub
   // scratch layout: w = u + tau k (FP64) | FP32 shadow of w (recomputing kernels) or the tangent
   // coefficients of precision prec (linearised kernels), each part 256-byte aligned
   auto al = [](int64_t b) { return (b + 255) / 256 * 256; };
-  const bool lin = c->jvp_variant == 0 && (lin2d_available(c) || lin3d_available(c));
+  bool lin = c->jvp_variant == 0 && (lin2d_available(c) || lin3d_available(c));
   const int64_t off1 = al(c->nblock * 8);
+  // orders 1 and 4 whose tangent coefficients the scratch does not hold run on the element kernels, which
+  // need the FP32 shadow only
+  const int variant = c->jvp_variant;
+  if (lin && c->dim == 2 && (c->k == 1 || c->k == 4) &&
+      off1 + al(lin2d_coef_bytes(c, prec)) > (int64_t)ILH_NOALLOC_SCRATCH_BYTES) {
+    lin = false;
+    c->jvp_variant = 1;
+  }
   const int64_t part2 = lin ? (c->dim == 3 ? lin3d_coef_bytes(c, prec) : lin2d_coef_bytes(c, prec)) : c->nblock * 4;
   const int64_t need = off1 + al(part2);
-  if (need > (int64_t)ILH_NOALLOC_SCRATCH_BYTES)
+  if (need > (int64_t)ILH_NOALLOC_SCRATCH_BYTES) {
+    c->jvp_variant = variant;
     return fail(c, ILH_EINVAL, "ilh_jvp_noalloc: this mesh needs " + std::to_string(need) +
                                    " bytes of scratch, the static array holds " +
                                    std::to_string((long long)ILH_NOALLOC_SCRATCH_BYTES));
+  }
   unsigned char* base = (unsigned char*)c->scratch;
   const int p = prec == 64 ? 1 : 0;
   // run ilh_jvp on the scratch buffers in place of the context's own, then restore the context's
@@ -928,6 +938,7 @@ int ilh_jvp_noalloc(ilh_ctx* c, int prec, const double* k, const double* u, doub
   else
     c->w32 = (float*)(base + off1);
   const int st = ilh_jvp(c, prec, k, u, tau, dk, jdk);
+  c->jvp_variant = variant;
   c->w64 = w64;
   c->w32 = w32;
   c->qd[p] = qd;
@@ -943,7 +954,7 @@ int ilh_vjp_lin(ilh_ctx* c, int prec, const void* y, void* jty) {
   if (!c || !y || !jty) return ILH_EINVAL;
   if (prec != 32 && prec != 64) return fail(c, ILH_EINVAL, "prec must be 32 or 64");
   const bool d3 = c->dim == 3;
-  if (!(d3 ? lin3d_available(c) : lin2d_available(c)))
+  if (!(d3 ? lin3d_available(c) : lin2d_available(c) && (c->k == 2 || c->k == 3)))
     return fail(c, ILH_EINVAL, "the transpose action is built for 2D meshes with k = 2, 3 and 3D with k = 2");
   int st;
   if (prec == 64) {

@@ -1,6 +1,6 @@
 // Stage residual (Sec. 4: R(k) of the implicit stage, with the mass-multiplied rows of the
 // block preconditioner's reading) on the work-group / lane maps of the linearised kernels.
-// 2D (k = 2, 3): one wave = EPW consecutive elements of one element row, lane (z, qx) =
+// 2D: one wave = EPW consecutive elements of one element row, lane (z, qx) =
 // quadrature column qx of element z, walking the Q1D quadrature rows.  3D (Q2Q1, no TG source):
 // see k_res3d.  FP64 throughout; the artificial viscosity enters through qp_force.
 //
@@ -28,7 +28,7 @@ __device__ __forceinline__ double tg_source_c(double x, double y, double gam) {
 }
 
 template <int D1D, int Q1D, int SRC>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D1D == 5 ? 1 : 2)))
 k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restrict__ u,
         const double* __restrict__ kk1, double tau, double* __restrict__ r1, double* __restrict__ dmin1,
         const double* __restrict__ kk2, double* __restrict__ r2) {
@@ -632,7 +632,7 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 
 // ---- host side ---------------------------------------------------------------------------
 bool res2d_available(const ilh_ctx* c) {
-  return c->dim == 2 && (c->k == 2 || c->k == 3) && c->nblock < (int64_t(1) << 28) && !c->general;
+  return c->dim == 2 && c->nblock < (int64_t(1) << 28) && !c->general;
 }
 
 bool res3d_available(const ilh_ctx* c) {
@@ -693,10 +693,14 @@ int launch_res2d(ilh_ctx* c, const double* k, const double* u, double tau, doubl
     return fail(c, ILH_EINVAL, "residual pair: both or neither of k2, r2; distinct outputs; no det J");
   const int code = 2 * c->k + (c->kp.tg_source ? 1 : 0);
   switch (code) {
+    case 2: res_t<1, 0>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 3: res_t<1, 1>(c, k, u, tau, r, dmin, k2, r2); break;
     case 4: res_t<2, 0>(c, k, u, tau, r, dmin, k2, r2); break;
     case 5: res_t<2, 1>(c, k, u, tau, r, dmin, k2, r2); break;
     case 6: res_t<3, 0>(c, k, u, tau, r, dmin, k2, r2); break;
     case 7: res_t<3, 1>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 8: res_t<4, 0>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 9: res_t<4, 1>(c, k, u, tau, r, dmin, k2, r2); break;
     default: return ILH_EINVAL;
   }
   ILH_HIP(c, hipGetLastError());
