@@ -117,7 +117,7 @@ struct ilh_ctx {
   // Krylov / Newton workspace (allocated on first use)
   int kry_m = 0;
   double* kry = nullptr;        // V [(m+1)][nblock], Z [m][nblock]
-  float* gscr = nullptr;        // learned-guess features and activations (allocated on first use)
+  float* gscr = nullptr;        // learned-guess features and activations, training scratch (allocated on first use)
   int64_t gscr_len = 0;
   double* gres = nullptr;       // learned-guess judge residual [nblock]
   double* pgb = nullptr;        // plain-guess fallback: candidate and residual [2][nblock] (first use)
@@ -431,6 +431,9 @@ bool tensor_mass_available(const ilh_ctx* c);
 int tensor_mass_solve(ilh_ctx* c, const MassOut& mo);
 // y = s M_E^-1 b, added to x when x is given (y may be x)
 int launch_mass_e_axpy(ilh_ctx* c, const double* b, const double* x, double s, double* y);
+
+// the learned guess's scratch holds at least `need` floats afterwards
+int ensure_gscr(ilh_ctx* c, int64_t need);
 
 // MLP and guess (ilh_mlp.hip)
 int guess_features(ilh_ctx* c, const double* u, double vs, double es, double xs, float* f, int nin);

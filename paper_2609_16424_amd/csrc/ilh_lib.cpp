@@ -210,6 +210,16 @@ static int dalloc(ilh_ctx* c, T** p, size_t count) {
   return ILH_OK;
 }
 
+int ensure_gscr(ilh_ctx* c, int64_t need) {
+  if (c->gscr_len >= need) return ILH_OK;
+  if (c->gscr) (void)hipFree(c->gscr);
+  c->gscr = nullptr;
+  c->gscr_len = 0;
+  const int st = dalloc(c, &c->gscr, (size_t)need);
+  if (!st) c->gscr_len = need;
+  return st;
+}
+
 // Krylov workspace for restart length m: the basis V, Z in FP64 (kry) or FP32 (kryf, f32 = true),
 // and two FP32 block vectors (kry32) for the cast actions and the probed preconditioner.
 static int ensure_solver_ws(ilh_ctx* c, int m, bool f32 = false) {
@@ -2235,13 +2245,7 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
   for (int l = 1; l <= m->nl; ++l) tot += ne * pad(m->widths[l]);
   const int64_t need = ne * p0 + 2 * tot;
   int st;
-  if (c->gscr_len < need) {
-    if (c->gscr) (void)hipFree(c->gscr);
-    c->gscr = nullptr;
-    c->gscr_len = 0;
-    if ((st = dalloc(c, &c->gscr, (size_t)need))) return st;
-    c->gscr_len = need;
-  }
+  if ((st = ensure_gscr(c, need))) return st;
   if (!c->gres && (st = dalloc(c, &c->gres, (size_t)c->nblock))) return st;
   float* feat = c->gscr;
   float* zs = feat + ne * p0;
