@@ -119,7 +119,7 @@ struct ilh_ctx {
   double* kry = nullptr;        // V [(m+1)][nblock], Z [m][nblock]
   float* gscr = nullptr;        // learned-guess features and activations, training scratch (allocated on first use)
   int64_t gscr_len = 0;
-  double* gres = nullptr;       // learned-guess judge residual [nblock]
+  double* gres = nullptr;       // learned-guess judge: residuals of the learned and the plain iterate [2][nblock]
   double* pgb = nullptr;        // plain-guess fallback: candidate and residual [2][nblock] (first use)
   double* pdv = nullptr;        // probed diagonal of the velocity block [nh1]
   double* peinv = nullptr;      // inverted probed energy blocks [Ne][Nl][Nl]
@@ -436,9 +436,8 @@ int launch_mass_e_axpy(ilh_ctx* c, const double* b, const double* x, double s, d
 int ensure_gscr(ilh_ctx* c, int64_t need);
 
 // MLP and guess (ilh_mlp.hip)
-int guess_features(ilh_ctx* c, const double* u, double vs, double es, double xs, float* f, int nin);
-int guess_targets(ilh_ctx* c, const double* k, double kvs, double kes, float* t, int nout);
-int guess_assemble(ilh_ctx* c, const float* pred, int nout, double kvs, double kes,
-                   const double* base, const double* u, double tau, double* k);
+// the assembly of ilh_guess_assemble; zero, zero2 (nullable): nh1 entries cleared by the same launch
+int guess_assemble(ilh_ctx* c, const float* pred, int ld, double kvs, double kes, const float* osc,
+                   const double* base, const double* u, double tau, double* kout, double* zero, double* zero2);
 
 }  // namespace ilh

@@ -210,6 +210,18 @@ static int dalloc(ilh_ctx* c, T** p, size_t count) {
   return ILH_OK;
 }
 
+// mapped, coherent host memory that kernels write scalars to
+static int ensure_hest(ilh_ctx* c) {
+  if (!c->hest) {
+    if (hipHostMalloc((void**)&c->hest, 272 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
+        hipSuccess)
+      return fail(c, ILH_ENOMEM, "pinned host buffer");
+    std::memset(c->hest, 0, 272 * sizeof(double));  // no tag (tags start at 1)
+    ILH_HIP(c, hipHostGetDevicePointer((void**)&c->hest_dev, c->hest, 0));
+  }
+  return ILH_OK;
+}
+
 int ensure_gscr(ilh_ctx* c, int64_t need) {
   if (c->gscr_len >= need) return ILH_OK;
   if (c->gscr) (void)hipFree(c->gscr);
@@ -1849,13 +1861,7 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
   if (!c->gsp && (st = dalloc(c, &c->gsp, (size_t)132 * 1024))) return st;
   if (!c->nwt && (st = dalloc(c, &c->nwt, 8 * (size_t)n))) return st;
   if (!c->hdev && (st = dalloc(c, &c->hdev, HDEV_LEN))) return st;
-  if (!c->hest) {
-    if (hipHostMalloc((void**)&c->hest, 272 * sizeof(double), hipHostMallocMapped | hipHostMallocCoherent) !=
-        hipSuccess)
-      return fail(c, ILH_ENOMEM, "pinned host buffer");
-    std::memset(c->hest, 0, 272 * sizeof(double));  // no tag (tags start at 1)
-    ILH_HIP(c, hipHostGetDevicePointer((void**)&c->hest_dev, c->hest, 0));
-  }
+  if ((st = ensure_hest(c))) return st;
   if (!c->gmd && (st = dalloc(c, &c->gmd, 64 * 64 + 3 * 65))) return st;
   if (!c->gs_words) {
     int dev = 0, cus = 0;
@@ -2246,7 +2252,8 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
   const int64_t need = ne * p0 + 2 * tot;
   int st;
   if ((st = ensure_gscr(c, need))) return st;
-  if (!c->gres && (st = dalloc(c, &c->gres, (size_t)c->nblock))) return st;
+  if (!c->gres && (st = dalloc(c, &c->gres, 2 * (size_t)c->nblock))) return st;
+  if ((st = ensure_hest(c))) return st;
   float* feat = c->gscr;
   float* zs = feat + ne * p0;
   float* acts = zs + tot;
@@ -2268,17 +2275,25 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
       return st;
     if ((st = ilh_mlp_forward(c, m->nl, m->widths, m->W, m->b, feat, (int)ne, zs, acts))) return st;
   }
-  if ((st = ilh_guess_assemble(c, out, pl, m->kvscale, m->kescale, m->osc, base, u, tau, k))) return st;
-  // judge: residual norms of the learned and the plain iterate
-  if ((st = ilh_residual(c, k, u, tau, c->gres))) return st;
-  const double nl = nrm2(c, c->gres, c->nblock, &st);
-  if (st) return st;
-  if ((st = ilh_residual(c, base, u, tau, c->gres))) return st;
-  const double nb = nrm2(c, c->gres, c->nblock, &st);
-  if (st) return st;
-  const bool use = std::isfinite(nl) && (nl < nb || !std::isfinite(nb));
-  if (!use) ILH_HIP(c, hipMemcpyAsync(k, base, c->nblock * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  // the assembly also clears the velocity rows of both residuals
+  double* rl = c->gres;
+  double* rb = c->gres + c->nblock;
+  if (c->dim != 2 || pl < 2 * ND + NLd) return fail(c, ILH_EINVAL, "prediction stride too small");
+  if ((st = guess_assemble(c, out, pl, m->kvscale, m->kescale, m->osc, base, u, tau, k, rl + c->nh1, rb + c->nh1)))
+    return st;
+  // judge: residual norms of the learned and the plain iterate, formed and read together
+  if ((st = residual_pair(c, k, rl, base, rb, u, tau))) return st;
+  int np = 0;
+  double* hp = c->hest_dev + 256;
+  if ((st = dot_part2(c, rl, rl, rb, rb, c->nblock, c->red, c->red + c->red_blocks, &np))) return st;
+  if ((st = launch_pair_final(c, c->red, np, 0, c->red + c->red_blocks, np, 0, hp))) return st;
   ILH_HIP(c, hipStreamSynchronize(c->stream));
+  const double nl = std::sqrt(c->hest[256]), nb = std::sqrt(c->hest[257]);
+  const bool use = std::isfinite(nl) && (nl < nb || !std::isfinite(nb));
+  if (!use) {
+    ILH_HIP(c, hipMemcpyAsync(k, base, c->nblock * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+    ILH_HIP(c, hipStreamSynchronize(c->stream));
+  }
   if (used) *used = use ? 1 : 0;
   return ILH_OK;
   ILH_CATCH(c)

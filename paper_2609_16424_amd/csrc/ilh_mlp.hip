@@ -54,6 +54,7 @@ __device__ __forceinline__ float gelu_d(float z) {
 // MFMA 16x16x32 operand layout: lane l holds row/col (l % 16) and the 8 consecutive k of
 // block (l / 16); the accumulator holds column (l % 16), rows 4 (l / 16) + 0..3.
 constexpr int ML_MAXL = 8;
+constexpr int FZ_WLDS = 57344;   // BF16 weights (rows padded by 8) that the fused inference call takes
 constexpr int ML_T = 512;        // threads of the row kernels: one wave per 16-column tile
 constexpr int ML_LD = 128 + 8;   // LDS row of an activation tile (BF16, padded)
 constexpr int ML_MAXB = 512;     // work-groups of the data-gradient launch (each walks 16-row tiles)
@@ -78,6 +79,24 @@ __device__ __forceinline__ bf16x8 ldbf8(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
+// a wave's operand of layer l: column n = 16 wave + ln of the output (clamped), its weights and bias
+__device__ __forceinline__ void load_weights(const MlpNet& F, const uint16_t* W, const float* bias, int l, int wave,
+                                             int ln, int kb, bf16x8 (&w)[4], float& b) {
+  const int n = min(wave * 16 + ln, F.np[l] - 1), ns = F.kp[l] / 32;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) w[q] = ldbf8(W + F.wo[l] + n * F.kp[l] + min(q, ns - 1) * 32 + kb);
+  b = bias[F.bo[l] + n];
+}
+// 16 rows (a: this lane's row of the LDS tile) times 16 columns over ns blocks of 32
+__device__ __forceinline__ f32x4 row_product(const uint16_t* a, int ns, const bf16x8 (&w)[4]) {
+  f32x4 acc = {0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (q < ns)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(a + q * 32), w[q], acc, 0, 0, 0);
+  return acc;
+}
+
 // Z_l = bf(A_{l-1}) W_l^T + b_l and A_l = gelu(Z_l) (last layer: Z_l) for 16 rows per work-group.
 __global__ void __launch_bounds__(ML_T) k_mlp_fwd(const MlpNet F, const uint16_t* __restrict__ W,
                                                   const float* __restrict__ bias, const float* __restrict__ x,
@@ -87,13 +106,7 @@ __global__ void __launch_bounds__(ML_T) k_mlp_fwd(const MlpNet F, const uint16_t
   const int row0 = blockIdx.x * 16;
   bf16x8 wc[4], wn[4];
   float bc = 0.0f, bn = 0.0f;
-  auto loadw = [&](int l, bf16x8(&w)[4], float& b) {
-    const int n = min(wave * 16 + ln, F.np[l] - 1), ns = F.kp[l] / 32;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) w[q] = ldbf8(W + F.wo[l] + n * F.kp[l] + min(q, ns - 1) * 32 + kb);
-    b = bias[F.bo[l] + n];
-  };
-  loadw(0, wc, bc);
+  load_weights(F, W, bias, 0, wave, ln, kb, wc, bc);
   {
     const int q = F.kp[0] / 4, r = tid / q, c4 = tid - r * q;
     if (r < 16) {
@@ -104,17 +117,12 @@ __global__ void __launch_bounds__(ML_T) k_mlp_fwd(const MlpNet F, const uint16_t
     }
   }
   for (int l = 0; l < F.nl; ++l) {
-    const int ns = F.kp[l] / 32, NP = F.np[l], cur = l & 1;
+    const int NP = F.np[l], cur = l & 1;
     const bool last = l == F.nl - 1;
     __syncthreads();  // this layer's input is complete, the other tile is no longer read
-    if (!last) loadw(l + 1, wn, bn);
+    if (!last) load_weights(F, W, bias, l + 1, wave, ln, kb, wn, bn);
     if (wave < NP / 16) {
-      f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (q < ns)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(&sA[cur][ln][q * 32 + kb]),
-                                                        wc[q], acc, 0, 0, 0);
+      const f32x4 acc = row_product(&sA[cur][ln][kb], F.kp[l] / 32, wc);
       const int n = wave * 16 + ln;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -199,12 +207,7 @@ __global__ void __launch_bounds__(ML_T) k_mlp_bwd(const MlpNet F, const uint16_t
         gz[j] = zs[F.ao[l - 1] + (int64_t)min(row0 + rl0 + j, batch - 1) * KP + k];
       __syncthreads();  // dZ_l is complete, the other tile is no longer read
       if (on) {
-        f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q < ns)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(&sD[cur][ln][q * 32 + kb]),
-                                                          w[q], acc, 0, 0, 0);
+        const f32x4 acc = row_product(&sD[cur][ln][kb], ns, w);
         float v[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = row0 + rl0 + j < batch ? acc[j] * gelu_d(gz[j]) : 0.0f;
@@ -420,104 +423,48 @@ __global__ void k_features(const KParams P, const FeatArgs A, float* feat, int l
 }
 
 // ---------------------------------------------------------------------------------------
-// Fused inference: the features of a tile of 16 elements, every layer and the store of the
-// network output in one launch.  Each work-group first copies all weights (BF16) and biases into
-// LDS and then walks element tiles; the eight waves compute the features of the tile together and
-// split each layer's 16-column output tiles, the activations passing between layers through two
-// alternating LDS tiles in the MFMA operand layout.  The operand rounding (BF16), the
-// accumulation order and the epilogue are those of k_dense_fwd, so the output is the layered
-// forward's.  Weight rows are padded by 8 BF16 (16 bytes) in LDS, so the 16 lanes of a quarter
-// wave read 16 different rows from 16 different bank groups.
-constexpr int FZ_MAXL = 8;
-constexpr int FZ_WLDS = 57344;  // BF16 weight elements in LDS (padded rows): 112 KiB
-constexpr int FZ_BLDS = FZ_MAXL * 128;
-constexpr int FZ_ALD = 128 + 8;  // activation tile row (BF16, padded)
-
-struct FusedNet {
-  int nl;
-  int kp[FZ_MAXL], np[FZ_MAXL];  // padded widths of each layer
-  int wg[FZ_MAXL];                // offset of layer l in the global W (KP x NP blocks)
-  int ws[FZ_MAXL];                // offset of layer l in the LDS copy (rows of KP + 8)
-  int bo[FZ_MAXL];                // offset of layer l's bias
-};
-
-constexpr int FZ_T = 512;  // threads of the work-group (8 waves)
-
-__global__ void __launch_bounds__(FZ_T) k_guess_fused(const KParams P, const FeatArgs FA, const FusedNet F,
+// Fused inference: the features of 16 elements, every layer and the store of the network output in
+// one launch, on the row scheme of k_mlp_fwd (a wave per 16-column tile, weights from L2 one layer ahead).
+// The operand rounding (BF16), the accumulation order and the epilogue are those of k_mlp_fwd, so the
+// output is the layered forward's.  Copying all weights to LDS first (111 KB a work-group, 336 tiles on
+// 256 compute units) took 27 us at 5,376 elements, this form 17.7 (half of it the features).
+__global__ void __launch_bounds__(ML_T) k_guess_fused(const KParams P, const FeatArgs FA, const MlpNet F,
                                                      const uint16_t* __restrict__ W, const float* __restrict__ bias,
                                                      float* __restrict__ pred, int ld_out) {
-  __shared__ __attribute__((aligned(16))) uint16_t sW[FZ_WLDS];
-  __shared__ float sB[FZ_BLDS];
-  __shared__ __attribute__((aligned(16))) uint16_t sA[2][16][FZ_ALD];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // weights: 8 BF16 (16 bytes) per copy, rows of KP to rows of KP + 8, eight copies in flight
-  for (int l = 0; l < F.nl; ++l) {
-    const int KP = F.kp[l], NP = F.np[l], KC = KP / 8, tot = NP * KC;
-    for (int i0 = tid; i0 < tot; i0 += FZ_T * 8) {
-      uint4 v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = min(i0 + FZ_T * u, tot - 1);
-        const int n = i / KC, kc = i - n * KC;
-        v[u] = *reinterpret_cast<const uint4*>(W + F.wg[l] + n * KP + kc * 8);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + FZ_T * u;
-        if (i < tot) {
-          const int n = i / KC, kc = i - n * KC;
-          *reinterpret_cast<uint4*>(sW + F.ws[l] + n * (KP + 8) + kc * 8) = v[u];
-        }
-      }
-    }
-    for (int i = tid; i < NP; i += FZ_T) sB[F.bo[l] + i] = bias[F.bo[l] + i];
+  __shared__ __attribute__((aligned(16))) uint16_t sA[2][16][ML_LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 15, kb = (lane >> 4) * 8;
+  const int64_t row0 = (int64_t)blockIdx.x * 16;
+  bf16x8 wc[4], wn[4];
+  float bc = 0.0f, bn = 0.0f;
+  load_weights(F, W, bias, 0, wave, ln, kb, wc, bc);
+  const int KP0 = F.kp[0];
+  for (int i = tid; i < 16 * KP0; i += ML_T) {
+    const int r = i / KP0, f = i - r * KP0;
+    const int64_t e = row0 + r;
+    sA[0][r][f] = f2bf(e < P.Ne ? feature_value(P, FA, e, f) : 0.0f);
   }
-  const int64_t ntiles = (P.Ne + 15) / 16;
-  const int kb = (lane >> 4) * 8;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t row0 = tile * 16;
-    // layer 0 input: the features of the tile's 16 elements, BF16, all threads
-    const int KP0 = F.kp[0];
-    for (int i = tid; i < 16 * KP0; i += FZ_T) {
-      const int r = i / KP0, f = i - r * KP0;
-      const int64_t e = row0 + r;
-      sA[0][r][f] = f2bf(e < P.Ne ? feature_value(P, FA, e, f) : 0.0f);
-    }
-    __syncthreads();  // the weights (first tile) and the features are in place
-    for (int l = 0; l < F.nl; ++l) {
-      const int KP = F.kp[l], NP = F.np[l];
-      const bool last = l == F.nl - 1;
-      const uint16_t* Wl = sW + F.ws[l];
-      const int cur = l & 1;
-      bf16x8 af[4];
+  for (int l = 0; l < F.nl; ++l) {
+    const int cur = l & 1;
+    const bool last = l == F.nl - 1;
+    __syncthreads();  // this layer's input is complete, the other tile is no longer read
+    if (!last) load_weights(F, W, bias, l + 1, wave, ln, kb, wn, bn);
+    if (wave < F.np[l] / 16) {
+      const f32x4 acc = row_product(&sA[cur][ln][kb], F.kp[l] / 32, wc);
+      const int n = wave * 16 + ln;
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s < KP / 32) af[s] = *reinterpret_cast<const bf16x8*>(&sA[cur][lane & 15][s * 32 + kb]);
-      for (int t = wave; t < NP / 16; t += FZ_T / 64) {
-        const int n = t * 16 + (lane & 15);
-        f32x4 acc = {0, 0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          if (s < KP / 32) {
-            const bf16x8 bf = *reinterpret_cast<const bf16x8*>(Wl + n * (KP + 8) + s * 32 + kb);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s], bf, acc, 0, 0, 0);
-          }
-        }
-        const float bn = sB[F.bo[l] + n];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int rl = (lane >> 4) * 4 + j;
-          const float z = acc[j] + bn;
-          if (last) {
-            const int64_t rr = row0 + rl;
-            if (rr < P.Ne && n < ld_out) pred[rr * ld_out + n] = z;
-          } else {
-            sA[cur ^ 1][rl][n] = f2bf(gelu(z));
-          }
+      for (int j = 0; j < 4; ++j) {
+        const int rl = (lane >> 4) * 4 + j;
+        const float z = acc[j] + bc;
+        if (last) {
+          if (row0 + rl < P.Ne && n < ld_out) pred[(row0 + rl) * ld_out + n] = z;
+        } else {
+          sA[cur ^ 1][rl][n] = f2bf(gelu(z));
         }
       }
-      __syncthreads();  // the next layer's input is complete, this layer's is no longer read
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wc[q] = wn[q];
+    bc = bn;
   }
 }
 
@@ -544,43 +491,42 @@ __global__ void k_targets(const KParams P, const double* kk, const double* base,
   }
 }
 
-// assembly, step 1: acc_v[node] += kvs * pred_v (sum over the elements containing the node)
-__global__ void k_assemble_acc(const KParams P, const float* pred, int ld, double kvs, const float* osc, double* acc) {
-  const int64_t e = blockIdx.x * (int64_t)blockDim.y + threadIdx.y;
-  if (e >= P.Ne) return;
-  const int k = P.k, D1D = k + 1, ND = D1D * D1D;
-  const int ex = (int)(e % P.n[0]), ey = (int)(e / P.n[0]);
-  const int64_t N = P.N, ng0 = P.ng[0];
-  for (int i = threadIdx.x; i < 2 * ND; i += blockDim.x) {
-    const int c = i / ND, li = i % ND, a = li % D1D, b = li / D1D;
-    const double sc = osc ? (double)osc[i] : 1.0;
-    unsafeAtomicAdd(&acc[c * N + (int64_t)(k * ey + b) * ng0 + k * ex + a], kvs * sc * (double)pred[e * ld + i]);
+// Assembly, one thread per H1 velocity entry or energy entry: k_v = base_v plus the mean over the (up
+// to four) elements that hold the node of kvs pred_v (0 on constrained rows), k_x = u_v + tau k_v, k_e =
+// base_e + kes pred_e.  Each node gathers its elements' predictions: no zero fill and no atomics in
+// front of it.  zero (nullable): 2 N entries cleared by the same launch.
+__global__ void k_assemble(const KParams P, const float* __restrict__ pred, int ld, double kvs, double kes,
+                           const float* __restrict__ osc, const double* __restrict__ base,
+                           const double* __restrict__ u, double tau, double* __restrict__ kout, double* zero,
+                           double* zero2) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t N = P.N, nh1 = 2 * N;
+  const int k = P.k, D1D = k + 1, ND = D1D * D1D, NL = k * k;
+  if (i < nh1) {
+    const int c = i < N ? 0 : 1;
+    const int64_t node = i - c * N;
+    const int ng0 = P.ng[0], I = (int)(node % ng0), J = (int)(node / ng0);
+    // the last element with the node at its start or inside, and the one before when it is on the edge
+    const int ex1 = min(I / k, P.n[0] - 1), ex0 = (I % k == 0 && I > 0 && I < ng0 - 1) ? ex1 - 1 : ex1;
+    const int ey1 = min(J / k, P.n[1] - 1), ey0 = (J % k == 0 && J > 0 && J < P.ng[1] - 1) ? ey1 - 1 : ey1;
+    double acc = 0.0;
+    for (int ey = ey0; ey <= ey1; ++ey)
+      for (int ex = ex0; ex <= ex1; ++ex) {
+        const int li = c * ND + (J - k * ey) * D1D + I - k * ex;
+        const double sc = osc ? (double)osc[li] : 1.0;
+        acc += kvs * sc * (double)pred[((int64_t)ey * P.n[0] + ex) * ld + li];
+      }
+    const bool cons = on_wall(P.walls, c, c == 0 ? I : J, P.ng[c]);
+    const double kv = cons ? 0.0 : base[nh1 + i] + acc / ((ex1 - ex0 + 1) * (ey1 - ey0 + 1));
+    kout[nh1 + i] = kv;
+    kout[i] = u[nh1 + i] + tau * kv;
+    if (zero) zero[i] = 0.0;
+    if (zero2) zero2[i] = 0.0;
+  } else if (i < nh1 + (int64_t)P.Ne * NL) {
+    const int64_t q = i - nh1, e = q / NL, j = q - e * NL;
+    const double sc = osc ? (double)osc[2 * ND + j] : 1.0;
+    kout[2 * nh1 + q] = base[2 * nh1 + q] + kes * sc * (double)pred[e * ld + 2 * ND + j];
   }
-}
-// step 2: k_v = base_v + acc / multiplicity (0 on constrained rows), k_x = u_v + tau k_v
-__global__ void k_assemble_nodes(const KParams P, const double* acc, const double* base, const double* u, double tau,
-                                 double* kout) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= 2 * P.N) return;
-  const int64_t N = P.N, node = i % N;
-  const int c = (int)(i / N), k = P.k;
-  const int I = (int)(node % P.ng[0]), J = (int)(node / P.ng[0]);
-  const int mx = (I % k == 0 && I > 0 && I < P.ng[0] - 1) ? 2 : 1;
-  const int my = (J % k == 0 && J > 0 && J < P.ng[1] - 1) ? 2 : 1;
-  const int gc = (c == 0) ? I : J, ngc = P.ng[c];
-  const bool cons = on_wall(P.walls, c, gc, ngc);
-  const double kv = cons ? 0.0 : base[2 * N + i] + acc[i] / (mx * my);
-  kout[2 * N + i] = kv;
-  kout[i] = u[2 * N + i] + tau * kv;
-}
-__global__ void k_assemble_e(const KParams P, const float* pred, int ld, double kes, const float* osc,
-                             const double* base, double* kout) {
-  const int NL = P.k * P.k, ND = (P.k + 1) * (P.k + 1);
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= (int64_t)P.Ne * NL) return;
-  const int64_t e = i / NL, j = i % NL, off = 4 * P.N;
-  const double sc = osc ? (double)osc[2 * ND + j] : 1.0;
-  kout[off + i] = base[off + i] + kes * sc * (double)pred[e * ld + 2 * ND + j];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -612,6 +558,15 @@ static MlpNet make_net(int nl, const int* widths, int batch) {
     ao += (int64_t)batch * F.np[l];
   }
   return F;
+}
+
+int guess_assemble(ilh_ctx* c, const float* pred, int ld, double kvs, double kes, const float* osc,
+                   const double* base, const double* u, double tau, double* kout, double* zero, double* zero2) {
+  const int64_t n = c->nh1 + c->nl2;
+  hipLaunchKernelGGL(k_assemble, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->kp, pred, ld, kvs, kes,
+                     osc, base, u, tau, kout, zero, zero2);
+  ILH_HIP(c, hipGetLastError());
+  return ILH_OK;
 }
 
 }  // namespace ilh
@@ -654,17 +609,7 @@ int ilh_guess_assemble(ilh_ctx* c, const float* pred, int ld, double kvs, double
   if (!c || !pred || !base || !u || !kout || c->dim != 2) return fail(c, ILH_EINVAL, "guess assemble: 2D only");
   const int ND = (c->k + 1) * (c->k + 1), NL = c->k * c->k;
   if (ld < 2 * ND + NL) return fail(c, ILH_EINVAL, "prediction stride too small");
-  double* acc = c->pcgbuf;  // nh1 doubles
-  int st = launch_fill(c, acc, 0.0, c->nh1);
-  if (st) return st;
-  hipLaunchKernelGGL(k_assemble_acc, dim3((unsigned)((c->Ne + 3) / 4)), dim3(64, 4), 0, c->stream, c->kp, pred, ld, kvs,
-                     osc, acc);
-  hipLaunchKernelGGL(k_assemble_nodes, dim3((unsigned)((c->nh1 + 255) / 256)), dim3(256), 0, c->stream, c->kp, acc,
-                     base, u, tau, kout);
-  hipLaunchKernelGGL(k_assemble_e, dim3((unsigned)((c->nl2 + 255) / 256)), dim3(256), 0, c->stream, c->kp, pred, ld,
-                     kes, osc, base, kout);
-  ILH_HIP(c, hipGetLastError());
-  return ILH_OK;
+  return guess_assemble(c, pred, ld, kvs, kes, osc, base, u, tau, kout, nullptr, nullptr);
   ILH_CATCH(c)
 }
 
@@ -691,34 +636,21 @@ int ilh_guess_mlp_fused(ilh_ctx* c, const ilh_guess_model* m, const double* u, c
   if (!c || !m || !u || !pred || !m->W || !m->b || c->dim != 2) return fail(c, ILH_EINVAL, "fused guess MLP: 2D, non-null");
   int st = check_widths(c, m->nl, m->widths);
   if (st) return st;
-  if (m->nl > FZ_MAXL) return fail(c, ILH_EINVAL, "fused guess MLP: at most 8 layers");
   const int ND = (c->k + 1) * (c->k + 1), NL = c->k * c->k;
   const int nin = 2 * ND + NL + 8 + (m->with_base ? 2 * ND + NL : 0);
   if (m->widths[0] != nin || m->widths[m->nl] != 2 * ND + NL)
     return fail(c, ILH_EINVAL, "fused guess MLP: widths do not match the features and outputs of this mesh");
   if (m->with_base && !base) return fail(c, ILH_EINVAL, "fused guess MLP: the model takes the base iterate");
-  FusedNet F{};
-  F.nl = m->nl;
-  int wg = 0, ws = 0, bo = 0;
-  for (int l = 0; l < m->nl; ++l) {
-    F.kp[l] = pad32(m->widths[l]);
-    F.np[l] = pad32(m->widths[l + 1]);
-    F.wg[l] = wg;
-    F.ws[l] = ws;
-    F.bo[l] = bo;
-    wg += F.kp[l] * F.np[l];
-    ws += F.np[l] * (F.kp[l] + 8);
-    bo += F.np[l];
-  }
-  if (ws > FZ_WLDS) return fail(c, ILH_EINVAL, "fused guess MLP: the weights exceed the LDS budget");
+  const MlpNet F = make_net(m->nl, m->widths, 0);
+  int64_t padded = 0;
+  for (int l = 0; l < m->nl; ++l) padded += (int64_t)F.np[l] * (F.kp[l] + 8);
+  if (padded > FZ_WLDS) return fail(c, ILH_EINVAL, "fused guess MLP: the weights exceed the LDS budget");
   if (ld < F.np[m->nl - 1]) return fail(c, ILH_EINVAL, "prediction stride below the padded output width");
   if ((reinterpret_cast<uintptr_t>(m->W) & 15) != 0) return fail(c, ILH_EINVAL, "fused guess MLP: W not 16-byte aligned");
   const FeatArgs fa{u, m->with_base ? base : nullptr, m->vscale, m->escale, m->xscale, m->kvscale, m->kescale,
                     m->mu, m->sd};
-  // one work-group per compute unit at most (the LDS holds one), each walking several tiles
-  const int64_t ntiles = (c->Ne + 15) / 16;
-  const unsigned nb = (unsigned)std::min<int64_t>(ntiles, 256);
-  hipLaunchKernelGGL(k_guess_fused, dim3(nb), dim3(FZ_T), 0, c->stream, c->kp, fa, F, m->W, m->b, pred, ld);
+  hipLaunchKernelGGL(k_guess_fused, dim3((unsigned)((c->Ne + 15) / 16)), dim3(ML_T), 0, c->stream, c->kp, fa, F, m->W, m->b,
+                     pred, ld);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
   ILH_CATCH(c)

@@ -250,7 +250,7 @@ class LearnedGuess:
         """Returns (k_guess, used_learned): one fused library call (features, MLP, assembly,
         residual judge against the plain iterate)."""
         base = self.h.plain_guess(u, hist, tau)
-        k = self.h.new()
+        k = torch.empty(self.h.nblock, dtype=torch.float64, device=self.h.device)  # every block is written
         used = C.c_int(0)
         self.h._stream()
         self.h._check(self.h.lib.ilh_guess_infer(self.h.ctx, C.byref(self.model()), self.h._vec(u, self.h.nblock),
