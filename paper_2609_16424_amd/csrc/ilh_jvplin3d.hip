@@ -24,8 +24,7 @@ namespace ilh {
 // ---- linearisation: state w (FP64) -> stored coefficients (T) ----------------------------
 template <int D1D, int Q1D, typename T, int VISC>
 __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double, D1D, Q1D> tb,
-                                              const double* __restrict__ w, double tau, T* __restrict__ qd,
-                                              int64_t qs) {
+                                              const double* __restrict__ w, double tau, T* __restrict__ qd) {
   constexpr int K = D1D - 1, L1D = K, NLD = L1D * L1D * L1D;
   constexpr int LPE = Q1D * Q1D, EPW = 64 / LPE;
   constexpr int NS = K * EPW + 1;
@@ -156,23 +155,26 @@ __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double
     lin_coefs<3, VISC>(P, gam, mq, dJ0, J, Gv, eq, cf);
 #pragma unroll
     for (int f = NPRE; f < NQD; ++f) cf[f] *= tau;
-    if constexpr (sizeof(T) == 4) {  // row-interleaved (FP32)
-      T* q = qd + (blk * Q1D + qz) * (NQD * 64) + lane;
+    T* q = qd + (blk * Q1D + qz) * (NQD * 64) + lane;
 #pragma unroll
-      for (int f = 0; f < NQD; ++f) q[f * 64] = T(cf[f]);
-    } else {  // field-major (FP64)
-      T* q = qd + (blk * Q1D + qz) * 64 + lane;
-#pragma unroll
-      for (int f = 0; f < NQD; ++f) q[f * qs] = T(cf[f]);
-    }
+    for (int f = 0; f < NQD; ++f) q[f * 64] = T(cf[f]);
   }
 }
 
 // ---- apply: direction dk (T) -> J dk (T) --------------------------------------------------
+// Bound by the coefficient stream (8 bytes x 20 or 29 a point in FP64), which one wavefront per SIMD
+// did not keep full: 70 % of its cycles waited.  FP64 therefore fits two: the position contractions
+// (27 values a lane) wait in LDS where the output columns go later, and the next step's coefficients
+// are asked for when the point's tangent is formed, into the registers it leaves.  FP32 has room for
+// three with the contractions and two steps' coefficients in registers.  57x44x39 Q2Q1 with viscosity
+// in FP64, fill included: 766 us before (one wavefront, field-major rows, one atomic per node and
+// element), 410 us now (1.53 GB of coefficients: 320 us at the rate of a large copy); without
+// viscosity 380 and 317 us.  FP32 with the coefficients copied to LDS directly measured 218 us
+// against 204 us, and is not used.
 template <int D1D, int Q1D, typename T, int VISC>
-__global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb,
-                                                const T* __restrict__ dk, const T* __restrict__ qd,
-                                                int64_t qs, double tau_, T* __restrict__ out) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk, const T* __restrict__ qd,
+          double tau_, T* __restrict__ out) {
   constexpr int K = D1D - 1, L1D = K, NLD = L1D * L1D * L1D;
   constexpr int LPE = Q1D * Q1D, EPW = 64 / LPE;
   constexpr int NS = K * EPW + 1;
@@ -183,7 +185,12 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
 
   __shared__ T sS[NF][D1D][D1D][NS];
   __shared__ T sE[EPW * NLD];
-  __shared__ T sO[64][NOP];
+  // during the column walk in FP64 the lane's position contractions; after it the output columns
+  // (lane, node)
+  constexpr bool PLDS = sizeof(T) == 8;
+  constexpr int NPC = 9 * D1D, NU = PLDS && NPC > NOP ? NPC : NOP;
+  __shared__ T sU[64 * NU];
+  auto sO = reinterpret_cast<T(*)[NOP]>(sU);
   __shared__ T sBG[2][Q1D][D1D];
   __shared__ T sBL[Q1D][L1D];
 
@@ -212,6 +219,14 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
   }
 #pragma unroll
   for (int r = 0; r < RL; ++r) lr[r] = ld32(dk, 2 * nh1 + ebase * NLD + min(lane + 64 * r, E * NLD - 1));
+  const T* __restrict__ qb = sbase(qd + (int64_t)tile * (Q1D * NQD * 64));
+  T cf[NQD];
+  auto ldstep = [&](const int qz, T* c) {
+    const T* rb = sbase(qb + qz * (NQD * 64));
+#pragma unroll
+    for (int f = 0; f < NQD; ++f) c[f] = ld32(rb, (uint32_t)(f * 64 + lane));
+  };
+  ldstep(0, cf);
   const int zl = lane / LPE;
   const double rj_l = P.rj0[ebase + (zl < E ? zl : 0)];
   for (int i = lane; i < Q1D * D1D; i += 64) {
@@ -232,7 +247,6 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
   lds_barrier();
 
   const int z = lane / LPE, rr = lane - z * LPE, qy = rr / Q1D, qx = rr - qy * Q1D;
-  const bool active = z < E;
   T Bx[D1D], Gx[D1D], By[D1D], Gy[D1D], BLx[L1D], BLy[L1D];
 #pragma unroll
   for (int a = 0; a < D1D; ++a) {
@@ -255,9 +269,11 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
     for (int c = 0; c < D1D; ++c) Tx[r][c] = Ty[r][c] = Tz[r][c] = T(0);
 #pragma unroll
   for (int cl = 0; cl < L1D; ++cl) TL[cl] = T(0);
-  if (active) {
+  {  // lanes past the strip walk along: their columns feed no output
     const int s0 = K * z;
+    constexpr int F0 = PLDS ? 3 : 0;  // first field whose contractions stay in registers
     T BB[NF][D1D], GB[NF][D1D], BG[NF][D1D];
+    T* const pc = sU + lane * NPC;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -276,10 +292,17 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
           gb += By[b] * ag;
           bg += Gy[b] * ab;
         }
-        BB[f][cz] = bb;
-        GB[f][cz] = gb;
-        BG[f][cz] = bg;
+        if (f < F0) {
+          pc[(f * D1D + cz) * 3] = gb;
+          pc[(f * D1D + cz) * 3 + 1] = bg;
+          pc[(f * D1D + cz) * 3 + 2] = bb;
+        } else {
+          BB[f][cz] = bb;
+          GB[f][cz] = gb;
+          BG[f][cz] = bg;
+        }
       }
+
     T EL[L1D];
 #pragma unroll
     for (int cl = 0; cl < L1D; ++cl) {
@@ -291,24 +314,7 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
       EL[cl] = acc;
     }
     const T wxy = tb.W[qx] * tb.W[qy] * T(rj_l);
-    constexpr bool ROWS = sizeof(T) == 4;  // coefficient layout: row-interleaved (FP32), field-major (FP64)
-    const T* __restrict__ qb = qd + (int64_t)tile * (Q1D * (ROWS ? NQD : 1) * 64);
-    const T* qf[ROWS ? 1 : NQD];
-    if constexpr (!ROWS) {
-#pragma unroll
-      for (int f = 0; f < NQD; ++f) qf[f] = sbase(qb + f * qs);
-    }
-    auto ldstep = [&](const int qz, T* c) {
-      if constexpr (ROWS) {
-        const T* rb = sbase(qb + qz * (NQD * 64));
-#pragma unroll
-        for (int f = 0; f < NQD; ++f) c[f] = ld32(rb, (uint32_t)(f * 64 + lane));
-      } else {
-#pragma unroll
-        for (int f = 0; f < NQD; ++f) c[f] = ld32(qf[f], (uint32_t)(qz * 64 + lane));
-      }
-    };
-    auto step = [&](const int qz, const T* cf) {
+    auto step = [&](const int qz) {
       // tau is folded into the coefficients: the contractions enter unscaled
       T dJ[3][3], dGv[3][3], dkv[3];
 #pragma unroll
@@ -317,9 +323,9 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
 #pragma unroll
         for (int c = 0; c < D1D; ++c) {
           const T Bz = tb.B[qz][c], Gz = tb.G[qz][c];
-          j0 += Bz * GB[r][c];
-          j1 += Bz * BG[r][c];
-          j2 += Gz * BB[r][c];
+          j0 += Bz * (PLDS ? pc[(r * D1D + c) * 3] : GB[r][c]);
+          j1 += Bz * (PLDS ? pc[(r * D1D + c) * 3 + 1] : BG[r][c]);
+          j2 += Gz * (PLDS ? pc[(r * D1D + c) * 3 + 2] : BB[r][c]);
           g0 += Bz * GB[3 + r][c];
           g1 += Bz * BG[3 + r][c];
           g2 += Gz * BB[3 + r][c];
@@ -339,6 +345,16 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
       const T mq = wxy * tb.W[qz];
       T dS[3][3], ds;
       lin_apply<3, T, VISC>(cf, dJ, dGv, dke, dS, ds);
+      if constexpr (PLDS) {
+        // the point's results are formed before the next coefficients are asked for: both sets in
+        // registers at once would not fit at two wavefronts per SIMD
+        asm volatile(""
+                     : "+v"(dS[0][0]), "+v"(dS[0][1]), "+v"(dS[0][2]), "+v"(dS[1][0]), "+v"(dS[1][1]),
+                       "+v"(dS[1][2]), "+v"(dS[2][0]), "+v"(dS[2][1]), "+v"(dS[2][2]), "+v"(ds)
+                     :
+                     : "memory");
+        if (qz + 1 < Q1D) ldstep(qz + 1, cf);
+      }
       const T cl_ = mq * dke - ds;
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
@@ -354,29 +370,35 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
 #pragma unroll
       for (int cl = 0; cl < L1D; ++cl) TL[cl] += tb.BL[qz][cl] * cl_;
     };
-    // the next step's coefficients are requested before this step's arithmetic
-    T cf[NQD];
-    ldstep(0, cf);
 #pragma unroll 1
     for (int qz = 0; qz < Q1D; ++qz) {
-      T cn[NQD];
-      ldstep(qz + 1 < Q1D ? qz + 1 : qz, cn);
-      step(qz, cf);
+      if constexpr (PLDS) {
+        asm volatile("" ::: "memory");  // the contractions in LDS are read again each step
+        step(qz);
+      } else {
+        T cn[NQD];
+        ldstep(qz + 1 < Q1D ? qz + 1 : qz, cn);
+        step(qz);
 #pragma unroll
-      for (int f = 0; f < NQD; ++f) cf[f] = cn[f];
+        for (int f = 0; f < NQD; ++f) cf[f] = cn[f];
+      }
     }
   }
-  if constexpr (sizeof(T) == 4) {
+  // the lane's indices once more, from a value the compiler does not connect with the first: what the
+  // gather and the column walk derived from them is not kept in registers up to here
+  int ln = threadIdx.x;
+  asm volatile("" : "+v"(ln));
+  const int pz = ln / LPE, pr = ln - pz * LPE, py = pr / Q1D, px = pr - py * Q1D;
   // velocity rows, one component at a time: each lane's column contributions to its element's
   // nodes (factored: out(a,b) = By_b (Gx_a Tx + Bx_a Tz) + Gy_b Bx_a Ty per z-layer) go to LDS;
   // one thread per node of the strip sums the columns of the (one or two) elements holding it
   // and issues one atomic add (constrained rows are set by the owner below)
 #pragma unroll
   for (int a = 0; a < D1D; ++a) {  // reloaded: not kept live through the column loop
-    Bx[a] = sBG[0][qx][a];
-    Gx[a] = sBG[1][qx][a];
-    By[a] = sBG[0][qy][a];
-    Gy[a] = sBG[1][qy][a];
+    Bx[a] = sBG[0][px][a];
+    Gx[a] = sBG[1][px][a];
+    By[a] = sBG[0][py][a];
+    Gy[a] = sBG[1][py][a];
   }
 #pragma unroll 1
   for (int r = 0; r < 3; ++r) {
@@ -394,11 +416,11 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
       for (int a = 0; a < D1D; ++a) {
         const T q1 = Gx[a] * tx + Bx[a] * tz, q2 = Bx[a] * ty;
 #pragma unroll
-        for (int b = 0; b < D1D; ++b) sO[lane][(cz * D1D + b) * D1D + a] = By[b] * q1 + Gy[b] * q2;
+        for (int b = 0; b < D1D; ++b) sO[ln][(cz * D1D + b) * D1D + a] = By[b] * q1 + Gy[b] * q2;
       }
     }
     lds_barrier();
-    for (int i = lane; i < D1D * D1D * NS; i += 64) {
+    for (int i = ln; i < D1D * D1D * NS; i += 64) {
       const int s = i % NS, t = i / NS, b = t % D1D, cz = t / D1D;
       if (s >= ns) continue;
       const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
@@ -418,70 +440,26 @@ __global__ void __launch_bounds__(64) k_jvp3d_q(const KParams P, const Tab2<T, D
     }
     lds_barrier();
   }
-  } else {  // FP64: per-element sums over the element's lanes, one atomic per node and element
-  // velocity rows, one component at a time: column contributions to the element's nodes,
-  // summed over the element's LPE lanes, scattered with atomics (shared nodes)
-  const int ex = ex0 + z;
-#pragma unroll
-  for (int a = 0; a < D1D; ++a) {  // reloaded: not kept live through the column loop
-    Bx[a] = sBG[0][qx][a];
-    Gx[a] = sBG[1][qx][a];
-    By[a] = sBG[0][qy][a];
-    Gy[a] = sBG[1][qy][a];
-  }
-#pragma unroll 1
-  for (int r = 0; r < 3; ++r) {
-#pragma unroll
-    for (int cz = 0; cz < D1D; ++cz)
-#pragma unroll
-      for (int b = 0; b < D1D; ++b)
-#pragma unroll
-        for (int a = 0; a < D1D; ++a) {
-          T tx = 0, ty = 0, tz = 0;
-#pragma unroll
-          for (int rq = 0; rq < 3; ++rq)
-            if (rq == r) {
-              tx = Tx[rq][cz];
-              ty = Ty[rq][cz];
-              tz = Tz[rq][cz];
-            }
-          sO[lane][(cz * D1D + b) * D1D + a] = Gx[a] * By[b] * tx + Bx[a] * Gy[b] * ty + Bx[a] * By[b] * tz;
-        }
-    lds_barrier();
-    if (active) {
-      for (int t = rr; t < NND; t += LPE) {
-        T o = 0;
-#pragma unroll
-        for (int q = 0; q < LPE; ++q) o += sO[z * LPE + q][t];
-        const int a = t % D1D, b = (t / D1D) % D1D, cz = t / (D1D * D1D);
-        const uint32_t I = K * ex + a, J = K * ey + b, Kz = K * ez + cz;
-        const uint32_t idx = r == 0 ? I : (r == 1 ? J : Kz), ngr = r == 0 ? ng0 : (r == 1 ? ng1 : ng2);
-        if (idx != 0 && idx != ngr - 1) unsafeAtomicAdd(&out[nh1 + r * N + Kz * ng01 + J * ng0 + I], o);
-      }
-    }
-    lds_barrier();
-  }
-  }
   // energy rows (element-owned)
 #pragma unroll
   for (int cl = 0; cl < L1D; ++cl)
 #pragma unroll
     for (int bl = 0; bl < L1D; ++bl)
 #pragma unroll
-      for (int al = 0; al < L1D; ++al) sO[lane][al + L1D * (bl + L1D * cl)] = BLx[al] * BLy[bl] * TL[cl];
+      for (int al = 0; al < L1D; ++al) sO[ln][al + L1D * (bl + L1D * cl)] = sBL[px][al] * sBL[py][bl] * TL[cl];
   lds_barrier();
-  if (active) {
-    for (int t = rr; t < NLD; t += LPE) {
+  if (pz < E) {
+    for (int t = pr; t < NLD; t += LPE) {
       T o = 0;
 #pragma unroll
-      for (int q = 0; q < LPE; ++q) o += sO[z * LPE + q][t];
-      out[2 * nh1 + (ebase + z) * NLD + t] = o;
+      for (int q = 0; q < LPE; ++q) o += sO[pz * LPE + q][t];
+      out[2 * nh1 + (ebase + pz) * NLD + t] = o;
     }
   }
   // position rows (dk_x - tau dk_v) and constrained velocity rows (dk_v), by node owner
   const T tau = T(tau_);
   const bool last_x = (ex0 + E == nx), last_y = (ey == ny - 1), last_z = (ez == P.n[2] - 1);
-  for (int i = lane; i < 3 * D1D * D1D * NS; i += 64) {
+  for (int i = ln; i < 3 * D1D * D1D * NS; i += 64) {
     const int s = i % NS, t = i / NS, b = t % D1D, cz = (t / D1D) % D1D, c = t / (D1D * D1D);
     if (s >= ns || !((s < K * E || last_x) && (b < K || last_y) && (cz < K || last_z))) continue;
     const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
@@ -529,10 +507,10 @@ template <typename T>
 static int lin3d_t(ilh_ctx* c, T* qd) {
   if (c->kp.visc)
     klaunch(c, k_lin3d<3, 4, T, 1>, lin3d_grid(c), dim3(64), 0, c->kp, make_tab3<double, 3, 4>(c),
-            (const double*)c->w64, c->lin_tau, qd, lin3d_stride(c));
+            (const double*)c->w64, c->lin_tau, qd);
   else
     klaunch(c, k_lin3d<3, 4, T, 0>, lin3d_grid(c), dim3(64), 0, c->kp, make_tab3<double, 3, 4>(c),
-            (const double*)c->w64, c->lin_tau, qd, lin3d_stride(c));
+            (const double*)c->w64, c->lin_tau, qd);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
@@ -541,10 +519,10 @@ template <typename T>
 static int apply3d_t(ilh_ctx* c, const T* dk, const T* qd, T* out) {
   if (c->kp.visc)
     klaunch(c, k_jvp3d_q<3, 4, T, 1>, lin3d_grid(c), dim3(64), 0, c->kp, make_tab3<T, 3, 4>(c), dk, qd,
-            lin3d_stride(c), c->lin_tau, out);
+            c->lin_tau, out);
   else
     klaunch(c, k_jvp3d_q<3, 4, T, 0>, lin3d_grid(c), dim3(64), 0, c->kp, make_tab3<T, 3, 4>(c), dk, qd,
-            lin3d_stride(c), c->lin_tau, out);
+            c->lin_tau, out);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }

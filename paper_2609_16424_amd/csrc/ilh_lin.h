@@ -121,14 +121,8 @@ template <int D, typename T, int VISC>
 __device__ __forceinline__ void lin_apply(const T* c, const T dJ[D][D], const T dGv[D][D], T de, T dS[D][D],
                                           T& ds) {
   constexpr int B = 2 * D * D;
-  T Ji[D][D], gv[D][D];
-#pragma unroll
-  for (int r = 0; r < D; ++r)
-#pragma unroll
-    for (int b = 0; b < D; ++b) {
-      Ji[r][b] = c[r * D + b];
-      gv[r][b] = c[D * D + r * D + b];
-    }
+  auto Ji = [&](int r, int b) { return c[r * D + b]; };
+  auto gv = [&](int r, int b) { return c[D * D + r * D + b]; };
   T U[D][D], dJi[D][D];
 #pragma unroll
   for (int a = 0; a < D; ++a)
@@ -136,30 +130,30 @@ __device__ __forceinline__ void lin_apply(const T* c, const T dJ[D][D], const T 
     for (int b = 0; b < D; ++b) {
       T acc = 0;
 #pragma unroll
-      for (int q = 0; q < D; ++q) acc += dJ[a][q] * Ji[q][b];
+      for (int q = 0; q < D; ++q) acc += dJ[a][q] * Ji(q, b);
       U[a][b] = acc;
     }
-#pragma unroll
-  for (int a = 0; a < D; ++a)
-#pragma unroll
-    for (int b = 0; b < D; ++b) {
-      T acc = 0;
-#pragma unroll
-      for (int q = 0; q < D; ++q) acc += Ji[a][q] * U[q][b];
-      dJi[a][b] = -acc;
-    }
   if constexpr (!VISC) {
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+#pragma unroll
+      for (int b = 0; b < D; ++b) {
+        T acc = 0;
+#pragma unroll
+        for (int q = 0; q < D; ++q) acc += Ji(a, q) * U[q][b];
+        dJi[a][b] = -acc;
+      }
     const T Pq = c[B], dP = c[B + 1] * de;
 #pragma unroll
     for (int r = 0; r < D; ++r)
 #pragma unroll
-      for (int a = 0; a < D; ++a) dS[r][a] = -dP * Ji[a][r] - Pq * dJi[a][r];
+      for (int a = 0; a < D; ++a) dS[r][a] = -dP * Ji(a, r) - Pq * dJi[a][r];
     T trdgv = 0, trgv = 0;
 #pragma unroll
     for (int r = 0; r < D; ++r) {
-      trgv += gv[r][r];
+      trgv += gv(r, r);
 #pragma unroll
-      for (int a = 0; a < D; ++a) trdgv += dGv[r][a] * Ji[a][r] - gv[r][a] * U[a][r];
+      for (int a = 0; a < D; ++a) trdgv += dGv[r][a] * Ji(a, r) - gv(r, a) * U[a][r];
     }
     ds = -dP * trgv - Pq * trdgv;
   } else {
@@ -171,7 +165,7 @@ __device__ __forceinline__ void lin_apply(const T* c, const T dJ[D][D], const T 
       for (int b = 0; b < D; ++b) {
         T acc = 0;
 #pragma unroll
-        for (int q = 0; q < D; ++q) acc += dGv[r][q] * Ji[q][b] - gv[r][q] * U[q][b];
+        for (int q = 0; q < D; ++q) acc += dGv[r][q] * Ji(q, b) - gv(r, q) * U[q][b];
         dgv[r][b] = acc;
       }
     T trU = 0, trdgv = 0;
@@ -180,29 +174,39 @@ __device__ __forceinline__ void lin_apply(const T* c, const T dJ[D][D], const T 
       trU += U[r][r];
       trdgv += dgv[r][r];
     }
+#pragma unroll
+    for (int a = 0; a < D; ++a)
+#pragma unroll
+      for (int b = 0; b < D; ++b) {
+        T acc = 0;
+#pragma unroll
+        for (int q = 0; q < D; ++q) acc += Ji(a, q) * U[q][b];
+        dJi[a][b] = -acc;
+      }
     const T dnu = c[B + NSYM + 2] * trU + c[B + NSYM + 3] * trdgv + c[B + NSYM + 4] * de;
     const T dP = c[B + NSYM] * de, mnu = c[B + NSYM + 1];
-    T Sig[D][D], dSig[D][D];
+    T dss = 0;
+    T dSig[D][D];
 #pragma unroll
     for (int r = 0; r < D; ++r)
 #pragma unroll
-      for (int q = 0; q < D; ++q) {
-        Sig[r][q] = c[B + sym_idx<D>(r, q)];
-        dSig[r][q] = (r == q ? -dP : T(0)) + dnu * (T(0.5) * (gv[r][q] + gv[q][r])) +
-                     mnu * (T(0.5) * (dgv[r][q] + dgv[q][r]));
+      for (int q = r; q < D; ++q) {
+        const T gs = gv(r, q) + gv(q, r), dgs = dgv[r][q] + dgv[q][r], sg = c[B + sym_idx<D>(r, q)];
+        const T v = (r == q ? -dP : T(0)) + dnu * (T(0.5) * gs) + mnu * (T(0.5) * dgs);
+        dSig[r][q] = dSig[q][r] = v;
+        // Sig and dSig are symmetric: the pair of transposed entries enters ds once, by its sum
+        dss += r == q ? v * gv(r, q) + sg * dgv[r][q] : v * gs + sg * dgs;
       }
-    T dss = 0;
+    ds = dss;
 #pragma unroll
     for (int r = 0; r < D; ++r)
 #pragma unroll
       for (int a = 0; a < D; ++a) {
         T acc = 0;
 #pragma unroll
-        for (int b = 0; b < D; ++b) acc += dSig[r][b] * Ji[a][b] + Sig[r][b] * dJi[a][b];
+        for (int b = 0; b < D; ++b) acc += dSig[r][b] * Ji(a, b) + c[B + sym_idx<D>(r, b)] * dJi[a][b];
         dS[r][a] = acc;
-        dss += dSig[r][a] * gv[r][a] + Sig[r][a] * dgv[r][a];
       }
-    ds = dss;
   }
 }
 

@@ -299,11 +299,13 @@ __global__ void __launch_bounds__(64) k_vjp2d_q(const KParams P, const Tab2<T, D
 // ---- 3D, Q2Q1: the transpose of k_jvp3d_q ------------------------------------------------
 // One wave = EPW = 4 consecutive elements of an element row, lane (element, q_x, q_y) owns a
 // quadrature column and walks q_z, as in the 3D forward kernels; the coefficients are read in
-// the layout k_lin3d stores them (row-interleaved in FP32, field-major in FP64).
+// the layout k_lin3d stores them.  FP64 keeps the lane's contractions in LDS during the walk and asks
+// for the next coefficients when the point's results are formed, so that two wavefronts fit a SIMD
+// (57x44x39 with viscosity: 815 us with one, 440 us with two; without viscosity 579 and 379 us).
 template <int D1D, int Q1D, typename T, int VISC>
-__global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb,
-                                                const T* __restrict__ y, const T* __restrict__ qd, int64_t qs,
-                                                double tau_, T* __restrict__ out) {
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_vjp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ y, const T* __restrict__ qd,
+          double tau_, T* __restrict__ out) {
   constexpr int K = D1D - 1, L1D = K, NLD = L1D * L1D * L1D;
   constexpr int LPE = Q1D * Q1D, EPW = 64 / LPE;
   constexpr int NS = K * EPW + 1;
@@ -314,7 +316,11 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
 
   __shared__ T sS[NF][D1D][D1D][NS];
   __shared__ T sE[EPW * NLD];
-  __shared__ T sO[64][NOP];
+  // during the column walk in FP64 the lane's contractions; after it the output columns (lane, node)
+  constexpr bool PLDS = sizeof(T) == 8;
+  constexpr int NPC = 9 * D1D, NU = PLDS && NPC > NOP ? NPC : NOP;
+  __shared__ T sU[64 * NU];
+  auto sO = reinterpret_cast<T(*)[NOP]>(sU);
   __shared__ T sBG[2][Q1D][D1D];
   __shared__ T sBL[Q1D][L1D];
 
@@ -345,6 +351,14 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
   }
 #pragma unroll
   for (int r = 0; r < RL; ++r) lr[r] = ld32(y, 2 * nh1 + ebase * NLD + min(lane + 64 * r, E * NLD - 1));
+  const T* __restrict__ qb = qd + (int64_t)tile * (Q1D * NQD * 64);
+  T cf[NQD];
+  auto ldstep = [&](const int qz) {
+    const T* rb = sbase(qb + qz * (NQD * 64));
+#pragma unroll
+    for (int f = 0; f < NQD; ++f) cf[f] = ld32(rb, (uint32_t)(f * 64 + lane));
+  };
+  ldstep(0);
   const int zl = lane / LPE;
   const double rj_l = P.rj0[ebase + (zl < E ? zl : 0)];
   for (int i = lane; i < Q1D * D1D; i += 64) {
@@ -365,7 +379,6 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
   lds_barrier();
 
   const int z = lane / LPE, rr = lane - z * LPE, qy = rr / Q1D, qx = rr - qy * Q1D;
-  const bool active = z < E;
   // per-lane sums over the column for the position (X*) and velocity (V*) rows: coefficients of
   // G_x B_y (x), B_x G_y (y), B_x B_y (z: derivative along z plus the value terms) per layer
   T Xx[3][D1D], Xy[3][D1D], Xz[3][D1D], Vx[3][D1D], Vy[3][D1D], Vz[3][D1D], TL[L1D];
@@ -375,7 +388,7 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
     for (int c = 0; c < D1D; ++c) Xx[r][c] = Xy[r][c] = Xz[r][c] = Vx[r][c] = Vy[r][c] = Vz[r][c] = T(0);
 #pragma unroll
   for (int cl = 0; cl < L1D; ++cl) TL[cl] = T(0);
-  if (active) {
+  {  // lanes past the strip walk along: their columns feed no output
     const int s0 = K * z;
     T Bx[D1D], Gx[D1D], By[D1D], Gy[D1D];
 #pragma unroll
@@ -385,6 +398,7 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
       By[a] = sBG[0][qy][a];
       Gy[a] = sBG[1][qy][a];
     }
+    T* const pc = sU + lane * NPC;
     T BB[3][D1D], GB[3][D1D], BG[3][D1D];
 #pragma unroll
     for (int f = 0; f < 3; ++f)
@@ -404,9 +418,15 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
           gb += By[b] * ag;
           bg += Gy[b] * ab;
         }
-        BB[f][cz] = bb;
-        GB[f][cz] = gb;
-        BG[f][cz] = bg;
+        if constexpr (PLDS) {
+          pc[(f * D1D + cz) * 3] = gb;
+          pc[(f * D1D + cz) * 3 + 1] = bg;
+          pc[(f * D1D + cz) * 3 + 2] = bb;
+        } else {
+          BB[f][cz] = bb;
+          GB[f][cz] = gb;
+          BG[f][cz] = bg;
+        }
       }
     T EL[L1D];
 #pragma unroll
@@ -420,19 +440,10 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
       EL[cl] = acc;
     }
     const T wxy = tb.W[qx] * tb.W[qy] * T(rj_l);
-    constexpr bool ROWS = sizeof(T) == 4;
-    const T* __restrict__ qb = qd + (int64_t)tile * (Q1D * (ROWS ? NQD : 1) * 64);
 #pragma unroll 1
     for (int qz = 0; qz < Q1D; ++qz) {
-      T cf[NQD];
-      if constexpr (ROWS) {
-        const T* rb = sbase(qb + qz * (NQD * 64));
-#pragma unroll
-        for (int f = 0; f < NQD; ++f) cf[f] = ld32(rb, (uint32_t)(f * 64 + lane));
-      } else {
-#pragma unroll
-        for (int f = 0; f < NQD; ++f) cf[f] = ld32(sbase(qb + f * qs), (uint32_t)(qz * 64 + lane));
-      }
+      if constexpr (PLDS) asm volatile("" ::: "memory");  // the contractions are read again each step
+      else if (qz) ldstep(qz);
       T A[3][3], yv[3];
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
@@ -440,15 +451,16 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
 #pragma unroll
         for (int c = 0; c < D1D; ++c) {
           const T Bz = tb.B[qz][c], Gz = tb.G[qz][c];
-          a0 += Bz * GB[r][c];
-          a1 += Bz * BG[r][c];
-          a2 += Gz * BB[r][c];
-          m += Bz * BB[r][c];
+          const T bb = PLDS ? pc[(r * D1D + c) * 3 + 2] : BB[r][c];
+          a0 += Bz * (PLDS ? pc[(r * D1D + c) * 3] : GB[r][c]);
+          a1 += Bz * (PLDS ? pc[(r * D1D + c) * 3 + 1] : BG[r][c]);
+          a2 += Gz * bb;
+          if constexpr (!PLDS) m += Bz * bb;
         }
         A[r][0] = a0;
         A[r][1] = a1;
         A[r][2] = a2;
-        yv[r] = m;
+        if constexpr (!PLDS) yv[r] = m;
       }
       T ye = 0;
 #pragma unroll
@@ -456,6 +468,25 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
       const T mq = wxy * tb.W[qz];
       T GJ[3][3], GGv[3][3], ge;
       lin_apply_t<3, T, VISC>(cf, A, -ye, GJ, GGv, ge);
+      if constexpr (PLDS) {
+        // the point's results are formed before the next coefficients are asked for: both sets in
+        // registers at once would not fit at two wavefronts per SIMD
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+          asm volatile(""
+                       : "+v"(GJ[r][0]), "+v"(GJ[r][1]), "+v"(GJ[r][2]), "+v"(GGv[r][0]), "+v"(GGv[r][1]),
+                         "+v"(GGv[r][2])
+                       :
+                       : "memory");
+        asm volatile("" : "+v"(ge) : : "memory");
+        if (qz + 1 < Q1D) ldstep(qz + 1);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {  // read again: six registers fewer across the point's arithmetic
+          yv[r] = T(0);
+#pragma unroll
+          for (int c = 0; c < D1D; ++c) yv[r] += tb.B[qz][c] * pc[(r * D1D + c) * 3 + 2];
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
 #pragma unroll
@@ -474,18 +505,23 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
       for (int cl = 0; cl < L1D; ++cl) TL[cl] += tb.BL[qz][cl] * te;
     }
   }
+  // the lane's indices once more, from a value the compiler does not connect with the first: what the
+  // gather and the column walk derived from them is not kept in registers up to here
+  int ln = threadIdx.x;
+  asm volatile("" : "+v"(ln));
+  const int pz = ln / LPE, pq = ln - pz * LPE, py = pq / Q1D, px = pq - py * Q1D;
   // H1 rows (position part, then velocity part), one component at a time: factored expansion of
   // each lane's column sums into sO, node sums over the (one or two) elements of the strip
   // holding the node, the owner's identity terms, one atomic per node and strip
-  const T Bxl[D1D] = {sBG[0][qx][0], sBG[0][qx][1], sBG[0][qx][2]};
-  const T Gxl[D1D] = {sBG[1][qx][0], sBG[1][qx][1], sBG[1][qx][2]};
-  const T Byl[D1D] = {sBG[0][qy][0], sBG[0][qy][1], sBG[0][qy][2]};
-  const T Gyl[D1D] = {sBG[1][qy][0], sBG[1][qy][1], sBG[1][qy][2]};
+  const T Bxl[D1D] = {sBG[0][px][0], sBG[0][px][1], sBG[0][px][2]};
+  const T Gxl[D1D] = {sBG[1][px][0], sBG[1][px][1], sBG[1][px][2]};
+  const T Byl[D1D] = {sBG[0][py][0], sBG[0][py][1], sBG[0][py][2]};
+  const T Gyl[D1D] = {sBG[1][py][0], sBG[1][py][1], sBG[1][py][2]};
   const bool last_x = (ex0 + E == nx), last_y = (ey == ny - 1), last_z = (ez == P.n[2] - 1);
 #pragma unroll 1
   for (int pr = 0; pr < 6; ++pr) {
     const int part = pr / 3, r = pr % 3;
-    if (active) {
+    if (pz < E) {
 #pragma unroll
       for (int cz = 0; cz < D1D; ++cz) {
         T tx = 0, ty = 0, tzv = 0;
@@ -500,12 +536,12 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
         for (int a = 0; a < D1D; ++a) {
           const T q1 = Gxl[a] * tx + Bxl[a] * tzv, q2 = Bxl[a] * ty;
 #pragma unroll
-          for (int b = 0; b < D1D; ++b) sO[lane][(cz * D1D + b) * D1D + a] = Byl[b] * q1 + Gyl[b] * q2;
+          for (int b = 0; b < D1D; ++b) sO[ln][(cz * D1D + b) * D1D + a] = Byl[b] * q1 + Gyl[b] * q2;
         }
       }
     }
     lds_barrier();
-    for (int i = lane; i < D1D * D1D * NS; i += 64) {
+    for (int i = ln; i < D1D * D1D * NS; i += 64) {
       const int s = i % NS, t = i / NS, b = t % D1D, cz = t / D1D;
       if (s >= ns) continue;
       const int zz = s / K, a = s - K * zz;
@@ -536,21 +572,21 @@ __global__ void __launch_bounds__(64) k_vjp3d_q(const KParams P, const Tab2<T, D
     lds_barrier();
   }
   // energy rows (element-owned)
-  if (active) {
+  if (pz < E) {
 #pragma unroll
     for (int cl = 0; cl < L1D; ++cl)
 #pragma unroll
       for (int bl = 0; bl < L1D; ++bl)
 #pragma unroll
-        for (int al = 0; al < L1D; ++al) sO[lane][al + L1D * (bl + L1D * cl)] = sBL[qx][al] * sBL[qy][bl] * TL[cl];
+        for (int al = 0; al < L1D; ++al) sO[ln][al + L1D * (bl + L1D * cl)] = sBL[px][al] * sBL[py][bl] * TL[cl];
   }
   lds_barrier();
-  if (active) {
-    for (int t = rr; t < NLD; t += LPE) {
+  if (pz < E) {
+    for (int t = pq; t < NLD; t += LPE) {
       T o = 0;
 #pragma unroll
-      for (int q = 0; q < LPE; ++q) o += sO[z * LPE + q][t];
-      out[2 * nh1 + (ebase + z) * NLD + t] = o;
+      for (int q = 0; q < LPE; ++q) o += sO[pz * LPE + q][t];
+      out[2 * nh1 + (ebase + pz) * NLD + t] = o;
     }
   }
 }
@@ -600,11 +636,10 @@ template <typename T>
 static int dispatch_vjp3(ilh_ctx* c, const T* y, const T* qd, T* out) {
   constexpr int EPW = 4;
   const dim3 g((c->n[0] + EPW - 1) / EPW, c->n[1], c->n[2]);
-  const int64_t qs = (int64_t)g.x * g.y * g.z * 4 * 64;
   if (c->kp.visc)
-    klaunch(c, k_vjp3d_q<3, 4, T, 1>, g, dim3(64), 0, c->kp, vjp_tab2<T, 3, 4>(c), y, qd, qs, c->lin_tau, out);
+    klaunch(c, k_vjp3d_q<3, 4, T, 1>, g, dim3(64), 0, c->kp, vjp_tab2<T, 3, 4>(c), y, qd, c->lin_tau, out);
   else
-    klaunch(c, k_vjp3d_q<3, 4, T, 0>, g, dim3(64), 0, c->kp, vjp_tab2<T, 3, 4>(c), y, qd, qs, c->lin_tau, out);
+    klaunch(c, k_vjp3d_q<3, 4, T, 0>, g, dim3(64), 0, c->kp, vjp_tab2<T, 3, 4>(c), y, qd, c->lin_tau, out);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
