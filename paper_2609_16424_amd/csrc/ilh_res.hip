@@ -332,12 +332,20 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 
 // ---- 3D, Q2Q1 (no TG source): the lane map of the 3D linearised kernels ---------------------
 // One wave = EPW elements of one element row (fixed y, z), lane (z, qy, qx) = quadrature column
-// (qx, qy) of element z walking its Q1D points in z.  Each velocity component's element sums go
-// through LDS over the element's lanes and take one atomic per node and element.
-template <int D1D, int Q1D>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1)))
-k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restrict__ u,
+// (qx, qy) of element z walking its Q1D points in z.  The lane's position contractions wait in LDS
+// during the walk (where the output columns go after it).  Each velocity component's sums over the
+// strip's columns go through LDS and take one atomic per node and strip.
+// Bound by FP64 arithmetic (about 3000 vector instructions a wave); one wavefront per SIMD left half
+// of the cycles idle, so registers (212, 252 with viscosity) and LDS (20 KB a wave) are laid out for
+// two, and the viscosity switch is fixed at compile time.  72^3 Q2Q1: 1250 us with one wavefront,
+// the contractions in registers and one atomic per node and element, 800 us now; 57x44x39 with
+// viscosity 430 and 331 us.
+template <int D1D, int Q1D, int VISC>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+k_res3d(const KParams P_, const Tab2<double, D1D, Q1D> tb, const double* __restrict__ u,
         const double* __restrict__ kk, double tau, double* __restrict__ r, double* __restrict__ dmin) {
+  KParams P = P_;
+  P.visc = VISC;  // the switch of the point's arithmetic, known here
   constexpr int K = D1D - 1, L1D = K, NLD = L1D * L1D * L1D;
   constexpr int LPE = Q1D * Q1D, EPW = 64 / LPE;
   constexpr int NS = K * EPW + 1;
@@ -348,7 +356,9 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 
   __shared__ double sW[9][D1D][D1D][NS];  // w_x (3), w_v (3), k_v (3)
   __shared__ double sE[2][NLS];           // w_e, k_e
-  __shared__ double sO[64][NOP];
+  constexpr int NPC = 9 * D1D, NU = NPC > NOP ? NPC : NOP;
+  __shared__ double sU[64 * NU];  // (lane, position contraction), then the output columns (lane, node)
+  auto sO = reinterpret_cast<double(*)[NOP]>(sU);
   __shared__ double sBG[2][Q1D][D1D];
   __shared__ double sBL[Q1D][L1D];
 
@@ -428,7 +438,7 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 #pragma unroll
   for (int cl = 0; cl < L1D; ++cl) TL[cl] = 0.0;
   double dm = 1e300;  // the lane's smallest det J (dmin set)
-  if (active) {
+  {  // lanes past the strip walk along: their columns feed no output
     const int s0 = K * z;
     double Bx[D1D], Gx[D1D], By[D1D], Gy[D1D], BLx[L1D], BLy[L1D];
 #pragma unroll
@@ -446,6 +456,7 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
     // x-y contractions per z-layer: values BB, x-derivatives GB, y-derivatives BG of w_x and
     // w_v; values of k_v
     double BB[6][D1D], GB[6][D1D], BG[6][D1D], KB[3][D1D];
+    double* const pc = sU + lane * NPC;
 #pragma unroll
     for (int f = 0; f < 6; ++f)
 #pragma unroll
@@ -464,9 +475,15 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
           gb += By[b] * ag;
           bg += Gy[b] * ab;
         }
-        BB[f][cz] = bb;
-        GB[f][cz] = gb;
-        BG[f][cz] = bg;
+        if (f < 3) {
+          pc[(f * D1D + cz) * 3] = gb;
+          pc[(f * D1D + cz) * 3 + 1] = bg;
+          pc[(f * D1D + cz) * 3 + 2] = bb;
+        } else {
+          BB[f][cz] = bb;
+          GB[f][cz] = gb;
+          BG[f][cz] = bg;
+        }
       }
 #pragma unroll
     for (int c = 0; c < 3; ++c)
@@ -501,6 +518,7 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
     const double wxy = tb.W[qx] * tb.W[qy] * rj_l;
 #pragma unroll 1
     for (int qz = 0; qz < Q1D; ++qz) {
+      asm volatile("" ::: "memory");  // the contractions in LDS are read again each step
       double J[3][3], Gv[3][3], kv[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -508,9 +526,9 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 #pragma unroll
         for (int cz = 0; cz < D1D; ++cz) {
           const double Bz = tb.B[qz][cz], Gz = tb.G[qz][cz];
-          j0 += Bz * GB[c][cz];
-          j1 += Bz * BG[c][cz];
-          j2 += Gz * BB[c][cz];
+          j0 += Bz * pc[(c * D1D + cz) * 3];
+          j1 += Bz * pc[(c * D1D + cz) * 3 + 1];
+          j2 += Gz * pc[(c * D1D + cz) * 3 + 2];
           g0 += Bz * GB[3 + c][cz];
           g1 += Bz * BG[3 + c][cz];
           g2 += Gz * BB[3 + c][cz];
@@ -531,7 +549,7 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
         ke += tb.BL[qz][cl] * EK[cl];
       }
       const double mq = wxy * tb.W[qz];
-      if (dmin)
+      if (dmin && active)
         dm = nan_min(dm, J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) -
                           J[0][1] * (J[1][0] * J[2][2] - J[1][2] * J[2][0]) +
                           J[0][2] * (J[1][0] * J[2][1] - J[1][1] * J[2][0]));
@@ -553,19 +571,24 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
       for (int cl = 0; cl < L1D; ++cl) TL[cl] += tb.BL[qz][cl] * cl_;
     }
   }
-  // velocity rows, one component at a time: column contributions to the element's nodes,
-  // summed over the element's LPE lanes, one atomic per node and element (constrained rows were
-  // written by their owner above)
+  // the lane's indices once more, from a value the compiler does not connect with the first: what the
+  // gather and the column walk derived from them is not kept in registers up to here
+  int ln = threadIdx.x;
+  asm volatile("" : "+v"(ln));
+  const int pz = ln / LPE, pq = ln - pz * LPE, py = pq / Q1D, px = pq - py * Q1D;
+  // velocity rows, one component at a time: each lane's column contributions to its element's
+  // nodes (factored: out(a,b) = By_b (Gx_a Tx + Bx_a Tz) + Gy_b Bx_a Ty per z-layer) go to LDS; one
+  // thread per node of the strip sums the columns of the (one or two) elements holding it and issues
+  // one atomic add (constrained rows were written by their owner above)
   {
     double Bx[D1D], Gx[D1D], By[D1D], Gy[D1D];
 #pragma unroll
     for (int a = 0; a < D1D; ++a) {
-      Bx[a] = sBG[0][qx][a];
-      Gx[a] = sBG[1][qx][a];
-      By[a] = sBG[0][qy][a];
-      Gy[a] = sBG[1][qy][a];
+      Bx[a] = sBG[0][px][a];
+      Gx[a] = sBG[1][px][a];
+      By[a] = sBG[0][py][a];
+      Gy[a] = sBG[1][py][a];
     }
-    const int ex = ex0 + z;
 #pragma unroll 1
     for (int c = 0; c < 3; ++c) {
 #pragma unroll
@@ -579,22 +602,30 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
             tz = Tz[cq][cz];
           }
 #pragma unroll
-        for (int b = 0; b < D1D; ++b)
+        for (int a = 0; a < D1D; ++a) {
+          const double q1 = Gx[a] * tx + Bx[a] * tz, q2 = Bx[a] * ty;
 #pragma unroll
-          for (int a = 0; a < D1D; ++a)
-            sO[lane][(cz * D1D + b) * D1D + a] = Gx[a] * By[b] * tx + Bx[a] * Gy[b] * ty + Bx[a] * By[b] * tz;
+          for (int b = 0; b < D1D; ++b) sO[ln][(cz * D1D + b) * D1D + a] = By[b] * q1 + Gy[b] * q2;
+        }
       }
       lds_barrier();
-      if (active) {
-        for (int t = rr; t < NND; t += LPE) {
-          double o = 0;
+      for (int i = ln; i < D1D * D1D * NS; i += 64) {
+        const int s = i % NS, t = i / NS, b = t % D1D, cz = t / D1D;
+        if (s >= ns) continue;
+        const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
+        const uint32_t idx = c == 0 ? I : (c == 1 ? J : Kz), ngc = c == 0 ? ng0 : (c == 1 ? ng1 : ng2);
+        if (idx == 0 || idx == ngc - 1) continue;
+        const int zz = s / K, a = s - K * zz;
+        double o = 0;
+        if (zz < E) {
 #pragma unroll
-          for (int q = 0; q < LPE; ++q) o += sO[z * LPE + q][t];
-          const int a = t % D1D, b = (t / D1D) % D1D, cz = t / (D1D * D1D);
-          const uint32_t I = K * ex + a, J = K * ey + b, Kz = K * ez + cz;
-          const uint32_t idx = c == 0 ? I : (c == 1 ? J : Kz), ngc = c == 0 ? ng0 : (c == 1 ? ng1 : ng2);
-          if (idx != 0 && idx != ngc - 1) unsafeAtomicAdd(&r[nh1 + c * N + Kz * ng01 + J * ng0 + I], o);
+          for (int q = 0; q < LPE; ++q) o += sO[zz * LPE + q][(cz * D1D + b) * D1D + a];
         }
+        if (a == 0 && zz > 0) {
+#pragma unroll
+          for (int q = 0; q < LPE; ++q) o += sO[(zz - 1) * LPE + q][(cz * D1D + b) * D1D + K];
+        }
+        unsafeAtomicAdd(&r[nh1 + c * N + row0 + cz * ng01 + b * ng0 + s], o);
       }
       lds_barrier();
     }
@@ -604,28 +635,28 @@ k_res3d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
     double BLx[L1D], BLy[L1D];
 #pragma unroll
     for (int a = 0; a < L1D; ++a) {
-      BLx[a] = sBL[qx][a];
-      BLy[a] = sBL[qy][a];
+      BLx[a] = sBL[px][a];
+      BLy[a] = sBL[py][a];
     }
 #pragma unroll
     for (int cl = 0; cl < L1D; ++cl)
 #pragma unroll
       for (int bl = 0; bl < L1D; ++bl)
 #pragma unroll
-        for (int al = 0; al < L1D; ++al) sO[lane][al + L1D * (bl + L1D * cl)] = BLx[al] * BLy[bl] * TL[cl];
+        for (int al = 0; al < L1D; ++al) sO[ln][al + L1D * (bl + L1D * cl)] = BLx[al] * BLy[bl] * TL[cl];
   }
   lds_barrier();
   if (dmin) {  // the work-group's smallest det J of the stage positions w_x
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) dm = nan_min(dm, __shfl_xor(dm, o, 64));
-    if (lane == 0) dmin[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = dm;
+    if (ln == 0) dmin[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = dm;
   }
-  if (active) {
-    for (int t = rr; t < NLD; t += LPE) {
+  if (pz < E) {
+    for (int t = pq; t < NLD; t += LPE) {
       double o = 0;
 #pragma unroll
-      for (int q = 0; q < LPE; ++q) o += sO[z * LPE + q][t];
-      r[2 * nh1 + (ebase + z) * NLD + t] = o;
+      for (int q = 0; q < LPE; ++q) o += sO[pz * LPE + q][t];
+      r[2 * nh1 + (ebase + pz) * NLD + t] = o;
     }
   }
 }
@@ -675,7 +706,10 @@ int launch_res3d(ilh_ctx* c, const double* k, const double* u, double tau, doubl
     tb.W[q] = c->h_w1[q];
   }
   const dim3 grid((c->n[0] + EPW - 1) / EPW, c->n[1], c->n[2]);
-  klaunch(c, k_res3d<D1D, Q1D>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin);
+  if (c->kp.visc)
+    klaunch(c, k_res3d<D1D, Q1D, 1>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin);
+  else
+    klaunch(c, k_res3d<D1D, Q1D, 0>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
