@@ -23,6 +23,9 @@
 namespace ilh {
 
 // ---- linearisation: state w (FP64) -> stored coefficients (T) ----------------------------
+// Bound by the coefficients it writes.  Rows of 60 of 64 lanes (six points a row, ten elements) left
+// the last cache line of each row partly written, which the memory completes by reading it: 1024^2
+// Q3Q2 in FP32 (1.94 GB) took 730 us, with whole lines 440 us.
 template <int D1D, int Q1D, typename T, int VISC, int SRC>
 __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double, D1D, Q1D> tb,
                                               const double* __restrict__ w, double tau, T* __restrict__ qd,
@@ -43,22 +46,25 @@ __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double
   const int nx = P.n[0];
   const int E = min(EPW, nx - ex0);
   const int ns = K * E + 1;
-  const int64_t ng0 = P.ng[0];
-  const int64_t N = P.N, nh1 = 2 * P.N;
-  const int64_t ebase = (int64_t)ey * nx + ex0;
+  const uint32_t ng0 = P.ng[0], N = (uint32_t)P.N, nh1 = 2 * N;
+  const uint32_t ebase = (uint32_t)ey * nx + ex0;
 
   constexpr int NTS = 4 * D1D * NS, RT = (NTS + 63) / 64;
   double tr[RT];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    const int i = lane + 64 * r, si = i % NS, t = i / NS, b = t % D1D, f = t / D1D;
-    tr[r] = 0.0;
-    if (i < NTS && si < ns) {
-      const int64_t node = (int64_t)(K * ey + b) * ng0 + (int64_t)K * ex0 + si;
-      tr[r] = w[(f < 2 ? f * N : nh1 + (f - 2) * N) + node];
-    }
+    // branch-free: lanes past the strip re-read its last node
+    const int i = lane + 64 * r, si = min(i % NS, ns - 1), t = min(i / NS, 4 * D1D - 1), b = t % D1D, f = t / D1D;
+    tr[r] = ld32(w, (f < 2 ? f * N : nh1 + (f - 2) * N) + (K * ey + b) * ng0 + K * ex0 + si);
   }
-  for (int i = lane; i < EPW * NLD; i += 64) sE[i] = (i < E * NLD) ? w[2 * nh1 + ebase * NLD + i] : 0.0;
+  constexpr int NLS = EPW * NLD, RL = (NLS + 63) / 64;
+  double lr[RL];
+#pragma unroll
+  for (int r = 0; r < RL; ++r) lr[r] = ld32(w, 2 * nh1 + ebase * NLD + min(lane + 64 * r, E * NLD - 1));
+  // the lanes past the strip repeat points of its last element: with every lane storing, the rows of
+  // coefficients are whole cache lines
+  const int z0 = lane / Q1D, z = min(z0, E - 1), qx = lane - z0 * Q1D;
+  const double gam = P.gamma[ebase + z], dJ0 = P.j0e[ebase + z], rj = P.rj0[ebase + z];
   for (int i = lane; i < Q1D * D1D; i += 64) {
     sBG[0][i / D1D][i % D1D] = tb.B[i / D1D][i % D1D];
     sBG[1][i / D1D][i % D1D] = tb.G[i / D1D][i % D1D];
@@ -69,12 +75,14 @@ __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double
     const int i = lane + 64 * r;
     if (i < NTS) (&sS[0][0][0])[i] = tr[r];
   }
-  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < RL; ++r) {
+    const int i = lane + 64 * r;
+    if (i < NLS) sE[i] = lr[r];
+  }
+  lds_barrier();
 
-  const int z = lane / Q1D, qx = lane - z * Q1D;
-  if (z >= E) return;  // no barrier follows
   const int s0 = K * z;
-  const int64_t e = ebase + z;
   double Bq[D1D], Gq[D1D], BLq[L1D];
 #pragma unroll
   for (int a = 0; a < D1D; ++a) {
@@ -106,8 +114,7 @@ __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double
     for (int al = 0; al < L1D; ++al) a0 += BLq[al] * sE[z * NLD + al + L1D * bl];
     ALe[bl] = a0;
   }
-  const double gam = P.gamma[e], dJ0 = P.j0e[e];
-  const double wx = tb.W[qx] * P.rj0[e];
+  const double wx = tb.W[qx] * rj;
   const int64_t blk = tile;
 #pragma unroll 1
   for (int qy = 0; qy < Q1D; ++qy) {

@@ -44,20 +44,27 @@ __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double
   const int nx = P.n[0], ny = P.n[1];
   const int E = min(EPW, nx - ex0);
   const int ns = K * E + 1;
-  const int64_t ng0 = P.ng[0], ng01 = (int64_t)P.ng[0] * P.ng[1];
-  const int64_t N = P.N, nh1 = 3 * P.N;
-  const int64_t ebase = ((int64_t)ez * ny + ey) * nx + ex0;
-  const int64_t row0 = (int64_t)(K * ez) * ng01 + (int64_t)(K * ey) * ng0 + (int64_t)K * ex0;
+  const uint32_t ng0 = P.ng[0], ng01 = ng0 * P.ng[1], N = (uint32_t)P.N, nh1 = 3 * N;
+  const uint32_t ebase = ((uint32_t)ez * ny + ey) * nx + ex0;
+  const uint32_t row0 = (uint32_t)(K * ez) * ng01 + (uint32_t)(K * ey) * ng0 + (uint32_t)(K * ex0);
 
   constexpr int NTS = NF * D1D * D1D * NS, RT = (NTS + 63) / 64;
   double tr[RT];
 #pragma unroll
   for (int r = 0; r < RT; ++r) {
-    const int i = lane + 64 * r, s = i % NS, t = i / NS, b = t % D1D, cz = (t / D1D) % D1D, f = t / (D1D * D1D);
-    tr[r] = 0.0;
-    if (i < NTS && s < ns) tr[r] = w[(f < 3 ? f * N : nh1 + (f - 3) * N) + row0 + cz * ng01 + b * ng0 + s];
+    // branch-free: lanes past the strip re-read its last node
+    const int i = lane + 64 * r, s = min(i % NS, ns - 1), t = min(i / NS, NF * D1D * D1D - 1), b = t % D1D,
+              cz = (t / D1D) % D1D, f = t / (D1D * D1D);
+    tr[r] = ld32(w, (f < 3 ? f * N : nh1 + (f - 3) * N) + row0 + cz * ng01 + b * ng0 + s);
   }
-  for (int i = lane; i < EPW * NLD; i += 64) sE[i] = (i < E * NLD) ? w[2 * nh1 + ebase * NLD + i] : 0.0;
+  constexpr int NLS = EPW * NLD, RL = (NLS + 63) / 64;
+  double lr[RL];
+#pragma unroll
+  for (int r = 0; r < RL; ++r) lr[r] = ld32(w, 2 * nh1 + ebase * NLD + min(lane + 64 * r, E * NLD - 1));
+  // the lanes past the strip repeat points of its last element: with every lane storing, the rows of
+  // coefficients are whole cache lines
+  const int z0 = lane / LPE, z = min(z0, E - 1), rr = lane - z0 * LPE, qy = rr / Q1D, qx = rr - qy * Q1D;
+  const double gam = P.gamma[ebase + z], dJ0 = P.j0e[ebase + z], rj = P.rj0[ebase + z];
   for (int i = lane; i < Q1D * D1D; i += 64) {
     sBG[0][i / D1D][i % D1D] = tb.B[i / D1D][i % D1D];
     sBG[1][i / D1D][i % D1D] = tb.G[i / D1D][i % D1D];
@@ -68,12 +75,14 @@ __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double
     const int i = lane + 64 * r;
     if (i < NTS) (&sS[0][0][0][0])[i] = tr[r];
   }
+#pragma unroll
+  for (int r = 0; r < RL; ++r) {
+    const int i = lane + 64 * r;
+    if (i < NLS) sE[i] = lr[r];
+  }
   lds_barrier();
 
-  const int z = lane / LPE, rr = lane - z * LPE, qy = rr / Q1D, qx = rr - qy * Q1D;
-  if (z >= E) return;  // no barrier follows
   const int s0 = K * z;
-  const int64_t e = ebase + z;
   double Bx[D1D], Gx[D1D], By[D1D], Gy[D1D], BLx[L1D], BLy[L1D];
 #pragma unroll
   for (int a = 0; a < D1D; ++a) {
@@ -121,8 +130,7 @@ __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double
       for (int al = 0; al < L1D; ++al) acc += BLy[bl] * BLx[al] * sE[z * NLD + al + L1D * (bl + L1D * cl)];
     EL[cl] = acc;
   }
-  const double gam = P.gamma[e], dJ0 = P.j0e[e];
-  const double wxy = tb.W[qx] * tb.W[qy] * P.rj0[e];
+  const double wxy = tb.W[qx] * tb.W[qy] * rj;
   const int64_t blk = tile;
 #pragma unroll 1
   for (int qz = 0; qz < Q1D; ++qz) {
