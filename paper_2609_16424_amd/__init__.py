@@ -118,7 +118,7 @@ class Hydro:
             raise IlhError(st, self.lib.ilh_last_error(self.ctx).decode())
 
     def _stream(self):
-        self.lib.ilh_set_stream(self.ctx, C.c_void_p(torch.cuda.current_stream(self.device).cuda_stream))
+        self.lib.ilh_set_stream(self.ctx, torch._C._cuda_getCurrentRawStream(self.device.index))
 
     def _vec(self, t, n, dtype=torch.float64, name="vector"):
         if not isinstance(t, torch.Tensor) or t.device != self.device or t.dtype != dtype:
@@ -129,6 +129,10 @@ class Hydro:
 
     def new(self, n=None, dtype=torch.float64):
         return torch.zeros(self.nblock if n is None else n, dtype=dtype, device=self.device)
+
+    def _out(self, dtype=torch.float64):
+        """A block vector for a call that writes all of it."""
+        return torch.empty(self.nblock, dtype=dtype, device=self.device)
 
     def split(self, u):
         return u[:self.nh1], u[self.nh1:2 * self.nh1], u[2 * self.nh1:]
@@ -155,7 +159,7 @@ class Hydro:
         return df1, dftv
 
     def residual(self, k, u, tau, out=None):
-        r = self.new() if out is None else out
+        r = self._out() if out is None else out
         self._stream()
         self._check(self.lib.ilh_residual(self.ctx, self._vec(k, self.nblock, name="k"),
                                           self._vec(u, self.nblock, name="u"), float(tau), _ptr(r)))
@@ -168,20 +172,19 @@ class Hydro:
 
     def jvp_lin(self, dk, prec=64, out=None):
         dt = torch.float64 if prec == 64 else torch.float32
-        o = self.new(dtype=dt) if out is None else out
+        o = self._out(dt) if out is None else out
         self._stream()
         self._check(self.lib.ilh_jvp_lin(self.ctx, prec, self._vec(dk, self.nblock, dt, "dk"),
                                          self._vec(o, self.nblock, dt, "out")))
         return o
 
     def jvp(self, k, u, tau, dk, prec=64):
-        self.linearize(k, u, tau)
-        return self.jvp_lin(dk, prec)
+        return self._one_shot(self.lib.ilh_jvp, k, u, tau, dk, "dk", prec)
 
     def vjp_lin(self, y, prec=64, out=None):
         """Transpose Jacobian action J^T y at the stored linearisation point (2D k = 2, 3; 3D k = 2)."""
         dt = torch.float64 if prec == 64 else torch.float32
-        o = self.new(dtype=dt) if out is None else out
+        o = self._out(dt) if out is None else out
         self._stream()
         self._check(self.lib.ilh_vjp_lin(self.ctx, prec, self._vec(y, self.nblock, dt, "y"),
                                          self._vec(o, self.nblock, dt, "out")))
@@ -192,7 +195,7 @@ class Hydro:
         on the device; `out`, if given, receives the result so that the call makes no allocation
         through torch either)."""
         dt = torch.float64 if prec == 64 else torch.float32
-        o = self.new(dtype=dt) if out is None else out
+        o = self._out(dt) if out is None else out
         self._stream()
         self._check(self.lib.ilh_jvp_noalloc(self.ctx, prec, self._vec(k, self.nblock, name="k"),
                                              self._vec(u, self.nblock, name="u"), float(tau),
@@ -201,8 +204,16 @@ class Hydro:
         return o
 
     def vjp(self, k, u, tau, y, prec=64):
-        self.linearize(k, u, tau)
-        return self.vjp_lin(y, prec)
+        return self._one_shot(self.lib.ilh_vjp, k, u, tau, y, "y", prec)
+
+    def _one_shot(self, f, k, u, tau, x, name, prec):
+        """Linearisation at (k, u, tau) and one action on x (f: ilh_jvp, ilh_vjp)."""
+        dt = torch.float64 if prec == 64 else torch.float32
+        o = self._out(dt)
+        self._stream()
+        self._check(f(self.ctx, prec, self._vec(k, self.nblock, name="k"), self._vec(u, self.nblock, name="u"),
+                      float(tau), self._vec(x, self.nblock, dt, name), _ptr(o)))
+        return o
 
     def rk2avg_step(self, u, dt):
         """One explicit RK2-average step, u updated in place (2D)."""
