@@ -29,12 +29,13 @@ namespace ilh {
 static constexpr int TM_W = 4;   // waves per work-group
 static constexpr int TM_U = 16;  // multiplies whose operands are in flight together
 
-// The 1D inverse mass matrix on the n k + 1 nodes of a direction, scaled by `scale`, as rows of
-// 2 bw + 1 band entries (row i, offset o: column i + o - bw); with lo / hi, the end node is held (its
-// row and column zero).  Banded Cholesky (half bandwidth k) in extended precision, so that the weights
-// are the inverse's entries rounded once, then every column by substitution over
-// a window wide enough that what it leaves out is below 1e-25.
-static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool hi, double scale, int* bw_out) {
+// The 1D inverse mass matrix on the n k + 1 nodes of a direction as rows of 2 bw + 1 band entries (row
+// i, offset o: column i + o - bw); with lo / hi, the end node is held (its row and column zero).
+// Banded Cholesky (half bandwidth k) in extended precision, so that the weights are the inverse's
+// entries rounded once, then the columns by substitution over a window wide enough that what it leaves
+// out is below 1e-25: those near the low end, which the middle repeats and, where both ends are
+// alike, the high end mirrors.  (Every column near both ends, over 160 nodes, took 2 ms a direction.)
+static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool hi, int* bw_out) {
   const int k = c->k, n1 = n * k + 1, D1D = k + 1, Q1D = 2 * k;
   std::vector<long double> m(D1D * D1D, 0.0L), A((size_t)n1 * D1D, 0.0L);  // A[i][k + j - i], j <= i
   for (int a = 0; a < D1D; ++a)
@@ -57,15 +58,20 @@ static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool h
         if (j - p <= k) s -= A[(size_t)i * D1D + k + p - i] * A[(size_t)j * D1D + k + p - j];
       A[(size_t)i * D1D + k + j - i] = j == i ? std::sqrt(s) : s / A[(size_t)j * D1D + k];
     }
-  const int win = 160;
+  const int win = 100;
   std::vector<double> B((size_t)n1 * (2 * win + 1), 0.0);
   std::vector<long double> y(n1, 0.0L);
-  const int far = win + 64;  // beyond it from both ends the columns repeat with the elements' period k
+  const int far = win;  // beyond it from both ends the columns repeat with the elements' period k
   for (int j = 0; j < n1; ++j) {
     const int i0 = std::max(0, j - win), i1 = std::min(n1 - 1, j + win);
     if (j >= far + k && j < n1 - far) {
       for (int i = i0; i <= i1; ++i)
         B[(size_t)i * (2 * win + 1) + win + j - i] = B[(size_t)(i - k) * (2 * win + 1) + win + j - i];
+      continue;
+    }
+    if (lo == hi && j > n1 - 1 - j) {
+      for (int i = i0; i <= i1; ++i)
+        B[(size_t)i * (2 * win + 1) + win + j - i] = B[(size_t)(n1 - 1 - i) * (2 * win + 1) + win + i - j];
       continue;
     }
     for (int i = j; i <= i1; ++i) {
@@ -79,7 +85,7 @@ static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool h
       y[i] = s / A[(size_t)i * D1D + k];
     }
     const bool held = (lo && j == 0) || (hi && j == n1 - 1);
-    for (int i = i0; i <= i1; ++i) B[(size_t)i * (2 * win + 1) + win + j - i] = held ? 0.0 : (double)(scale * y[i]);
+    for (int i = i0; i <= i1; ++i) B[(size_t)i * (2 * win + 1) + win + j - i] = held ? 0.0 : (double)y[i];
   }
   double top = 0.0;
   for (double v : B) top = std::max(top, std::fabs(v));
@@ -108,11 +114,24 @@ bool tensor_mass_available(const ilh_ctx* c) {
 // 1 / (rho0 |J0|) is folded into direction 0.
 static int tensor_setup(ilh_ctx* c) {
   if (c->tm_ok) return ILH_OK;
+  struct Inv {
+    int n, ends, bw;
+    std::vector<double> w;
+  };
+  std::vector<Inv> invs;  // directions of one extent and the same held ends share theirs
   for (int d = 0; d < c->dim; ++d)
     for (int held = 0; held < 2; ++held) {
-      const bool lo = held && ((c->kp.walls >> (2 * d)) & 1), hi = held && ((c->kp.walls >> (2 * d + 1)) & 1);
-      int bw = 0;
-      const std::vector<double> W = inverse_band(c, c->n[d], lo, hi, d == 0 ? 1.0 / c->rj0_one : 1.0, &bw);
+      const int ends = held ? (c->kp.walls >> (2 * d)) & 3 : 0;
+      const double scale = d == 0 ? 1.0 / c->rj0_one : 1.0;
+      size_t at = 0;
+      while (at < invs.size() && (invs[at].n != c->n[d] || invs[at].ends != ends)) ++at;
+      if (at == invs.size()) {
+        Inv v{c->n[d], ends, 0, {}};
+        v.w = inverse_band(c, c->n[d], (ends & 1) != 0, (ends & 2) != 0, &v.bw);
+        invs.push_back(std::move(v));
+      }
+      const std::vector<double>& W = invs[at].w;
+      const int bw = invs[at].bw;
       const int n1 = c->ng[d], nb = 2 * bw + 1, tiles = (n1 + 15) / 16, nt = (16 + 2 * bw + 3) / 4;
       std::vector<double> P((size_t)tiles * nt * 64, 0.0);
       for (int b = 0; b < tiles; ++b)
@@ -120,7 +139,7 @@ static int tensor_setup(ilh_ctx* c) {
           for (int l = 0; l < 64; ++l) {
             const int i = 16 * b + l % 16, col = 16 * b - bw + 4 * t + l / 16, o = col - i + bw;
             if (i < n1 && col >= 0 && col < n1 && o >= 0 && o < nb)
-              P[((size_t)b * nt + t) * 64 + l] = W[(size_t)i * nb + o];
+              P[((size_t)b * nt + t) * 64 + l] = scale * W[(size_t)i * nb + o];
           }
       double*& dst = c->tm_w[d][held];
       if (!dst) ILH_HIP(c, hipMalloc((void**)&dst, P.size() * sizeof(double)));
