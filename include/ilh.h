@@ -424,7 +424,7 @@ int ilh_set_apply_waves(ilh_ctx* ctx, int waves);
  * it, where the basis vectors fit the registers of one work-group per compute unit (up to 14 basis
  * vectors), else as three launches.  us bounds the time the work-groups wait for one another
  * (default 5,000 microseconds): a step whose work-groups could not all be placed in that time
- * (other work holds the device) is given up on the device without a store, the solver repeats
+ * (other work holds the device) is given up, the launches behind it return at once, the solver repeats
  * the cycle with the three launches and the context keeps to them.  us < 0 takes the three
  * launches from the start; us = 0 gives every such step up (the fallback's test).  The result does
  * not depend on it beyond the order of FP additions.  us above 1e6 or NaN: ILH_EINVAL. */

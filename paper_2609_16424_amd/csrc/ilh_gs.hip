@@ -8,25 +8,24 @@
 // cross the chip once.  Register rows per thread (2 NP) times 512 threads times one work-group per
 // compute unit is the capacity; larger vectors take the three launches.
 //
-// Measured (rocprofv3, us per Arnoldi step; three launches -> one): 11.8 -> 6.3 to 8.9 on 8 x 8 Q2Q1
-// (FP64 basis, 3 work-groups), 19.3 -> 9.7 to 13.5 on the 112 x 48 Q3Q2 triple point (240), 20.6 -> 14 to
-// 19.8 at 128 x 128 Q3Q2 (243; what is left there is the launch, the loads and the 10 MB of stores, the
-// meeting takes 3.5).  Implicit steps: 1.14 -> 0.76, 7.0 -> 5.8 and 0.483 -> 0.453 ms.
+// Measured (rocprofv3, us per Arnoldi step; three launches -> one): 11.8 -> 5.0 to 7.6 on 8 x 8 Q2Q1
+// (FP64 basis, 3 work-groups), 19.3 -> 9.2 on the 112 x 48 Q3Q2 triple point (240 groups).  Implicit
+// steps: 1.09 -> 0.67 and 6.8 -> 5.2 ms; 128 x 128 Q3Q2 (243 groups) 0.480 -> 0.437 ms: there the
+// launch, the loads and the 10 MB of stores remain.
 //
 // The meeting.  Each data work-group stores its partial sums with agent-scope atomic stores (they go
-// past the XCD's L2), waits until they are done, adds one to its arrival word (group b to word b mod
-// GS_WORDS), and waits for every word to reach its count; then every group reads all partial sums
-// (agent-scope loads) and adds them in one fixed order, so that all hold the same bits.  No cache is
-// written back or invalidated: nothing else passes between work-groups inside the launch.  The words
-// lie GS_STRIDE apart, so that neither the additions nor the polling loads of 243 groups queue at one
-// address: with a single word the wait took 4 to 8 us of a 16 us launch.
+// past the XCD's L2) into words that hold GS_EMPTY until then; every group reads the words of all
+// groups (agent-scope loads) until none is empty, and adds them in one fixed order, so that all hold
+// the same bits.  No cache is written back or invalidated and nothing is counted: the data are their own
+// arrival mark.  Arrivals counted in 16 words 256 bytes apart, behind a wait for the stores, took two
+// round trips more (1.8 us of 11.8 a step on the triple point), with a single word 4 to 8 us more.  Steps alternate between two areas;
+// each step empties the words that the next one fills, the cycle's start those of step 0.
 //
 // The wait ends whatever else runs on the device: a work-group that has waited for `limit` ticks of
-// the 100 MHz clock sets the abort bit of a word that is short of its count, by compare-and-swap
-// (which fails if a group has arrived there meanwhile).  A word that is full never takes the bit and
-// one that has it never becomes full, so either every group finds all words full or every group
-// finds a bit.  In the second case each returns without a store, and whoever set the bit marks the
-// cycle as ended and tells the host, which repeats the cycle with the three launches.
+// the 100 MHz clock marks the cycle as ended (every launch behind this one returns at once), tells the
+// host and returns.  Other groups may have seen all sums and stored their rows: the host repeats the
+// cycle, which forms every vector anew, with the three launches.  A residual estimate that the
+// control group published is one of complete sums and holds in either case.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,39 +38,23 @@
 namespace ilh {
 
 static constexpr int GS_T = 512;          // threads of a work-group
-static constexpr int GS_MAXJ = GS_STEPS - 1;      // largest basis count: 2 j + 3 sums fit wave_sums<32>
+static constexpr int GS_MAXJ = 14;        // largest basis count: 2 j + 3 sums fit 32
 static constexpr int GS_MAXB = 256;       // work-groups: the control group and up to 255 data groups
-static constexpr unsigned GS_ABORT = 0x80000000u;
-static constexpr int GS_WORDS = 16, GS_STRIDE = GS_STEP_WORDS / GS_WORDS;  // arrival words of a step
+static constexpr int GS_AREA = 32 * GS_MAXB;      // partial sums of one step
 
-// Wave 0 of a group waits until the words count the arrivals of nbd groups (lane l < GS_WORDS polls
-// word l; `short_of` more arrivals than there are groups are expected in word 0); false when the step
-// was given up, *mine when by this wave.
-__device__ __forceinline__ bool gs_wait(unsigned* words, int nbd, unsigned short_of, uint64_t limit, bool* mine) {
-  const int lane = threadIdx.x & 63;
-  const bool polls = lane < GS_WORDS;
-  const unsigned full = polls ? (unsigned)((nbd + GS_WORDS - 1 - lane) / GS_WORDS) + (lane == 0 ? short_of : 0u) : 0u;
-  unsigned* word = words + (polls ? lane : 0) * GS_STRIDE;
-  const uint64_t t0 = wall_clock64();
-  for (;;) {
-    const unsigned v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__ballot(polls && (v & GS_ABORT) != 0) != 0) return false;
-    const uint64_t open = __ballot(polls && v != full);
-    if (open == 0) return true;
-    if (wall_clock64() - t0 > limit) {
-      bool set = false;
-      if (lane == __ffsll((long long)open) - 1) {
-        unsigned e = v;
-        set = __hip_atomic_compare_exchange_strong(word, &e, v | GS_ABORT, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-      }
-      // (a failed exchange is another arrival or another group's bit: at most one per arrival)
-      if (__ballot(set) != 0) {
-        *mine = true;
-        return false;
-      }
-    }
-  }
+// A partial sum as it is stored (never GS_EMPTY, which is one NaN among many)
+__device__ __forceinline__ unsigned long long gs_bits(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  return u == GS_EMPTY ? 0x7FF8000000000000ull : u;
+}
+
+// The cycle-end flag as the waves of a group read it: a group that gives a step up may set it while
+// another still starts, so a group goes on only if none of its waves saw it.
+__device__ __forceinline__ bool gs_ended(const double* endw) {
+  bool e = false;
+#pragma unroll
+  for (int i = 0; i < GS_T / 64; ++i) e = e || endw[i] != 0.0;
+  return e;
 }
 
 // Work-group 0 is the control group: it holds no rows, waits for the sums and runs the serial part
@@ -84,8 +67,8 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
                                                    TV* __restrict__ z, float* __restrict__ z32,
                                                    TV* __restrict__ zero_v, const double* __restrict__ dv,
                                                    const double* __restrict__ me, int64_t estride,
-                                                   const double* __restrict__ escale, int coupled, double* part,
-                                                   unsigned* words, unsigned short_of, uint64_t limit, double* hest) {
+                                                   const double* __restrict__ escale, int coupled,
+                                                   unsigned long long* part, int never, uint64_t limit, double* hest) {
   constexpr int R = 2 * NP;
   constexpr int NA = 2 * J + 3;
   constexpr int NS = NA <= 16 ? 16 : 32;  // sums, padded
@@ -93,9 +76,13 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
   __shared__ double S[NS];
   __shared__ double sh[NW][NS];
   __shared__ double csl[64], snl[64], coll[65], pl[65], sc[6];
-  __shared__ int ok_s;
+  __shared__ int late_s;
+  __shared__ double endw[NW];
   const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
   const bool control = blockIdx.x == 0;
+  unsigned long long* mine = part + (J & 1) * GS_AREA;         // this step's partial sums
+  unsigned long long* next = part + ((J + 1) & 1) * GS_AREA;  // the next step's
+  if (t == 0) late_s = 0;
   const int b = (int)blockIdx.x - 1;
   const bool h1 = b < nbx;
   TV* uj = V + (int64_t)J * ldv;
@@ -139,7 +126,6 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
       ur[r] = ld32(ub, row[r]);
       wr[r] = ld32(wb, row[r]);
     }
-    if (ended != 0.0) return;  // behind the loads: one round trip for both
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       ur[r] = in[r] ? ur[r] : TV(0);
@@ -149,6 +135,7 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
     // wave 16 at a time (all 31 at once spilled the widest instances)
 #pragma unroll
     for (int q0 = 0; q0 < NA; q0 += 16) {
+      if (ended != 0.0) break;  // behind the loads: one round trip for both
       double acc[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[q] = 0.0;
@@ -176,15 +163,18 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
       for (int s = 0; s < R; ++s)
         dd[s] = (z && escale && in[s]) ? escale[(row[s] - (uint32_t)(2 * nh1)) / (uint32_t)Nl] : 1.0;
     }
+    if (lane == 0) endw[wid] = ended;
     __syncthreads();
+    if (gs_ended(endw)) return;
     if (t < NA) {
       double s = 0.0;
 #pragma unroll
       for (int i = 0; i < NW; ++i) s += sh[i][t];
-      __hip_atomic_store(&part[(int64_t)t * nbd + b], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&mine[t * nbd + b], gs_bits(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    if (J < GS_MAXJ && t >= 64 && t < 64 + NA + 2)
+      __hip_atomic_store(&next[(t - 64) * nbd + b], GS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else {
-    if (ended != 0.0) return;
     // the operands of the serial part, staged while the data groups work
     const double* cs = G + 64 * 64;
     if (t < J - 1) {
@@ -199,51 +189,47 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
       sc[3] = h[255];
       sc[4] = h[HDEV_LGSP + 65];
     }
+    if (lane == 0) endw[wid] = ended;
+    __syncthreads();
+    if (gs_ended(endw)) return;
   }
-  if (wid == 0) {
-    // the wave that stored the partial sums: they are past the L2 before its arrival is counted
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane == 0 && !control)
-      __hip_atomic_fetch_add(words + (b % GS_WORDS) * GS_STRIDE, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    bool mine = false;
-    const bool ok = gs_wait(words, nbd, short_of, limit, &mine);
-    if (lane == 0) {
-      if (mine) {  // this group gave the step up: the cycle ends here, and the host repeats it
-        h[HDEV_LGSE] = -1.0;
-        if (hest) {
-          *reinterpret_cast<double2*>(hest + HEST_ABORT) = make_double2((double)J, h[255]);
-          __threadfence_system();
-        }
-      }
-      ok_s = ok ? 1 : 0;
-    }
-  }
-  __syncthreads();
-  if (!ok_s) return;
   {
-    // all partial sums in one fixed order: 16 lanes per sum, 16 partials per lane (nbd <= 255),
-    // all loads in flight together
+    // 16 lanes per sum, 16 partials per lane (nbd <= 255), all loads of a round in flight together; a
+    // wave asks again for the words that were empty
     const int s = t >> 4, l16 = t & 15;
-    if (s < NA) {
-      const double* p = part + (int64_t)s * nbd;
-      double x[16];
+    const unsigned long long* p = mine + s * nbd;
+    unsigned long long x[16];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int i = l16 + 16 * q;
-        x[q] = 0.0;
-        if (16 * q < nbd)  // uniform
-          x[q] = __hip_atomic_load(&p[i < nbd ? i : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (i >= nbd) x[q] = 0.0;
-      }
-      double a = 0.0;
+    for (int q = 0; q < 16; ++q) x[q] = s < NA && l16 + 16 * q < nbd ? GS_EMPTY : 0ull;
+    const uint64_t t0 = wall_clock64();
+    bool late = false;
+    while (!late) {
+      bool wait = never && s < NA;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) a += x[q];
+      for (int q = 0; q < 16; ++q)
+        if (x[q] == GS_EMPTY) x[q] = __hip_atomic_load(&p[l16 + 16 * q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-      if (l16 == 0) S[s] = a;
+      for (int q = 0; q < 16; ++q) wait = wait || x[q] == GS_EMPTY;
+      if (__ballot(wait) == 0) break;
+      late = wall_clock64() - t0 > limit;
     }
+    if (late && lane == 0) {  // the step is given up: the cycle ends here, and the host repeats it
+      late_s = 1;
+      h[HDEV_LGSE] = -1.0;
+      if (hest) {
+        *reinterpret_cast<double2*>(hest + HEST_ABORT) = make_double2((double)J, h[255]);
+        __threadfence_system();
+      }
+    }
+    double a = 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) a += __longlong_as_double((long long)x[q]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    if (l16 == 0 && s < NA) S[s] = a;
   }
   __syncthreads();
+  if (late_s) return;
   if (control) {
     if (t == 0) {
       lgs_column(S, J, m, 1, csl, snl, coll, pl, sc, h, G, hest, false);
@@ -358,14 +344,12 @@ int lgs_step(ilh_ctx* c, int np, TV* V, int64_t ldv, int j, int m, double* h, do
   const double* me = probe ? c->peinv : c->MEinv;
   const int64_t estride = probe ? (int64_t)c->Nl * c->Nl : c->me_stride;
   const double* escale = probe ? nullptr : c->me_scale;
-  // a zero wait expects one arrival more than there are groups: the step is always given up
-  const unsigned short_of = c->gs_wait_us == 0.0 ? 1u : 0u;
+  const int never = c->gs_wait_us == 0.0 ? 1 : 0;  // a zero wait: the step is always given up
   const uint64_t limit = (uint64_t)(c->gs_wait_us * 100.0);
   auto f = np == 1 ? gs_kernel<TV, 1>(j) : gs_kernel<TV, sizeof(TV) == 4 ? 3 : 2>(j);
   hipLaunchKernelGGL(f, dim3(1 + nbx + nbe), dim3(GS_T), 0, c->stream, V, ldv, m, h, G, c->nh1, c->Ne, c->Nl, nbx,
-                     nbx + nbe, z, z32, zero_v, dv, me, estride, escale, coupled, part,
-                     c->gs_words + (int64_t)j * GS_STEP_WORDS, short_of, limit,
-                     hest);
+                     nbx + nbe, z, z32, zero_v, dv, me, estride, escale, coupled,
+                     reinterpret_cast<unsigned long long*>(part), never, limit, hest);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
@@ -375,5 +359,12 @@ template int lgs_step<float>(ilh_ctx*, int, float*, int64_t, int, int, double*, 
                              int, double*, double*);
 
 int lgs_step_max_j() { return GS_MAXJ; }
+
+// words (from the start of the partial sums) that the cycle's start sets to GS_EMPTY for step 0
+int lgs_step_first(const ilh_ctx* c, int np) {
+  int nbx, nbe;
+  gs_groups(c, np, &nbx, &nbe);
+  return 3 * (nbx + nbe);
+}
 
 }  // namespace ilh

@@ -142,7 +142,6 @@ struct ilh_ctx {
                                 // {h_j+1,j, tag} at [4j, 4j + 4); [256, 258) a pair of norms
   double* hest_dev = nullptr;   // its device (mapped) address
   double est_tag = 0.0;         // tag of the current FGMRES cycle (host counter)
-  unsigned* gs_words = nullptr;  // arrival words of the one-launch Arnoldi steps, zeroed by each cycle's start
   int gs_cus = 0;                // compute units of the device (bounds the work-groups that meet in a launch)
   double gs_wait_us = 5000.0;    // longest wait of those work-groups; < 0: three launches instead; 0: always given up
   double* gmd = nullptr;        // device Givens state of FGMRES: H [64][64], cs, sn [64], g [65]
@@ -370,8 +369,10 @@ int lgs_update(ilh_ctx* c, TV* V, int64_t ldv, int j, const double* h, TV* z, fl
                int coupled, const double* tau_dev, double* hest, const double* end);
 // The same step j (<= lgs_step_max_j()) as one launch, np node pairs per thread (ilh_gs.hip);
 // lgs_step_pairs: the np that fits this context, 0 where the three launches are taken.
-// Arrival words: GS_STEP_WORDS per step, for GS_STEPS steps.
-constexpr int GS_STEP_WORDS = 1024, GS_STEPS = 15;
+// An empty word of the one-launch step's partial sums; lgs_step_first: how many of them the cycle's
+// start empties.
+constexpr unsigned long long GS_EMPTY = ~0ull;
+int lgs_step_first(const ilh_ctx* c, int np);
 int lgs_step_pairs(const ilh_ctx* c, bool f32);
 int lgs_step_max_j();
 template <typename TV>

@@ -351,7 +351,6 @@ void ilh_destroy(ilh_ctx* c) {
   if (c->capstream) (void)hipStreamDestroy(c->capstream);
   if (c->red_host) (void)hipHostFree(c->red_host);
   if (c->hest) (void)hipHostFree(c->hest);
-  if (c->gs_words) (void)hipFree(c->gs_words);
   delete c;
 }
 
@@ -1220,10 +1219,10 @@ static int read_pair(ilh_ctx* c, double* a, double* b) {
 // kernels read
 // (beta2 nullable: beta = sqrt(*beta2), the norm of a restart residual formed on the device; a
 // zero norm gives a zero basis vector, whose cycle then ends at its first column)
-// words: the arrival words of the cycle's one-launch steps, zeroed
+// gsp: the first ngsp partial sums of the cycle's one-launch steps, emptied
 template <typename TV>
 __global__ void k_scale_copy(TV* y, const double* x, double beta_h, int64_t n, double* h, double target,
-                             double tag, double tau, const double* beta2, unsigned* words) {
+                             double tag, double tau, const double* beta2, double* gsp, int ngsp) {
   const double beta = beta2 ? sqrt(*beta2) : beta_h;
   const double f = beta > 0.0 ? 1.0 / beta : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1236,8 +1235,8 @@ __global__ void k_scale_copy(TV* y, const double* x, double beta_h, int64_t n, d
   }
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     y[i] = (TV)(x[i] * f);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < GS_STEPS * GS_STEP_WORDS; i += gridDim.x * blockDim.x)
-    words[i] = 0u;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ngsp; i += gridDim.x * blockDim.x)
+    gsp[i] = __longlong_as_double((long long)GS_EMPTY);
 }
 
 // Exact diagonal blocks of the Jacobian at the current linearisation point, read off by FP32
@@ -1668,7 +1667,7 @@ struct Solver {
       // V0 = r / beta (beta, the target and the cycle's tag to the device), z_0 = P V0
       const double tag = (c->est_tag += 1.0);
       hipLaunchKernelGGL(k_scale_copy<TV>, dim3(1024), dim3(256), 0, c->stream, V, rhs, beta, n, hd, target, tag,
-                         tau, beta2_dev, c->gs_words);
+                         tau, beta2_dev, c->gsp, pairs > 0 ? lgs_step_first(c, pairs) : 0);
       if ((st = precond(V, Z, V + n))) return st;
       const int calls0 = jvp_calls, total0 = total;
       bool given_up = false;  // a one-launch step of this cycle was given up on the device
@@ -1863,12 +1862,11 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
   if (!c->hdev && (st = dalloc(c, &c->hdev, HDEV_LEN))) return st;
   if ((st = ensure_hest(c))) return st;
   if (!c->gmd && (st = dalloc(c, &c->gmd, 64 * 64 + 3 * 65))) return st;
-  if (!c->gs_words) {
+  if (!c->gs_cus) {
     int dev = 0, cus = 0;
     ILH_HIP(c, hipGetDevice(&dev));
     ILH_HIP(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     c->gs_cus = cus;
-    if ((st = dalloc(c, &c->gs_words, GS_STEPS * GS_STEP_WORDS))) return st;
   }
   // The iterate k is only read: every Newton update writes a trial buffer (kA or kB), which then
   // becomes the iterate; the guess and the zero vector serve as iterates without a copy.
