@@ -224,8 +224,10 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
     double a = 0.0;
 #pragma unroll
     for (int q = 0; q < 16; ++q) a += __longlong_as_double((long long)x[q]);
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    a += lane_other<8>(a);
+    a += lane_other<4>(a);
+    a += lane_other<2>(a);
+    a += lane_other<1>(a);
     if (l16 == 0 && s < NA) S[s] = a;
   }
   __syncthreads();
