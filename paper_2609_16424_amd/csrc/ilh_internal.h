@@ -337,6 +337,7 @@ int launch_precond(ilh_ctx* c, const TV* r, TV* z, float* z32, double tau, int c
 // kernels also zero the velocity rows of yz (nullable: the output of the action they feed),
 // after taking from it the previous probe's entries: the velocity diagonal of probe
 // (tcomp, tcol) into tD, column tj of the energy blocks into tB (each nullable)
+int launch_probe2d(ilh_ctx* c, double ax);
 int launch_probe_v_dir(ilh_ctx* c, float* d, int comp, int col, double tau, float* yz = nullptr, int tcomp = -1,
                        int tcol = -1, double* tD = nullptr);
 int launch_probe_e_dir(ilh_ctx* c, float* d, int j, float* yz = nullptr, int tcomp = -1, int tcol = -1,

@@ -1239,14 +1239,26 @@ __global__ void k_scale_copy(TV* y, const double* x, double beta_h, int64_t n, d
     gsp[i] = __longlong_as_double((long long)GS_EMPTY);
 }
 
-// Exact diagonal blocks of the Jacobian at the current linearisation point, read off by FP32
-// Jacobian actions on coloured unit directions: the diagonal of the velocity block (mode 2:
-// directions (0, e, 0)) or of the velocity block with the position block eliminated (mode 1:
-// directions (tau e, e, 0)), and every element's energy block.
+// Exact diagonal blocks of the Jacobian at the current linearisation point: the diagonal of the
+// velocity block (mode 2: directions (0, e, 0)) or of the velocity block with the position block
+// eliminated (mode 1: directions (tau e, e, 0)), and every element's energy block.  Where the 2D strip
+// kernels apply they are formed from the FP32 tangent coefficients in one pass, elsewhere read off by
+// FP32 Jacobian actions on coloured unit directions.
 static int build_probe_prec(ilh_ctx* c, int mode) {
   int st;
   if (!c->pdv && (st = dalloc(c, &c->pdv, (size_t)c->nh1))) return st;
   if (!c->peinv && (st = dalloc(c, &c->peinv, (size_t)c->Ne * c->Nl * c->Nl))) return st;
+  if (c->jvp_variant == 0 && lin2d_available(c)) {
+    if (!c->qd_ok[0]) {
+      const int ls = tstart_k(c, 5);
+      st = launch_lin2d(c, 32);
+      tstop_k(c, ls);
+      if (st) return st;
+      c->qd_ok[0] = true;
+    }
+    if ((st = launch_probe2d(c, mode == 1 ? c->lin_tau : 0.0))) return st;
+    return launch_invert_blocks(c, c->peinv);
+  }
   float* d = c->kry32;
   float* y = c->kry32 + c->nblock;
   const int M = c->k + 1;
