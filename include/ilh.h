@@ -421,8 +421,8 @@ int ilh_set_apply_rows(ilh_ctx* ctx, int rows);
  * result does not depend on it beyond the order of FP additions.  Other values: ILH_EINVAL. */
 int ilh_set_apply_waves(ilh_ctx* ctx, int waves);
 /* The Gram-Schmidt part of an Arnoldi step runs as one launch, whose work-groups meet once inside
- * it, where the basis vectors fit the registers of one work-group per compute unit (up to 14 basis
- * vectors), else as three launches.  us bounds the time the work-groups wait for one another
+ * it, where the basis vectors fit the registers of one work-group per compute unit (up to 16 to 22
+ * basis vectors), else as three launches.  us bounds the time the work-groups wait for one another
  * (default 5,000 microseconds): a step whose work-groups could not all be placed in that time
  * (other work holds the device) is given up, the launches behind it return at once, the solver repeats
  * the cycle with the three launches and the context keeps to them.  us < 0 takes the three

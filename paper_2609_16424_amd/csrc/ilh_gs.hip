@@ -38,9 +38,13 @@
 namespace ilh {
 
 static constexpr int GS_T = 512;          // threads of a work-group
-static constexpr int GS_MAXJ = 14;        // largest basis count: 2 j + 3 sums fit 32
 static constexpr int GS_MAXB = 256;       // work-groups: the control group and up to 255 data groups
-static constexpr int GS_AREA = 32 * GS_MAXB;      // partial sums of one step
+static constexpr int GS_AREA = 64 * GS_MAXB;      // partial sums of one step
+// Largest basis count: the rows of the vectors fit 256 registers (two wavefronts per SIMD)
+template <typename TV, int NP>
+constexpr int gs_max_j() {
+  return NP == 1 ? 22 : sizeof(TV) == 8 ? 16 : 20;
+}
 
 // A partial sum as it is stored (never GS_EMPTY, which is one NaN among many)
 __device__ __forceinline__ unsigned long long gs_bits(double v) {
@@ -61,6 +65,7 @@ __device__ __forceinline__ bool gs_ended(const double* endw) {
 // (lgs_column).  Groups [1, 1 + nbx) hold NP node pairs (i, nh1 + i) per thread, the rest 2 NP sets of
 // GS_T / Nl whole elements.  The update does not wait for the serial part: when column j - 1 ends
 // the cycle, the vectors stored here are ones that the solution over j columns does not read.
+// close: the closing step, which has no w (its sums are zero): it ends with the serial part.
 template <typename TV, int J, int NP>
 __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t ldv, int m, double* h, double* G,
                                                    int64_t nh1, int64_t Ne, int Nl, int nbx, int nbd,
@@ -68,10 +73,11 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
                                                    TV* __restrict__ zero_v, const double* __restrict__ dv,
                                                    const double* __restrict__ me, int64_t estride,
                                                    const double* __restrict__ escale, int coupled,
-                                                   unsigned long long* part, int never, uint64_t limit, double* hest) {
+                                                   unsigned long long* part, int never, uint64_t limit, double* hest,
+                                                   int close) {
   constexpr int R = 2 * NP;
   constexpr int NA = 2 * J + 3;
-  constexpr int NS = NA <= 16 ? 16 : 32;  // sums, padded
+  constexpr int NS = (NA + 15) / 16 * 16;  // sums, padded
   constexpr int NW = GS_T / 64;
   __shared__ double S[NS];
   __shared__ double sh[NW][NS];
@@ -124,7 +130,7 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       ur[r] = ld32(ub, row[r]);
-      wr[r] = ld32(wb, row[r]);
+      wr[r] = close ? TV(0) : ld32(wb, row[r]);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -172,7 +178,7 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
       for (int i = 0; i < NW; ++i) s += sh[i][t];
       __hip_atomic_store(&mine[t * nbd + b], gs_bits(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (J < GS_MAXJ && t >= 64 && t < 64 + NA + 2)
+    if (J < gs_max_j<TV, NP>() && t >= 64 && t < 64 + NA + 2)
       __hip_atomic_store(&next[(t - 64) * nbd + b], GS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else {
     // the operands of the serial part, staged while the data groups work
@@ -193,10 +199,11 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
     __syncthreads();
     if (gs_ended(endw)) return;
   }
-  {
+#pragma unroll
+  for (int s0 = 0; s0 < NA; s0 += GS_T / 16) {
     // 16 lanes per sum, 16 partials per lane (nbd <= 255), all loads of a round in flight together; a
     // wave asks again for the words that were empty
-    const int s = t >> 4, l16 = t & 15;
+    const int s = s0 + (t >> 4), l16 = t & 15;
     const unsigned long long* p = mine + s * nbd;
     unsigned long long x[16];
 #pragma unroll
@@ -234,11 +241,12 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
   if (late_s) return;
   if (control) {
     if (t == 0) {
-      lgs_column(S, J, m, 1, csl, snl, coll, pl, sc, h, G, hest, false);
+      lgs_column(S, J, m, close ? 0 : 1, csl, snl, coll, pl, sc, h, G, hest, false);
       if (J > 0 && hest) publish_estimate(hest, J - 1, h[352 + 2 * (J - 1)], h[353 + 2 * (J - 1)], sc[3]);
     }
     return;
   }
+  if (close) return;
   // the update's coefficients, as lgs_column forms them
   double rinv = 1.0, d = S[2 * J + 1];
   if constexpr (J > 0) {
@@ -311,7 +319,7 @@ static auto gs_table(std::integer_sequence<int, I...>) {
 }
 template <typename TV, int NP>
 static auto gs_kernel(int j) {
-  return gs_table<TV, NP>(std::make_integer_sequence<int, GS_MAXJ + 1>())[j];
+  return gs_table<TV, NP>(std::make_integer_sequence<int, gs_max_j<TV, NP>() + 1>())[j];
 }
 
 // work-groups for NP node pairs per thread
@@ -336,10 +344,16 @@ int lgs_step_pairs(const ilh_ctx* c, bool f32) {
   return 0;
 }
 
+// largest j of the one-launch step with np node pairs per thread
+int lgs_step_max_j(int np, bool f32) {
+  return f32 ? (np == 1 ? gs_max_j<float, 1>() : gs_max_j<float, 3>())
+             : (np == 1 ? gs_max_j<double, 1>() : gs_max_j<double, 2>());
+}
+
 template <typename TV>
 int lgs_step(ilh_ctx* c, int np, TV* V, int64_t ldv, int j, int m, double* h, double* G, TV* z, float* z32,
-             TV* zero_v, int probe, int coupled, double* part, double* hest) {
-  if (j < 0 || j > GS_MAXJ) return fail(c, ILH_EINVAL, "one-launch Arnoldi step: basis count out of range");
+             TV* zero_v, int probe, int coupled, double* part, double* hest, bool close) {
+  if (j < 0 || j > lgs_step_max_j(np, sizeof(TV) == 4)) return fail(c, ILH_EINVAL, "one-launch Arnoldi step: basis count out of range");
   int nbx, nbe;
   gs_groups(c, np, &nbx, &nbe);
   const double* dv = probe ? c->pdv : c->Mdiag;
@@ -351,16 +365,16 @@ int lgs_step(ilh_ctx* c, int np, TV* V, int64_t ldv, int j, int m, double* h, do
   auto f = np == 1 ? gs_kernel<TV, 1>(j) : gs_kernel<TV, sizeof(TV) == 4 ? 3 : 2>(j);
   hipLaunchKernelGGL(f, dim3(1 + nbx + nbe), dim3(GS_T), 0, c->stream, V, ldv, m, h, G, c->nh1, c->Ne, c->Nl, nbx,
                      nbx + nbe, z, z32, zero_v, dv, me, estride, escale, coupled,
-                     reinterpret_cast<unsigned long long*>(part), never, limit, hest);
+                     reinterpret_cast<unsigned long long*>(part), never, limit, hest,
+                     close ? 1 : 0);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
 template int lgs_step<double>(ilh_ctx*, int, double*, int64_t, int, int, double*, double*, double*, float*, double*,
-                              int, int, double*, double*);
+                              int, int, double*, double*, bool);
 template int lgs_step<float>(ilh_ctx*, int, float*, int64_t, int, int, double*, double*, float*, float*, float*, int,
-                             int, double*, double*);
+                             int, double*, double*, bool);
 
-int lgs_step_max_j() { return GS_MAXJ; }
 
 // words (from the start of the partial sums) that the cycle's start sets to GS_EMPTY for step 0
 int lgs_step_first(const ilh_ctx* c, int np) {

@@ -368,17 +368,18 @@ int lgs_final(ilh_ctx* c, const double* part, int np, int j, int m, int has_w, d
 template <typename TV>
 int lgs_update(ilh_ctx* c, TV* V, int64_t ldv, int j, const double* h, TV* z, float* z32, TV* zero_v, int probe,
                int coupled, const double* tau_dev, double* hest, const double* end);
-// The same step j (<= lgs_step_max_j()) as one launch, np node pairs per thread (ilh_gs.hip);
-// lgs_step_pairs: the np that fits this context, 0 where the three launches are taken.
+// The same step j (<= lgs_step_max_j(np, FP32 basis)) as one launch, np node pairs per thread
+// (ilh_gs.hip), the closing step (close) too; lgs_step_pairs: the np that fits this context, 0 where
+// the three launches are taken.
 // An empty word of the one-launch step's partial sums; lgs_step_first: how many of them the cycle's
 // start empties.
 constexpr unsigned long long GS_EMPTY = ~0ull;
 int lgs_step_first(const ilh_ctx* c, int np);
 int lgs_step_pairs(const ilh_ctx* c, bool f32);
-int lgs_step_max_j();
+int lgs_step_max_j(int np, bool f32);
 template <typename TV>
 int lgs_step(ilh_ctx* c, int np, TV* V, int64_t ldv, int j, int m, double* h, double* G, TV* z, float* z32,
-             TV* zero_v, int probe, int coupled, double* part, double* hest);
+             TV* zero_v, int probe, int coupled, double* part, double* hest, bool close);
 // (skip nullable: the kernel returns at once when *skip is nonzero)
 int launch_jvp2d_q_f64(ilh_ctx* c, const double* dk, double* out, const double* tau_dev, const double* skip = nullptr);
 int launch_jvp2d_q_f32to64(ilh_ctx* c, const float* dk, double* out, const double* tau_dev,

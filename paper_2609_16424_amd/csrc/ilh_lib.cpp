@@ -1540,13 +1540,13 @@ struct Solver {
     if (full && (st = apply_basis(Z + (int64_t)j * n, w, skip))) return st;
     const int slot = tstart(c, 3);
     int np = 0;
-    if (full && pairs > 0 && j <= lgs_step_max_j()) {
+    if (pairs > 0 && j <= lgs_step_max_j(pairs, F32)) {
       const bool next = j + 1 < L;  // step j + 1 applies J to z_{j+1}
       TV* zn = next ? Z + (int64_t)(j + 1) * n : nullptr;
       TV* out = (next && direct()) ? V + (int64_t)(j + 2) * n : nullptr;
       float* z32 = (next && o->jvp_prec == 32 && !F32) ? c->kry32 : nullptr;
       if ((st = lgs_step<TV>(c, pairs, V, n, j, m, hd, c->gmd, zn, z32, out, o->prec_probe, o->prec_coupled, c->gsp,
-                             c->hest_dev)))
+                             c->hest_dev, !full)))
         return st;
       z32_of = z32 ? zn : nullptr;
       zeroed_v = out;
