@@ -170,17 +170,18 @@ __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double
 }
 
 // ---- apply: direction dk (T) -> J dk (T) --------------------------------------------------
-// Bound by the coefficient stream (8 bytes x 20 or 29 a point in FP64), which one wavefront per SIMD
-// did not keep full: 70 % of its cycles waited.  FP64 therefore fits two: the position contractions
-// (27 values a lane) wait in LDS where the output columns go later, and the next step's coefficients
-// are asked for when the point's tangent is formed, into the registers it leaves.  FP32 has room for
-// three with the contractions and two steps' coefficients in registers.  57x44x39 Q2Q1 with viscosity
-// in FP64, fill included: 766 us before (one wavefront, field-major rows, one atomic per node and
-// element), 410 us now (1.53 GB of coefficients: 320 us at the rate of a large copy); without
-// viscosity 380 and 317 us.  FP32 with the coefficients copied to LDS directly measured 218 us
-// against 204 us, and is not used.
+// Bound by the coefficient stream (8 or 4 bytes x 20 or 29 a point) once enough wavefronts keep it
+// full, which registers decide.  Two per SIMD in FP64 and four in FP32 fit because the position
+// contractions (27 values a lane) wait in LDS, where FP64's output columns go later, and because the
+// next step's coefficients are asked for when the point's tangent is formed, into the registers it
+// leaves.  57x44x39 Q2Q1 with viscosity, fill included: FP64 766 us before (one wavefront per SIMD,
+// which waited 70 % of its cycles; field-major rows, one atomic per node and element), 410 us now
+// (1.53 GB of coefficients: 320 us at the rate of a large copy); FP32 204 and 178 us (160); without
+// viscosity 380 and 317, 161 and 134 us.  FP32 with the coefficients copied to LDS directly measured
+// 218 us against 204, with two steps' coefficients and the contractions in registers at three
+// wavefronts 183 against 178.
 template <int D1D, int Q1D, typename T, int VISC>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4)))
 k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk, const T* __restrict__ qd,
           double tau_, T* __restrict__ out) {
   constexpr int K = D1D - 1, L1D = K, NLD = L1D * L1D * L1D;
@@ -193,10 +194,9 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
 
   __shared__ T sS[NF][D1D][D1D][NS];
   __shared__ T sE[EPW * NLD];
-  // during the column walk in FP64 the lane's position contractions; after it the output columns
+  // during the column walk the lane's position contractions; after it (FP64) the output columns
   // (lane, node)
-  constexpr bool PLDS = sizeof(T) == 8;
-  constexpr int NPC = 9 * D1D, NU = PLDS && NPC > NOP ? NPC : NOP;
+  constexpr int NPC = 9 * D1D, NU = sizeof(T) == 8 && NOP > NPC ? NOP : NPC;
   __shared__ T sU[64 * NU];
   auto sO = reinterpret_cast<T(*)[NOP]>(sU);
   __shared__ T sBG[2][Q1D][D1D];
@@ -214,27 +214,29 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
   const uint32_t ebase = ((uint32_t)ez * ny + ey) * nx + ex0;
   const uint32_t row0 = (uint32_t)(K * ez) * ng01 + (uint32_t)(K * ey) * ng0 + (uint32_t)(K * ex0);
 
-  constexpr int NTS = NF * D1D * D1D * NS, RT = (NTS + 63) / 64;
+  constexpr int NNE = 3 * D1D * D1D * NS, RG = (NNE + 63) / 64;  // node entries (c, cz, b, s)
   constexpr int NLS = EPW * NLD, RL = (NLS + 63) / 64;
-  T tr[RT], lr[RL];
+  T gx[RG], gv[RG], lr[RL];
   // branch-free gathers: lanes past the strip re-read its last node (their LDS slots feed no
   // output), so every load is in flight before the first LDS store
 #pragma unroll
-  for (int r = 0; r < RT; ++r) {
-    const int i = lane + 64 * r, s = min(i % NS, ns - 1), t = min(i / NS, NF * D1D * D1D - 1), b = t % D1D,
-              cz = (t / D1D) % D1D, f = t / (D1D * D1D);
-    tr[r] = ld32(dk, (f < 3 ? f * N : nh1 + (f - 3) * N) + row0 + (uint32_t)cz * ng01 + (uint32_t)b * ng0 + s);
+  for (int q = 0; q < RG; ++q) {
+    const int i = min(lane + 64 * q, NNE - 1), s = min(i % NS, ns - 1), t = i / NS, b = t % D1D,
+              cz = (t / D1D) % D1D, c = t / (D1D * D1D);
+    const uint32_t gi = c * N + row0 + (uint32_t)cz * ng01 + (uint32_t)b * ng0 + s;
+    gx[q] = ld32(dk, gi);
+    gv[q] = ld32(dk, nh1 + gi);
   }
 #pragma unroll
   for (int r = 0; r < RL; ++r) lr[r] = ld32(dk, 2 * nh1 + ebase * NLD + min(lane + 64 * r, E * NLD - 1));
   const T* __restrict__ qb = sbase(qd + (int64_t)tile * (Q1D * NQD * 64));
   T cf[NQD];
-  auto ldstep = [&](const int qz, T* c) {
+  auto ldstep = [&](const int qz) {
     const T* rb = sbase(qb + qz * (NQD * 64));
 #pragma unroll
-    for (int f = 0; f < NQD; ++f) c[f] = ld32(rb, (uint32_t)(f * 64 + lane));
+    for (int f = 0; f < NQD; ++f) cf[f] = ld32(rb, (uint32_t)(f * 64 + lane));
   };
-  ldstep(0, cf);
+  ldstep(0);
   const int zl = lane / LPE;
   const double rj_l = P.rj0[ebase + (zl < E ? zl : 0)];
   for (int i = lane; i < Q1D * D1D; i += 64) {
@@ -242,10 +244,22 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
     sBG[1][i / D1D][i % D1D] = tb.G[i / D1D][i % D1D];
   }
   for (int i = lane; i < Q1D * L1D; i += 64) sBL[i / L1D][i % L1D] = tb.BL[i / L1D][i % L1D];
+  const T tau = T(tau_);
+  const bool last_x = (ex0 + E == nx), last_y = (ey == ny - 1), last_z = (ez == P.n[2] - 1);
 #pragma unroll
-  for (int r = 0; r < RT; ++r) {
-    const int i = lane + 64 * r;
-    if (i < NTS) (&sS[0][0][0][0])[i] = tr[r];
+  for (int q = 0; q < RG; ++q) {
+    const int i = lane + 64 * q;
+    if (i >= NNE) continue;
+    const int s = i % NS, t = i / NS, b = t % D1D, cz = (t / D1D) % D1D, c = t / (D1D * D1D);
+    sS[c][cz][b][s] = gx[q];
+    sS[3 + c][cz][b][s] = gv[q];
+    // position rows (dk_x - tau dk_v) and constrained velocity rows (dk_v): the node's single owner
+    if (s >= ns || !((s < K * E || last_x) && (b < K || last_y) && (cz < K || last_z))) continue;
+    const uint32_t gi = c * N + row0 + (uint32_t)cz * ng01 + (uint32_t)b * ng0 + s;
+    st32(out, gi, gx[q] - tau * gv[q]);
+    const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
+    const uint32_t idx = c == 0 ? I : (c == 1 ? J : Kz), ngc = c == 0 ? ng0 : (c == 1 ? ng1 : ng2);
+    if (idx == 0 || idx == ngc - 1) st32(out, nh1 + gi, gv[q]);
   }
 #pragma unroll
   for (int r = 0; r < RL; ++r) {
@@ -279,8 +293,7 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
   for (int cl = 0; cl < L1D; ++cl) TL[cl] = T(0);
   {  // lanes past the strip walk along: their columns feed no output
     const int s0 = K * z;
-    constexpr int F0 = PLDS ? 3 : 0;  // first field whose contractions stay in registers
-    T BB[NF][D1D], GB[NF][D1D], BG[NF][D1D];
+    T BB[NF][D1D], GB[NF][D1D], BG[NF][D1D];  // (the velocity fields')
     T* const pc = sU + lane * NPC;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -300,7 +313,7 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
           gb += By[b] * ag;
           bg += Gy[b] * ab;
         }
-        if (f < F0) {
+        if (f < 3) {
           pc[(f * D1D + cz) * 3] = gb;
           pc[(f * D1D + cz) * 3 + 1] = bg;
           pc[(f * D1D + cz) * 3 + 2] = bb;
@@ -331,9 +344,9 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
 #pragma unroll
         for (int c = 0; c < D1D; ++c) {
           const T Bz = tb.B[qz][c], Gz = tb.G[qz][c];
-          j0 += Bz * (PLDS ? pc[(r * D1D + c) * 3] : GB[r][c]);
-          j1 += Bz * (PLDS ? pc[(r * D1D + c) * 3 + 1] : BG[r][c]);
-          j2 += Gz * (PLDS ? pc[(r * D1D + c) * 3 + 2] : BB[r][c]);
+          j0 += Bz * pc[(r * D1D + c) * 3];
+          j1 += Bz * pc[(r * D1D + c) * 3 + 1];
+          j2 += Gz * pc[(r * D1D + c) * 3 + 2];
           g0 += Bz * GB[3 + r][c];
           g1 += Bz * BG[3 + r][c];
           g2 += Gz * BB[3 + r][c];
@@ -353,16 +366,14 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
       const T mq = wxy * tb.W[qz];
       T dS[3][3], ds;
       lin_apply<3, T, VISC>(cf, dJ, dGv, dke, dS, ds);
-      if constexpr (PLDS) {
-        // the point's results are formed before the next coefficients are asked for: both sets in
-        // registers at once would not fit at two wavefronts per SIMD
-        asm volatile(""
-                     : "+v"(dS[0][0]), "+v"(dS[0][1]), "+v"(dS[0][2]), "+v"(dS[1][0]), "+v"(dS[1][1]),
-                       "+v"(dS[1][2]), "+v"(dS[2][0]), "+v"(dS[2][1]), "+v"(dS[2][2]), "+v"(ds)
-                     :
-                     : "memory");
-        if (qz + 1 < Q1D) ldstep(qz + 1, cf);
-      }
+      // the point's results are formed before the next coefficients are asked for: both sets in
+      // registers at once would not fit
+      asm volatile(""
+                   : "+v"(dS[0][0]), "+v"(dS[0][1]), "+v"(dS[0][2]), "+v"(dS[1][0]), "+v"(dS[1][1]),
+                     "+v"(dS[1][2]), "+v"(dS[2][0]), "+v"(dS[2][1]), "+v"(dS[2][2]), "+v"(ds)
+                   :
+                   : "memory");
+      if (qz + 1 < Q1D) ldstep(qz + 1);
       const T cl_ = mq * dke - ds;
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
@@ -380,16 +391,8 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
     };
 #pragma unroll 1
     for (int qz = 0; qz < Q1D; ++qz) {
-      if constexpr (PLDS) {
-        asm volatile("" ::: "memory");  // the contractions in LDS are read again each step
-        step(qz);
-      } else {
-        T cn[NQD];
-        ldstep(qz + 1 < Q1D ? qz + 1 : qz, cn);
-        step(qz);
-#pragma unroll
-        for (int f = 0; f < NQD; ++f) cf[f] = cn[f];
-      }
+      asm volatile("" ::: "memory");  // the contractions in LDS are read again each step
+      step(qz);
     }
   }
   // the lane's indices once more, from a value the compiler does not connect with the first: what the
@@ -397,6 +400,71 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
   int ln = threadIdx.x;
   asm volatile("" : "+v"(ln));
   const int pz = ln / LPE, pr = ln - pz * LPE, py = pr / Q1D, px = pr - py * Q1D;
+  if constexpr (sizeof(T) == 4) {
+    // FP32: an element's columns are the 16 lanes of a row, so its sums over (q_x, q_y) are quad and row
+    // adds of the vector unit; lane (a, b) of the element ends with the sums of node (a, b).  The
+    // node column shared with the next element of the strip goes to that element's lanes; one atomic
+    // per node and strip (constrained rows were written by their owner above).  Through LDS these
+    // sums and their indices were a third of the kernel's vector instructions (32^3: 50 us an action, 41 without).
+    static_assert(sizeof(T) == 8 || (D1D == 3 && Q1D == 4), "one row of 16 lanes per element");
+#pragma unroll
+    for (int a = 0; a < D1D; ++a) {  // reloaded: not kept live through the column loop
+      Bx[a] = sBG[0][px][a];
+      Gx[a] = sBG[1][px][a];
+      By[a] = sBG[0][py][a];
+      Gy[a] = sBG[1][py][a];
+    }
+    const uint32_t I = K * (ex0 + pz) + px, J = K * ey + py;
+    const bool cI = I == 0 || I == ng0 - 1, cJ = J == 0 || J == ng1 - 1;
+    const bool node = px < D1D && py < D1D && pz < E && !(px == K && pz + 1 < E), takes = px == 0 && pz > 0;
+    const uint32_t off = row0 + (uint32_t)(K * pz + px) + (uint32_t)py * ng0;
+    const int from = 4 * (ln - (LPE - K));
+    // (formed in every lane, then selected: not sunk into branches on the lane)
+    auto pick = [](int i, T v0, T v1, T v2) {
+      asm volatile("" : "+v"(v0), "+v"(v1), "+v"(v2));
+      const T t = i == 1 ? v1 : v2;
+      return i == 0 ? v0 : t;
+    };
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      T v[D1D], left[D1D];
+#pragma unroll
+      for (int cz = 0; cz < D1D; ++cz) {
+        T q1[D1D], q2[D1D], o[D1D];
+#pragma unroll
+        for (int a = 0; a < D1D; ++a) {
+          q1[a] = quad_sum(Gx[a] * Tx[r][cz] + Bx[a] * Tz[r][cz]);
+          q2[a] = quad_sum(Bx[a] * Ty[r][cz]);
+        }
+        const T s1 = pick(px, q1[0], q1[1], q1[2]), s2 = pick(px, q2[0], q2[1], q2[2]);
+#pragma unroll
+        for (int b = 0; b < D1D; ++b) o[b] = quads_sum(By[b] * s1 + Gy[b] * s2);
+        v[cz] = pick(py, o[0], o[1], o[2]);
+      }
+#pragma unroll
+      for (int cz = 0; cz < D1D; ++cz)
+        left[cz] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v[cz])));
+#pragma unroll
+      for (int cz = 0; cz < D1D; ++cz) {
+        const T o = takes ? v[cz] + left[cz] : v[cz];
+        const uint32_t Kz = K * ez + cz;
+        const bool cons = r == 0 ? cI : (r == 1 ? cJ : Kz == 0 || Kz == ng2 - 1);
+        if (node && !cons) atomic_add32(out, nh1 + r * N + cz * ng01 + off, o);
+      }
+    }
+    // energy rows (element-owned): lane (al + 2 cl, bl) takes entry (al, bl, cl)
+    const int al = px & 1, cl = px >> 1;
+    T w[2][2], o[2];
+#pragma unroll
+    for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+      for (int a2 = 0; a2 < 2; ++a2) w[c2][a2] = quad_sum(sBL[px][a2] * TL[c2]);
+    const T w1 = pick(px, w[0][0], w[0][1], w[1][0]);
+    const T wl = px == 3 ? w[1][1] : w1;
+#pragma unroll
+    for (int b2 = 0; b2 < 2; ++b2) o[b2] = quads_sum(sBL[py][b2] * wl);
+    if (py < 2 && pz < E) st32(out, 2 * nh1 + (ebase + pz) * NLD + al + 2 * (py + 2 * cl), py == 0 ? o[0] : o[1]);
+  } else {
   // velocity rows, one component at a time: each lane's column contributions to its element's
   // nodes (factored: out(a,b) = By_b (Gx_a Tx + Bx_a Tz) + Gy_b Bx_a Ty per z-layer) go to LDS;
   // one thread per node of the strip sums the columns of the (one or two) elements holding it
@@ -464,18 +532,6 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
       out[2 * nh1 + (ebase + pz) * NLD + t] = o;
     }
   }
-  // position rows (dk_x - tau dk_v) and constrained velocity rows (dk_v), by node owner
-  const T tau = T(tau_);
-  const bool last_x = (ex0 + E == nx), last_y = (ey == ny - 1), last_z = (ez == P.n[2] - 1);
-  for (int i = ln; i < 3 * D1D * D1D * NS; i += 64) {
-    const int s = i % NS, t = i / NS, b = t % D1D, cz = (t / D1D) % D1D, c = t / (D1D * D1D);
-    if (s >= ns || !((s < K * E || last_x) && (b < K || last_y) && (cz < K || last_z))) continue;
-    const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
-    const uint32_t gi = c * N + row0 + (uint32_t)cz * ng01 + (uint32_t)b * ng0 + s;
-    const T dkv = sS[3 + c][cz][b][s];
-    out[gi] = sS[c][cz][b][s] - tau * dkv;
-    const uint32_t idx = c == 0 ? I : (c == 1 ? J : Kz), ngc = c == 0 ? ng0 : (c == 1 ? ng1 : ng2);
-    if (idx == 0 || idx == ngc - 1) out[nh1 + gi] = dkv;  // the owner is the only writer
   }
 }
 

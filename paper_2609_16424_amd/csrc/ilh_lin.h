@@ -349,6 +349,21 @@ __device__ __forceinline__ void lds_barrier() {
 // and atomics issued after it.
 __device__ __forceinline__ void vm_drained() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// v of the lane that the data-parallel-primitive control C names (an add of it is one instruction)
+template <int C>
+__device__ __forceinline__ float dpp_of(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C, 0xF, 0xF, true));
+}
+// sums over the four lanes of a quad, and over the four quads of a row of 16 lanes, in every lane
+__device__ __forceinline__ float quad_sum(float v) {
+  v += dpp_of<0xB1>(v);  // quad_perm [1,0,3,2]
+  return v + dpp_of<0x4E>(v);  // quad_perm [2,3,0,1]
+}
+__device__ __forceinline__ float quads_sum(float v) {
+  v += dpp_of<0x124>(v);  // row_ror:4
+  return v + dpp_of<0x128>(v);  // row_ror:8
+}
+
 // Work-group -> tile map for a chip of 8 XCDs, each with its own L2: work-groups are handed to
 // the XCDs in turn (w mod 8), so neighbouring tiles would sit on different L2s and the cache
 // lines they share (node rows at strip ends, the direction's overlapping strips) would be
