@@ -46,12 +46,6 @@ constexpr int gs_max_j() {
   return NP == 1 ? 22 : sizeof(TV) == 8 ? 16 : 20;
 }
 
-// A partial sum as it is stored (never GS_EMPTY, which is one NaN among many)
-__device__ __forceinline__ unsigned long long gs_bits(double v) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  return u == GS_EMPTY ? 0x7FF8000000000000ull : u;
-}
-
 // The cycle-end flag as the waves of a group read it: a group that gives a step up may set it while
 // another still starts, so a group goes on only if none of its waves saw it.
 __device__ __forceinline__ bool gs_ended(const double* endw) {

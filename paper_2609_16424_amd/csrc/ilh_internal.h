@@ -160,7 +160,7 @@ struct ilh_ctx {
   int tused = 0;
   int64_t tgen = 0;  // flushes so far (a pending slot index is valid within one generation)
   hipEvent_t xev0 = nullptr, xev1 = nullptr;  // open single-kernel slot, taken by the next klaunch
-  hipEvent_t pev = nullptr;  // end of the Newton solve's first norm pair (read while later work runs)
+  unsigned long long* nwords = nullptr;  // partial sums of launch_norms (first use; empty between launches)
   double tms[ILH_TIMING_CLASSES] = {};
   int64_t tcnt[ILH_TIMING_CLASSES] = {};
   std::string err;
@@ -261,13 +261,9 @@ int launch_jacobi(ilh_ctx* c, const double* r, double* z);   // z = r / Mdiag
 int dot_host(ilh_ctx* c, const double* x, const double* y, int64_t n, double* out);
 // device-side dot into d_out (no sync)
 int dot_dev(ilh_ctx* c, const double* x, const double* y, int64_t n, double* d_out);
-// the block partial sums of x . y into part (*np of them)
-int dot_part(ilh_ctx* c, const double* x, const double* y, int64_t n, double* part, int* np);
-// x . y into part and x2 . y2 into part2 (np partials each) by one launch
-int dot_part2(ilh_ctx* c, const double* x, const double* y, const double* x2, const double* y2, int64_t n,
-              double* part, double* part2, int* np);
-// out[0], out[1] = sum (mode 0) or minimum (mode 1) of each partial set, one launch
-int launch_pair_final(ilh_ctx* c, const double* pa, int na, int ma, const double* pb, int nb, int mb, double* out);
+// (ilh_ops.hip) the records {value, tag} of |x|^2 and |x2|^2, or of the minimum of mins and |x|^2
+int launch_norms(ilh_ctx* c, const double* x, const double* x2, int64_t n, const double* mins, int nm, double* rec,
+                 double tag);
 // out = k1 or 2 k1 - k2 (nhist 1 or 2), position block u_v + tau out_v when tau > 0
 int launch_extrap(ilh_ctx* c, double* out, const double* u, const double* k1, const double* k2, int nhist,
                   double tau);
@@ -290,6 +286,8 @@ constexpr int HDEV_RBETA2 = 771;
 constexpr int HDEV_LEN = 776;
 // hest[HEST_ABORT, +2): {step, tag} of a cycle whose one-launch step was given up
 constexpr int HEST_ABORT = 260;
+// hest[HEST_PAIR, +4): the two records {value, tag} of launch_norms
+constexpr int HEST_PAIR = 256;
 // y = H(0:n, 0:n)^-1 g
 int launch_trisolve(ilh_ctx* c, const double* G, int m, int n, double* y);
 // x += Z y with y = H(0:jn, 0:jn)^-1 g, one launch (accumulate = false: x = Z y, x need not be

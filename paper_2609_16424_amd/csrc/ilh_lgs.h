@@ -82,6 +82,12 @@ __device__ __forceinline__ int wave_sums(double (&acc)[K]) {
   return v;
 }
 
+// A partial sum as it is stored (never GS_EMPTY, which is one NaN among many)
+__device__ __forceinline__ unsigned long long gs_bits(double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  return u == GS_EMPTY ? 0x7FF8000000000000ull : u;
+}
+
 // The residual estimate and h_{j+1,j} of column j to host memory (mapped, coherent) as two 16-byte
 // records {estimate, tag} and {h_{j+1,j}, tag}: each record is one store, so the host never pairs
 // a new tag with an old value whatever order the two stores become visible in

@@ -345,7 +345,7 @@ void ilh_destroy(ilh_ctx* c) {
       if (p) (void)hipFree(p);
   if (c->tm_tmp) (void)hipFree(c->tm_tmp);
   for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
-  if (c->pev) (void)hipEventDestroy(c->pev);
+  if (c->nwords) (void)hipFree(c->nwords);
   for (hipGraphExec_t e : c->gexec)
     if (e) (void)hipGraphExecDestroy(e);
   if (c->capstream) (void)hipStreamDestroy(c->capstream);
@@ -1692,6 +1692,7 @@ struct Solver {
         // dry without it (every enqueued kernel done) is an error, so the wait always ends
         const volatile double* est = c->hest;
         const auto t0 = std::chrono::steady_clock::now();
+        auto asked = t0;
         auto arrived = [&]() { return est[4 * jj + 1] == tag && est[4 * jj + 3] == tag; };
         for (unsigned spins = 1; !arrived(); ++spins) {
           __builtin_ia32_pause();
@@ -1700,6 +1701,9 @@ struct Solver {
             return ILH_OK;
           }
           if ((spins & 1023) == 0) {
+            const auto now = std::chrono::steady_clock::now();
+            if (now - asked < std::chrono::milliseconds(1)) continue;
+            asked = now;  // (a query costs the stream a marker: not within an ordinary wait)
             const hipError_t q = hipStreamQuery(c->stream);
             if (q != hipSuccess && q != hipErrorNotReady) ILH_HIP(c, q);
             if (q == hipSuccess && !arrived()) {
@@ -1845,6 +1849,35 @@ struct Solver {
   }
 };
 
+// The two values of launch_norms with this tag, read from mapped host memory: the wait ends when the tags
+// arrive, when the stream runs dry without them, or after two minutes
+static int read_norms(ilh_ctx* c, double tag, double* a, double* b) {
+  const volatile double* rec = c->hest + HEST_PAIR;
+  auto arrived = [&]() { return rec[1] == tag && rec[3] == tag; };
+  const auto t0 = std::chrono::steady_clock::now();
+  auto asked = t0;
+  for (unsigned spins = 1; !arrived(); ++spins) {
+    __builtin_ia32_pause();
+    if ((spins & 1023) != 0) continue;
+    const auto now = std::chrono::steady_clock::now();
+    if (now - asked < std::chrono::milliseconds(1)) continue;
+    asked = now;  // (a query costs the stream a marker: not within an ordinary wait)
+    const hipError_t q = hipStreamQuery(c->stream);
+    if (q != hipSuccess && q != hipErrorNotReady) ILH_HIP(c, q);
+    if (q == hipSuccess) {
+      // (host-mapped stores can trail the completion the stream reports)
+      while (!arrived() && std::chrono::steady_clock::now() - now < std::chrono::milliseconds(10))
+        __builtin_ia32_pause();
+      if (!arrived()) return fail(c, ILH_EHIP, "a finished reduction left no residual norms");
+    }
+    if (now - t0 > std::chrono::seconds(120)) return fail(c, ILH_EHIP, "timed out waiting for residual norms");
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  *a = rec[0];
+  *b = rec[2];
+  return ILH_OK;
+}
+
 // The linearisation at k (state u + tau k) with its tangent coefficients formed at once for the
 // action precision prec (the linearised variant; else the state copies only)
 static int linearize_now(ilh_ctx* c, const double* k, const double* u, double tau, int prec) {
@@ -1892,51 +1925,38 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
   double* rt = c->nwt + 7 * n;
   Solver<TV> S{c, o, tau};
   double* dsc = dev_pair(c);
-  double* pa = c->red;                   // partial sums of the first norm of a pair
-  double* pb = c->red + c->red_blocks;   // and of the second
-  double* hp = c->hest_dev + 256;        // the pair, in mapped host memory
-  auto read_hp = [&](double* a, double* b) -> int {
-    ILH_HIP(c, hipStreamSynchronize(c->stream));
-    *a = c->hest[256];
-    *b = c->hest[257];
-    return ILH_OK;
+  double tag = 0.0;  // of the norms asked for last
+  auto norms = [&](const double* x, const double* x2, const double* mins, int nm) {
+    return launch_norms(c, x, x2, n, mins, nm, c->hest_dev + HEST_PAIR, tag = (c->est_tag += 1.0));
   };
-  // The first pair (|R(0)|, |R(guess)|) is read while the stream already runs the linearisation
-  // at the first iterate, which is then taken in the common case (the iterate kept and not yet
-  // within the tolerance): an event marks the end of the pair's reduction, the linearisation
-  // is enqueued behind it, and the host waits for the event only.  A rejected guess or a met
-  // tolerance discards that linearisation (the next one overwrites it).
+  // Norms are read while the stream already runs the linearisation at the iterate that the next Newton
+  // step takes in the common case (kspec: the first iterate, or a trial that a full step leaves); a
+  // rejected iterate or a met tolerance discards that linearisation (the next one overwrites it).
   const double* k_lin = nullptr;  // the iterate the stream has been linearised at
-  auto read_first = [&](const double* kspec, double* a, double* b) -> int {
+  auto read_ahead = [&](const double* kspec, double* a, double* b) -> int {
     int s1;
-    if (o->max_newton < 1) return read_hp(a, b);
-    if (!c->pev) ILH_HIP(c, hipEventCreateWithFlags(&c->pev, hipEventDisableTiming));
-    ILH_HIP(c, hipEventRecord(c->pev, c->stream));
-    if ((s1 = linearize_now(c, kspec, u, tau, o->jvp_prec))) return s1;
-    k_lin = kspec;
-    ILH_HIP(c, hipEventSynchronize(c->pev));
-    *a = c->hest[256];
-    *b = c->hest[257];
-    return ILH_OK;
+    k_lin = nullptr;
+    if (kspec) {
+      if ((s1 = linearize_now(c, kspec, u, tau, o->jvp_prec))) return s1;
+      k_lin = kspec;
+    }
+    return read_norms(c, tag, a, b);
   };
   if (!c->zero_ok) {
     if ((st = launch_fill(c, zero, 0.0, n))) return st;
     c->zero_ok = true;  // nothing else writes this part of the workspace
   }
-  int npa = 0, npb = 0;
   // the velocity rows of both residual buffers zeroed by one launch
   if ((st = k_guess ? launch_fill2(c, rt + c->nh1, r + c->nh1, 0.0, c->nh1) : launch_fill(c, rt + c->nh1, 0.0, c->nh1)))
     return st;
   // R(0) in rt, and R(k_guess) in r (one launch for the two where the 2D strip kernel applies)
   if ((st = k_guess ? residual_pair(c, zero, rt, k_guess, r, u, tau) : residual_into(c, zero, u, tau, rt, false)))
     return st;
-  if ((st = k_guess ? dot_part2(c, rt, rt, r, r, n, pa, pb, &npa) : dot_part(c, rt, rt, n, pa, &npa))) return st;
-  npb = npa;
+  if ((st = norms(rt, k_guess ? r : nullptr, nullptr, 0))) return st;
   double r0 = 0.0, nr = 0.0;
   if (k_guess) {
     // |R(0)| and |R(k_guess)| read together
-    if ((st = launch_pair_final(c, pa, npa, 0, pb, npb, 0, hp))) return st;
-    if ((st = read_first(k_guess, &r0, &nr))) return st;
+    if ((st = read_ahead(o->max_newton < 1 ? nullptr : k_guess, &r0, &nr))) return st;
     r0 = std::sqrt(r0);
     nr = std::sqrt(nr);
     stats.res0 = r0;
@@ -1951,8 +1971,7 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
     }
   } else {
     double unused;
-    if ((st = launch_pair_final(c, pa, npa, 0, pa, npa, 0, hp))) return st;
-    if ((st = read_first(zero, &r0, &unused))) return st;
+    if ((st = read_ahead(o->max_newton < 1 ? nullptr : zero, &r0, &unused))) return st;
     r0 = std::sqrt(r0);
     nr = r0;
     stats.res0 = r0;
@@ -1976,7 +1995,11 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
       c->err = "Newton reached max_newton";
       break;
     }
-    if (!(it == 0 && k == k_lin) && (st = ilh_linearize(c, k, u, tau))) return st;
+    if (k != k_lin && (st = ilh_linearize(c, k, u, tau))) return st;
+    k_lin = nullptr;
+    // the solve leaves about gmres_rtol of the residual: where that is not yet within the tolerance, the
+    // next Newton step's linearisation is enqueued before the trial's norm is read
+    const bool goes_on = it + 1 < o->max_newton && o->gmres_rtol * nr > o->tol * r0;
     if (o->prec_probe && (it == 0 || !o->prec_lag) && (st = build_probe_prec(c, o->prec_probe))) return st;
     // the Newton direction is -x with J x = R(k): the solve takes r as its right-hand side and
     // the trials step by -alpha x
@@ -1997,9 +2020,8 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
         if ((st = launch_waxpy(c, kt, k, -alpha, dk, n, rt + c->nh1, c->nh1))) return st;
         int ng = 0;
         if ((st = residual_detj_part(c, kt, u, tau, rt, &ng))) return st;
-        if ((st = dot_part(c, rt, rt, n, pb, &npb))) return st;
-        if ((st = launch_pair_final(c, c->dmin_part, ng, 1, pb, npb, 0, hp))) return st;
-        if ((st = read_hp(&md, &nrt2))) return st;
+        if ((st = norms(rt, nullptr, c->dmin_part, ng))) return st;
+        if ((st = read_ahead(goes_on && h == 0 ? kt : nullptr, &md, &nrt2))) return st;
       } else {
         if ((st = launch_waxpy(c, kt, k, -alpha, dk, n))) return st;
         if ((st = launch_waxpy(c, trial, u, tau, kt, c->nh1))) return st;
@@ -2293,12 +2315,12 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
     return st;
   // judge: residual norms of the learned and the plain iterate, formed and read together
   if ((st = residual_pair(c, k, rl, base, rb, u, tau))) return st;
-  int np = 0;
-  double* hp = c->hest_dev + 256;
-  if ((st = dot_part2(c, rl, rl, rb, rb, c->nblock, c->red, c->red + c->red_blocks, &np))) return st;
-  if ((st = launch_pair_final(c, c->red, np, 0, c->red + c->red_blocks, np, 0, hp))) return st;
-  ILH_HIP(c, hipStreamSynchronize(c->stream));
-  const double nl = std::sqrt(c->hest[256]), nb = std::sqrt(c->hest[257]);
+  const double tag = (c->est_tag += 1.0);
+  double nl, nb;
+  if ((st = launch_norms(c, rl, rb, c->nblock, nullptr, 0, c->hest_dev + HEST_PAIR, tag))) return st;
+  if ((st = read_norms(c, tag, &nl, &nb))) return st;
+  nl = std::sqrt(nl);
+  nb = std::sqrt(nb);
   const bool use = std::isfinite(nl) && (nl < nb || !std::isfinite(nb));
   if (!use) {
     ILH_HIP(c, hipMemcpyAsync(k, base, c->nblock * sizeof(double), hipMemcpyDeviceToDevice, c->stream));

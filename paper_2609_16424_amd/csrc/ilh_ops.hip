@@ -184,13 +184,7 @@ __device__ __forceinline__ double block_min(double v) {
 }
 
 // partial sums of x . y, one per block; grid.y = 2: the blocks of row 1 take x2 . y2 into part2
-__global__ void __launch_bounds__(TPB) k_dot_part(const double* x, const double* y, int64_t n, double* part,
-                                                  const double* x2, const double* y2, double* part2) {
-  if (blockIdx.y != 0) {
-    x = x2;
-    y = y2;
-    part = part2;
-  }
+__global__ void __launch_bounds__(TPB) k_dot_part(const double* x, const double* y, int64_t n, double* part) {
   double acc = 0;
   for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) acc += x[i] * y[i];
   acc = block_sum<TPB>(acc);
@@ -216,47 +210,71 @@ static int red_blocks(ilh_ctx* c, int64_t n) {
 
 int dot_dev(ilh_ctx* c, const double* x, const double* y, int64_t n, double* d_out) {
   const int nb = red_blocks(c, n);
-  hipLaunchKernelGGL(k_dot_part, dim3(nb), dim3(TPB), 0, c->stream, x, y, n, c->red, x, y, c->red);
+  hipLaunchKernelGGL(k_dot_part, dim3(nb), dim3(TPB), 0, c->stream, x, y, n, c->red);
   hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(TPB), 0, c->stream, c->red, nb, d_out, 0);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
 
-int dot_part(ilh_ctx* c, const double* x, const double* y, int64_t n, double* part, int* np) {
-  const int nb = red_blocks(c, n);
-  hipLaunchKernelGGL(k_dot_part, dim3(nb), dim3(TPB), 0, c->stream, x, y, n, part, x, y, part);
-  ILH_HIP(c, hipGetLastError());
-  *np = nb;
-  return ILH_OK;
-}
-int dot_part2(ilh_ctx* c, const double* x, const double* y, const double* x2, const double* y2, int64_t n,
-              double* part, double* part2, int* np) {
-  const int nb = red_blocks(c, n);
-  hipLaunchKernelGGL(k_dot_part, dim3(nb, 2), dim3(TPB), 0, c->stream, x, y, n, part, x2, y2, part2);
-  ILH_HIP(c, hipGetLastError());
-  *np = nb;
-  return ILH_OK;
-}
-
-// Two reductions of partial sums finished in one launch: out[0] = the sum (ma = 0) or the
-// minimum (ma = 1) of pa[0..na), out[1] likewise of pb; out may be host-mapped memory, read once
-// the stream has synchronised
-__global__ void __launch_bounds__(TPB) k_pair_final(const double* pa, int na, int ma, const double* pb, int nb,
-                                                    int mb, double* out) {
-  double a = ma ? 1e300 : 0.0, b = mb ? 1e300 : 0.0;
-  for (int i = threadIdx.x; i < na; i += TPB) a = ma ? nan_min(a, pa[i]) : a + pa[i];
-  for (int i = threadIdx.x; i < nb; i += TPB) b = mb ? nan_min(b, pb[i]) : b + pb[i];
-  a = ma ? block_min<TPB>(a) : block_sum<TPB>(a);
-  b = mb ? block_min<TPB>(b) : block_sum<TPB>(b);
+// |x|^2 and, where x2 is set, |x2|^2, or the minimum of mins[0 .. nm) and |x|^2, as two records
+// {value, tag} in mapped host memory: rec[0 .. 2) the first or the minimum, rec[2 .. 4) the second (or the
+// first again).  nb work-groups a vector leave their partial sums in `words` (agent-scope stores; GS_EMPTY
+// before), the last work-group reads them until none is empty, empties them again and adds them in one
+// order; it is dispatched after the others, so it never keeps them from running.  One launch and no
+// synchronisation: the host reads the tag.  (Partial sums, a final launch and a stream
+// synchronisation took some 10 us more of every Newton iteration.)
+__global__ void __launch_bounds__(TPB) k_norms(const double* x, const double* x2, int64_t n, int nb,
+                                               unsigned long long* words, const double* mins, int nm, double* rec,
+                                               double tag) {
+  const int ns = x2 ? 2 * nb : nb, b = blockIdx.x;
+  if (b < ns) {
+    const bool second = b >= nb;
+    const double* v = second ? x2 : x;
+    double acc = 0;
+    for (int64_t i = (int64_t)(second ? b - nb : b) * TPB + threadIdx.x; i < n; i += (int64_t)nb * TPB)
+      acc += v[i] * v[i];
+    acc = block_sum<TPB>(acc);
+    if (threadIdx.x == 0)
+      __hip_atomic_store(&words[b], gs_bits(acc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
+  double m = 1e300, s[2] = {0.0, 0.0};
+  for (int i = threadIdx.x; i < nm; i += TPB) m = nan_min(m, mins[i]);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {  // nb <= TPB: one word a thread and sum
+    if ((int)threadIdx.x >= nb || q * nb >= ns) continue;
+    unsigned long long* w = &words[q * nb + threadIdx.x];
+    unsigned long long u;
+    do u = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    while (u == GS_EMPTY);
+    __hip_atomic_store(w, GS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s[q] = __longlong_as_double((long long)u);
+  }
+  if (nm > 0) m = block_min<TPB>(m);
+  s[0] = block_sum<TPB>(s[0]);
+  if (x2) s[1] = block_sum<TPB>(s[1]);
   if (threadIdx.x == 0) {
-    out[0] = a;
-    out[1] = b;
+    double2* r = reinterpret_cast<double2*>(rec);
+    r[0] = make_double2(nm > 0 ? m : s[0], tag);
+    r[1] = make_double2(x2 ? s[1] : s[0], tag);
     __threadfence_system();
   }
 }
 
-int launch_pair_final(ilh_ctx* c, const double* pa, int na, int ma, const double* pb, int nb, int mb, double* out) {
-  hipLaunchKernelGGL(k_pair_final, dim3(1), dim3(TPB), 0, c->stream, pa, na, ma, pb, nb, mb, out);
+__global__ void k_empty(unsigned long long* w, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) w[i] = GS_EMPTY;
+}
+
+int launch_norms(ilh_ctx* c, const double* x, const double* x2, int64_t n, const double* mins, int nm, double* rec,
+                 double tag) {
+  const int nb = (int)std::min<int64_t>(TPB, std::max<int64_t>(1, (n + 4 * TPB - 1) / (4 * TPB)));
+  if (!c->nwords) {
+    ILH_HIP(c, hipMalloc((void**)&c->nwords, 2 * TPB * sizeof(unsigned long long)));
+    hipLaunchKernelGGL(k_empty, dim3(2), dim3(TPB), 0, c->stream, c->nwords, 2 * TPB);
+  }
+  hipLaunchKernelGGL(k_norms, dim3((x2 ? 2 : 1) * nb + 1), dim3(TPB), 0, c->stream, x, x2, n, nb, c->nwords, mins, nm,
+                     rec, tag);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
