@@ -281,8 +281,6 @@ constexpr int HDEV_FLAG = 640;
 // step)
 constexpr int HDEV_LGSP = 704;
 constexpr int HDEV_LGSE = 770;
-// 771: |r|^2 of a restart residual, formed on the device and read by the next cycle's scaling
-constexpr int HDEV_RBETA2 = 771;
 constexpr int HDEV_LEN = 776;
 // hest[HEST_ABORT, +2): {step, tag} of a cycle whose one-launch step was given up
 constexpr int HEST_ABORT = 260;
@@ -294,7 +292,16 @@ int launch_trisolve(ilh_ctx* c, const double* G, int m, int n, double* y);
 // initialised; with jn = 0 it is zeroed)
 template <typename TV>
 int launch_trisolve_maxpy(ilh_ctx* c, double* x, const TV* Z, int64_t ldz, const double* G, int jn, int64_t n,
-                          bool accumulate = true);
+                          bool accumulate, float* x32 = nullptr, double* zero = nullptr, int64_t nz = 0);
+// (ilh_ops.hip) the start of an FGMRES cycle; the residual of a restart
+struct CycleStart {
+  double target, tag, tau;
+};
+int launch_restart_residual(ilh_ctx* c, double* r, const double* b, int64_t n, double* part, int* np);
+template <typename TV>
+int launch_cycle_start(ilh_ctx* c, TV* V, const double* r, double beta, const double* part, int np, double* h,
+                       const CycleStart& cs, double* gsp, int ngsp, int probe, int coupled, TV* z, float* z32,
+                       TV* zero_v);
 // Norm reduction and Givens update of Arnoldi step j: the partial sums of |w|^2 (part, np blocks),
 // the Arnoldi scalars h, the rotations G (layout at givens_update), and the mapped host buffer of
 // residual estimates (hest, nullable).  Runs as its own one-block kernel, or as the extra last

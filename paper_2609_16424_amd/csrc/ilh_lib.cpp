@@ -1212,33 +1212,6 @@ static int read_pair(ilh_ctx* c, double* a, double* b) {
   return ILH_OK;
 }
 
-// y = x / beta; beta is also stored to *beta_out, the scale of the stored vector y, 1, to *s0
-// and the FGMRES cycle's tag to *tag_out
-// y = x / beta with the cycle's Arnoldi scalars: h[240] = beta, h[252] = the residual target,
-// h[255] = the cycle's tag, s_0 = h[256] = 1, and the stage factor h[250] = tau that the step
-// kernels read
-// (beta2 nullable: beta = sqrt(*beta2), the norm of a restart residual formed on the device; a
-// zero norm gives a zero basis vector, whose cycle then ends at its first column)
-// gsp: the first ngsp partial sums of the cycle's one-launch steps, emptied
-template <typename TV>
-__global__ void k_scale_copy(TV* y, const double* x, double beta_h, int64_t n, double* h, double target,
-                             double tag, double tau, const double* beta2, double* gsp, int ngsp) {
-  const double beta = beta2 ? sqrt(*beta2) : beta_h;
-  const double f = beta > 0.0 ? 1.0 / beta : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    h[250] = tau;
-    h[240] = beta;
-    h[252] = target;
-    h[255] = tag;
-    h[256] = 1.0;
-    h[HDEV_LGSE] = 0.0;
-  }
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    y[i] = (TV)(x[i] * f);
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ngsp; i += gridDim.x * blockDim.x)
-    gsp[i] = __longlong_as_double((long long)GS_EMPTY);
-}
-
 // Exact diagonal blocks of the Jacobian at the current linearisation point: the diagonal of the
 // velocity block (mode 2: directions (0, e, 0)) or of the velocity block with the position block
 // eliminated (mode 1: directions (tau e, e, 0)), and every element's energy block.  Where the 2D strip
@@ -1318,6 +1291,29 @@ struct Solver {
     return st;
   }
 
+  // v_0 = r / beta (beta, the target, tau and the cycle's tag to the device) and z_0 = P v_0
+  int cycle_start(TV* V, TV* Z, const double* r, double beta, const double* part, int np, const CycleStart& cs) {
+    int st;
+    const int64_t n = c->nblock;
+    const int slot = tstart(c, 4);
+    z32_of = nullptr;
+    zeroed_v = nullptr;
+    float* z32 = (o->jvp_prec == 32 && !F32) ? c->kry32 : nullptr;
+    TV* zv = direct() ? V + n + c->nh1 : nullptr;
+    const bool own = o->prec_probe || o->pcg_iters <= 0;  // the preconditioner is applied here
+    if (!own) z32 = nullptr, zv = nullptr;
+    if ((st = launch_cycle_start<TV>(c, V, r, beta, part, np, c->hdev, cs, c->gsp,
+                                     pairs > 0 ? lgs_step_first(c, pairs) : 0, o->prec_probe, o->prec_coupled, Z, z32,
+                                     zv)))
+      return st;
+    if (z32) z32_of = Z;
+    if (zv) zeroed_v = V + n;
+    if (!own) st = precond_body(V, Z, V + n, nullptr, nullptr);  // (PCG velocity block: over z_0)
+    tstop(c, slot);
+    return st;
+  }
+
+  const double* prepared = nullptr;  // an action's output whose velocity rows are zero, its input's FP32 copy in kry32
   const TV* z32_of = nullptr;  // FP64 basis: the vector whose FP32 copy is in kry32 (written by precond)
   const TV* zeroed_v = nullptr;  // the basis vector whose velocity rows precond zeroed
   int pairs = 0;  // node pairs per thread of the one-launch Arnoldi step (0: three launches)
@@ -1414,6 +1410,8 @@ struct Solver {
     int st;
     ++jvp_calls;
     skippable = false;
+    const bool ready = prepared == y;
+    prepared = nullptr;
     if (o->jvp_prec == 32) {
       float* x32 = c->kry32;
       float* y32 = c->kry32 + c->nblock;
@@ -1440,10 +1438,10 @@ struct Solver {
         return st;
       }
       if (direct64()) {
-        // (restart residuals) the FP32 copy of x and the zero velocity rows of y in one launch,
-        // then the action writes the FP64 y itself at the host's tau
-        if (!have32 && (st = launch_cast_d2f(c, x32, x, c->nblock, y + c->nh1, c->nh1))) return st;
-        if (have32 && (st = launch_fill(c, y + c->nh1, 0.0, c->nh1))) return st;
+        // (restart residuals) the action writes the FP64 y itself at the host's tau, from the FP32 copy of x
+        // onto zero velocity rows: both there already, or one launch
+        if (!ready && !have32 && (st = launch_cast_d2f(c, x32, x, c->nblock, y + c->nh1, c->nh1))) return st;
+        if (!ready && have32 && (st = launch_fill(c, y + c->nh1, 0.0, c->nh1))) return st;
         if (!c->qd_ok[0]) {
           const int ls = tstart_k(c, 5);
           st = launch_lin2d(c, 32);
@@ -1461,7 +1459,7 @@ struct Solver {
       return launch_cast_f2d(c, y, y32, c->nblock);
     }
     if constexpr (!F32) {
-      const bool zeroed = (const void*)y == (const void*)zeroed_v;
+      const bool zeroed = ready || (const void*)y == (const void*)zeroed_v;
       zeroed_v = nullptr;
       if (zeroed && direct()) {  // the velocity rows of y are zero already: no fill ahead of the action
         if (!c->qd_ok[1]) {
@@ -1665,7 +1663,8 @@ struct Solver {
     *its = 0;
     if (beta == 0.0) return launch_fill(c, x, 0.0, n);
     const double target = o->gmres_rtol * beta;
-    const double* beta2_dev = nullptr;  // set once a restart forms the residual norm on the device
+    const double* beta2_part = nullptr;  // partial sums of a restart's squared residual norm, once there is one
+    int nbeta2 = 0;
     const double* rhs = b;
     double* rbuf = c->nwt + 3 * n;  // tmp vector
     int total = 0;
@@ -1678,9 +1677,7 @@ struct Solver {
     while (true) {
       // V0 = r / beta (beta, the target and the cycle's tag to the device), z_0 = P V0
       const double tag = (c->est_tag += 1.0);
-      hipLaunchKernelGGL(k_scale_copy<TV>, dim3(1024), dim3(256), 0, c->stream, V, rhs, beta, n, hd, target, tag,
-                         tau, beta2_dev, c->gsp, pairs > 0 ? lgs_step_first(c, pairs) : 0);
-      if ((st = precond(V, Z, V + n))) return st;
+      if ((st = cycle_start(V, Z, rhs, beta, beta2_part, nbeta2, CycleStart{target, tag, tau}))) return st;
       const int calls0 = jvp_calls, total0 = total;
       bool given_up = false;  // a one-launch step of this cycle was given up on the device
       int j_end = 0;
@@ -1830,19 +1827,25 @@ struct Solver {
         if ((st = check(m - 1, end))) return st;
         j_end = m;
       }
-      // y = H^-1 g (upper triangular), x += Z y (x = Z y in the first cycle)
-      if ((st = launch_trisolve_maxpy<TV>(c, x, Z, n, G, j_end, n, x_set))) return st;
+      // y = H^-1 g (upper triangular), x += Z y (x = Z y in the first cycle), and what the action of a
+      // restart reads and adds to: the FP32 copy of x, the zero velocity rows of its output
+      const bool again = !stop && total < o->gmres_maxit;
+      const bool prepare = again && j_end > 0 && direct();
+      if ((st = launch_trisolve_maxpy<TV>(c, x, Z, n, G, j_end, n, x_set, prepare && direct64() ? c->kry32 : nullptr,
+                                          prepare ? rbuf + c->nh1 : nullptr, c->nh1)))
+        return st;
       x_set = true;
-      if (stop) break;
-      // restart: r = b - J x, its |r|^2 left on the device for the next cycle's scaling kernel
+      if (!again) break;
+      // restart: r = b - J x, its |r|^2 left on the device as partial sums for the next cycle's start
       // (no synchronisation; a restart residual that already meets the target, which the
       // cycle's own estimates make rare, ends the next cycle at its first column)
-      if (total >= o->gmres_maxit) break;
+      z32_of = nullptr;
+      zeroed_v = nullptr;
+      prepared = prepare ? rbuf : nullptr;
       if ((st = apply(x, rbuf))) return st;
-      if ((st = launch_axpby(c, rbuf, 1.0, b, -1.0, n))) return st;
+      if ((st = launch_restart_residual(c, rbuf, b, n, c->red, &nbeta2))) return st;
       rhs = rbuf;
-      if ((st = dot_dev(c, rbuf, rbuf, n, hd + HDEV_RBETA2))) return st;
-      beta2_dev = hd + HDEV_RBETA2;
+      beta2_part = c->red;
     }
     *its = total;
     return ILH_OK;

@@ -717,7 +717,8 @@ __global__ void k_trisolve(const double* G, int n, double* y) {
 template <typename TV>
 __global__ void __launch_bounds__(TPB) k_trisolve_maxpy(double* __restrict__ x, const TV* __restrict__ Z,
                                                         int64_t ldz, const double* __restrict__ G, int jn, int64_t n,
-                                                        int accumulate) {
+                                                        int accumulate, float* __restrict__ x32,
+                                                        double* __restrict__ zero, int64_t nz) {
   extern __shared__ double tsh[];  // H (jn x jn, row-major), then y (jn)
   double* Hs = tsh;
   double* ys = tsh + jn * jn;
@@ -738,25 +739,28 @@ __global__ void __launch_bounds__(TPB) k_trisolve_maxpy(double* __restrict__ x, 
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     double acc = 0;
     for (int j = 0; j < jn; ++j) acc += ys[j] * (double)Z[(int64_t)j * ldz + i];
-    x[i] = accumulate ? x[i] + acc : acc;
+    const double v = accumulate ? x[i] + acc : acc;
+    x[i] = v;
+    if (x32) x32[i] = (float)v;
+    if (i < nz) zero[i] = 0.0;
   }
 }
 
 template <typename TV>
 int launch_trisolve_maxpy(ilh_ctx* c, double* x, const TV* Z, int64_t ldz, const double* G, int jn, int64_t n,
-                          bool accumulate) {
+                          bool accumulate, float* x32, double* zero, int64_t nz) {
   if (jn <= 0) return accumulate ? ILH_OK : launch_fill(c, x, 0.0, n);
   if (jn > 64) return fail(c, ILH_EINVAL, "triangular solve: at most 64 columns");
   const size_t shm = (size_t)(jn * jn + jn) * sizeof(double);
   hipLaunchKernelGGL(k_trisolve_maxpy<TV>, dim3(std::min(nblk(n), 1024)), dim3(TPB), shm, c->stream, x, Z, ldz, G, jn,
-                     n, accumulate ? 1 : 0);
+                     n, accumulate ? 1 : 0, x32, zero, zero ? nz : 0);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }
 template int launch_trisolve_maxpy<double>(ilh_ctx*, double*, const double*, int64_t, const double*, int, int64_t,
-                                          bool);
+                                          bool, float*, double*, int64_t);
 template int launch_trisolve_maxpy<float>(ilh_ctx*, double*, const float*, int64_t, const double*, int, int64_t,
-                                         bool);
+                                         bool, float*, double*, int64_t);
 
 int launch_trisolve(ilh_ctx* c, const double* G, int m, int n, double* y) {
   (void)m;
@@ -1659,6 +1663,102 @@ template int launch_precond_probe<double>(ilh_ctx*, const double*, double*, floa
                                           const double*, const double*, const GivensJob*);
 template int launch_precond_probe<float>(ilh_ctx*, const float*, float*, float*, double, int, float*,
                                          const double*, const double*, const GivensJob*);
+
+// ------------------------------------------------------------------ start of an FGMRES cycle
+// r = b - r and the partial sums of |r|^2 (r holds J x on entry)
+__global__ void __launch_bounds__(TPB) k_restart_residual(double* r, const double* b, int64_t n, double* part) {
+  double acc = 0;
+  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
+    const double v = b[i] - r[i];
+    r[i] = v;
+    acc += v * v;
+  }
+  acc = block_sum<TPB>(acc);
+  if (threadIdx.x == 0) part[blockIdx.x] = acc;
+}
+
+int launch_restart_residual(ilh_ctx* c, double* r, const double* b, int64_t n, double* part, int* np) {
+  *np = (int)std::min<int64_t>(TPB, std::max<int64_t>(1, (n + 4 * TPB - 1) / (4 * TPB)));
+  hipLaunchKernelGGL(k_restart_residual, dim3(*np), dim3(TPB), 0, c->stream, r, b, n, part);
+  ILH_HIP(c, hipGetLastError());
+  return ILH_OK;
+}
+
+// v_0 = r / beta and z_0 = P v_0 (the block preconditioner of k_precond and k_precond_probe, its operands
+// passed) with the cycle's scalars (CycleStart) in one launch.  beta is the host's, or the root of
+// the sum of np partial sums, which every work-group adds for itself.  A restart took eight launches
+// from the solution update to here, each a few microseconds: four now.
+template <typename TV>
+__global__ void __launch_bounds__(TPB) k_cycle_start(TV* __restrict__ V, const double* __restrict__ r, double beta_h,
+                                                     const double* part, int np, double* h, const CycleStart cs,
+                                                     double* gsp, int ngsp, const double* __restrict__ dv,
+                                                     const double* __restrict__ Me, int64_t estride,
+                                                     const double* __restrict__ escale, int coupled,
+                                                     TV* __restrict__ z, float* z32, TV* zero_v, int64_t nh1,
+                                                     int64_t Ne, int Nl) {
+  __shared__ double beta_s;
+  double beta = beta_h;
+  if (np > 0) {
+    double acc = (int)threadIdx.x < np ? part[threadIdx.x] : 0.0;  // np <= TPB
+    acc = block_sum<TPB>(acc);
+    if (threadIdx.x == 0) beta_s = sqrt(acc);
+    __syncthreads();
+    beta = beta_s;
+  }
+  const double f = beta > 0.0 ? 1.0 / beta : 0.0;  // a zero norm: a cycle that ends at its first column
+  const int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x;
+  if (i == 0) {
+    h[250] = cs.tau;
+    h[240] = beta;
+    h[252] = cs.target;
+    h[255] = cs.tag;
+    h[256] = 1.0;
+    h[HDEV_LGSE] = 0.0;
+  }
+  if (i < ngsp) gsp[i] = __longlong_as_double((long long)GS_EMPTY);
+  if (zero_v && i < nh1) zero_v[i] = TV(0);  // velocity rows of the first Jacobian action's output
+  if (i < nh1) {
+    const TV vx = (TV)(r[i] * f), vv = (TV)(r[nh1 + i] * f);
+    V[i] = vx;
+    V[nh1 + i] = vv;
+    const double zv = (double)vv / dv[i];
+    const double zx = coupled ? cs.tau * zv + (double)vx : (double)vx;
+    z[i] = (TV)zx;
+    z[nh1 + i] = (TV)zv;
+    if (z32) {
+      z32[i] = (float)zx;
+      z32[nh1 + i] = (float)zv;
+    }
+  } else if (i < nh1 + Ne * Nl) {
+    const int64_t k = i - nh1, e = k / Nl;
+    const int rr = (int)(k % Nl);
+    V[2 * nh1 + k] = (TV)(r[2 * nh1 + k] * f);
+    const double* M = Me + e * estride + rr * Nl;
+    double acc = 0;
+    for (int j = 0; j < Nl; ++j) acc += M[j] * (double)(TV)(r[2 * nh1 + e * Nl + j] * f);
+    if (escale) acc *= escale[e];
+    z[2 * nh1 + k] = (TV)acc;
+    if (z32) z32[2 * nh1 + k] = (float)acc;
+  }
+}
+
+template <typename TV>
+int launch_cycle_start(ilh_ctx* c, TV* V, const double* r, double beta, const double* part, int np, double* h,
+                       const CycleStart& cs, double* gsp, int ngsp, int probe, int coupled, TV* z, float* z32,
+                       TV* zero_v) {
+  const int64_t n = c->nh1 + c->Ne * c->Nl;
+  if (np > TPB || ngsp > n) return fail(c, ILH_EINVAL, "cycle start: more partial sums than it reads or empties");
+  hipLaunchKernelGGL(k_cycle_start<TV>, dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, c->stream, V, r, beta,
+                     part, np, h, cs, gsp, ngsp, probe ? c->pdv : c->Mdiag, probe ? c->peinv : c->MEinv,
+                     probe ? (int64_t)c->Nl * c->Nl : c->me_stride, probe ? nullptr : c->me_scale, coupled, z, z32,
+                     zero_v, c->nh1, c->Ne, c->Nl);
+  ILH_HIP(c, hipGetLastError());
+  return ILH_OK;
+}
+template int launch_cycle_start<double>(ilh_ctx*, double*, const double*, double, const double*, int, double*,
+                                        const CycleStart&, double*, int, int, int, double*, float*, double*);
+template int launch_cycle_start<float>(ilh_ctx*, float*, const double*, double, const double*, int, double*,
+                                       const CycleStart&, double*, int, int, int, float*, float*, float*);
 
 // ------------------------------------------------------------------ mass operators
 // y += M_V x (values-only partial assembly).  bc != 0: constrained inputs read as zero and
