@@ -172,14 +172,14 @@ __global__ void __launch_bounds__(64) k_lin3d(const KParams P, const Tab2<double
 // ---- apply: direction dk (T) -> J dk (T) --------------------------------------------------
 // Bound by the coefficient stream (8 or 4 bytes x 20 or 29 a point) once enough wavefronts keep it
 // full, which registers decide.  Two per SIMD in FP64 and four in FP32 fit because the position
-// contractions (27 values a lane) wait in LDS, where FP64's output columns go later, and because the
+// contractions (27 values a lane) wait in LDS, and because the
 // next step's coefficients are asked for when the point's tangent is formed, into the registers it
-// leaves.  57x44x39 Q2Q1 with viscosity, fill included: FP64 766 us before (one wavefront per SIMD,
-// which waited 70 % of its cycles; field-major rows, one atomic per node and element), 410 us now
-// (1.53 GB of coefficients: 320 us at the rate of a large copy); FP32 204 and 178 us (160); without
-// viscosity 380 and 317, 161 and 134 us.  FP32 with the coefficients copied to LDS directly measured
-// 218 us against 204, with two steps' coefficients and the contractions in registers at three
-// wavefronts 183 against 178.
+// leaves.  57x44x39 Q2Q1 with viscosity, fill included: FP64 766 us with one wavefront per SIMD, which
+// waited 70 % of its cycles, field-major rows and one atomic per node and element, 410 us with two,
+// 373 us with the node sums in the vector unit (1.53 GB of coefficients: 320 us at the rate of a large
+// copy); FP32 204 and 178 us (160); without viscosity 380 and 277, 161 and 134 us.  FP32 with the
+// coefficients copied to LDS directly measured 218 us against 204, with two steps' coefficients and
+// the contractions in registers at three wavefronts 183 against 178.
 template <int D1D, int Q1D, typename T, int VISC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 2 : 4)))
 k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk, const T* __restrict__ qd,
@@ -189,16 +189,11 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
   constexpr int NS = K * EPW + 1;
   constexpr int NQD = LinLayout<3, VISC, 0>::NQD;
   constexpr int NF = 6;                      // dkx0 dkx1 dkx2 dkv0 dkv1 dkv2
-  constexpr int NND = D1D * D1D * D1D;       // H1 nodes per element
-  constexpr int NOP = (NND > NLD ? NND : NLD) | 1;  // odd LDS row length (bank spread)
 
   __shared__ T sS[NF][D1D][D1D][NS];
   __shared__ T sE[EPW * NLD];
-  // during the column walk the lane's position contractions; after it (FP64) the output columns
-  // (lane, node)
-  constexpr int NPC = 9 * D1D, NU = sizeof(T) == 8 && NOP > NPC ? NOP : NPC;
-  __shared__ T sU[64 * NU];
-  auto sO = reinterpret_cast<T(*)[NOP]>(sU);
+  constexpr int NPC = 9 * D1D;
+  __shared__ T sU[64 * NPC];  // (lane, position contraction)
   __shared__ T sBG[2][Q1D][D1D];
   __shared__ T sBL[Q1D][L1D];
 
@@ -400,75 +395,9 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
   int ln = threadIdx.x;
   asm volatile("" : "+v"(ln));
   const int pz = ln / LPE, pr = ln - pz * LPE, py = pr / Q1D, px = pr - py * Q1D;
-  if constexpr (sizeof(T) == 4) {
-    // FP32: an element's columns are the 16 lanes of a row, so its sums over (q_x, q_y) are quad and row
-    // adds of the vector unit; lane (a, b) of the element ends with the sums of node (a, b).  The
-    // node column shared with the next element of the strip goes to that element's lanes; one atomic
-    // per node and strip (constrained rows were written by their owner above).  Through LDS these
-    // sums and their indices were a third of the kernel's vector instructions (32^3: 50 us an action, 41 without).
-    static_assert(sizeof(T) == 8 || (D1D == 3 && Q1D == 4), "one row of 16 lanes per element");
-#pragma unroll
-    for (int a = 0; a < D1D; ++a) {  // reloaded: not kept live through the column loop
-      Bx[a] = sBG[0][px][a];
-      Gx[a] = sBG[1][px][a];
-      By[a] = sBG[0][py][a];
-      Gy[a] = sBG[1][py][a];
-    }
-    const uint32_t I = K * (ex0 + pz) + px, J = K * ey + py;
-    const bool cI = I == 0 || I == ng0 - 1, cJ = J == 0 || J == ng1 - 1;
-    const bool node = px < D1D && py < D1D && pz < E && !(px == K && pz + 1 < E), takes = px == 0 && pz > 0;
-    const uint32_t off = row0 + (uint32_t)(K * pz + px) + (uint32_t)py * ng0;
-    const int from = 4 * (ln - (LPE - K));
-    // (formed in every lane, then selected: not sunk into branches on the lane)
-    auto pick = [](int i, T v0, T v1, T v2) {
-      asm volatile("" : "+v"(v0), "+v"(v1), "+v"(v2));
-      const T t = i == 1 ? v1 : v2;
-      return i == 0 ? v0 : t;
-    };
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      T v[D1D], left[D1D];
-#pragma unroll
-      for (int cz = 0; cz < D1D; ++cz) {
-        T q1[D1D], q2[D1D], o[D1D];
-#pragma unroll
-        for (int a = 0; a < D1D; ++a) {
-          q1[a] = quad_sum(Gx[a] * Tx[r][cz] + Bx[a] * Tz[r][cz]);
-          q2[a] = quad_sum(Bx[a] * Ty[r][cz]);
-        }
-        const T s1 = pick(px, q1[0], q1[1], q1[2]), s2 = pick(px, q2[0], q2[1], q2[2]);
-#pragma unroll
-        for (int b = 0; b < D1D; ++b) o[b] = quads_sum(By[b] * s1 + Gy[b] * s2);
-        v[cz] = pick(py, o[0], o[1], o[2]);
-      }
-#pragma unroll
-      for (int cz = 0; cz < D1D; ++cz)
-        left[cz] = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v[cz])));
-#pragma unroll
-      for (int cz = 0; cz < D1D; ++cz) {
-        const T o = takes ? v[cz] + left[cz] : v[cz];
-        const uint32_t Kz = K * ez + cz;
-        const bool cons = r == 0 ? cI : (r == 1 ? cJ : Kz == 0 || Kz == ng2 - 1);
-        if (node && !cons) atomic_add32(out, nh1 + r * N + cz * ng01 + off, o);
-      }
-    }
-    // energy rows (element-owned): lane (al + 2 cl, bl) takes entry (al, bl, cl)
-    const int al = px & 1, cl = px >> 1;
-    T w[2][2], o[2];
-#pragma unroll
-    for (int c2 = 0; c2 < 2; ++c2)
-#pragma unroll
-      for (int a2 = 0; a2 < 2; ++a2) w[c2][a2] = quad_sum(sBL[px][a2] * TL[c2]);
-    const T w1 = pick(px, w[0][0], w[0][1], w[1][0]);
-    const T wl = px == 3 ? w[1][1] : w1;
-#pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2) o[b2] = quads_sum(sBL[py][b2] * wl);
-    if (py < 2 && pz < E) st32(out, 2 * nh1 + (ebase + pz) * NLD + al + 2 * (py + 2 * cl), py == 0 ? o[0] : o[1]);
-  } else {
-  // velocity rows, one component at a time: each lane's column contributions to its element's
-  // nodes (factored: out(a,b) = By_b (Gx_a Tx + Bx_a Tz) + Gy_b Bx_a Ty per z-layer) go to LDS;
-  // one thread per node of the strip sums the columns of the (one or two) elements holding it
-  // and issues one atomic add (constrained rows are set by the owner below)
+  // velocity rows: node sums (node_sums3), one atomic per node and strip (constrained rows were written
+  // by their owner above)
+  static_assert(D1D == 3 && Q1D == 4, "one row of 16 lanes per element");
 #pragma unroll
   for (int a = 0; a < D1D; ++a) {  // reloaded: not kept live through the column loop
     Bx[a] = sBG[0][px][a];
@@ -476,63 +405,24 @@ k_jvp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ dk,
     By[a] = sBG[0][py][a];
     Gy[a] = sBG[1][py][a];
   }
-#pragma unroll 1
+  const uint32_t I = K * (ex0 + pz) + px, J = K * ey + py;
+  const bool cI = I == 0 || I == ng0 - 1, cJ = J == 0 || J == ng1 - 1;
+  const bool node = px < D1D && py < D1D && pz < E && !(px == K && pz + 1 < E);
+  const uint32_t off = row0 + (uint32_t)(K * pz + px) + (uint32_t)py * ng0;
+#pragma unroll
   for (int r = 0; r < 3; ++r) {
+    T v[D1D];
+    node_sums3<T>(Tx[r], Ty[r], Tz[r], Bx, Gx, By, Gy, px, py, 4 * (ln - (LPE - K)), px == 0 && pz > 0, v);
 #pragma unroll
     for (int cz = 0; cz < D1D; ++cz) {
-      T tx = 0, ty = 0, tz = 0;
-#pragma unroll
-      for (int rq = 0; rq < 3; ++rq)
-        if (rq == r) {
-          tx = Tx[rq][cz];
-          ty = Ty[rq][cz];
-          tz = Tz[rq][cz];
-        }
-#pragma unroll
-      for (int a = 0; a < D1D; ++a) {
-        const T q1 = Gx[a] * tx + Bx[a] * tz, q2 = Bx[a] * ty;
-#pragma unroll
-        for (int b = 0; b < D1D; ++b) sO[ln][(cz * D1D + b) * D1D + a] = By[b] * q1 + Gy[b] * q2;
-      }
+      const uint32_t Kz = K * ez + cz;
+      const bool cons = r == 0 ? cI : (r == 1 ? cJ : Kz == 0 || Kz == ng2 - 1);
+      if (node && !cons) atomic_add32(out, nh1 + r * N + cz * ng01 + off, v[cz]);
     }
-    lds_barrier();
-    for (int i = ln; i < D1D * D1D * NS; i += 64) {
-      const int s = i % NS, t = i / NS, b = t % D1D, cz = t / D1D;
-      if (s >= ns) continue;
-      const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
-      const uint32_t idx = r == 0 ? I : (r == 1 ? J : Kz), ngr = r == 0 ? ng0 : (r == 1 ? ng1 : ng2);
-      if (idx == 0 || idx == ngr - 1) continue;
-      const int zz = s / K, a = s - K * zz;
-      T o = 0;
-      if (zz < E) {
-#pragma unroll
-        for (int q = 0; q < LPE; ++q) o += sO[zz * LPE + q][(cz * D1D + b) * D1D + a];
-      }
-      if (a == 0 && zz > 0) {
-#pragma unroll
-        for (int q = 0; q < LPE; ++q) o += sO[(zz - 1) * LPE + q][(cz * D1D + b) * D1D + K];
-      }
-      unsafeAtomicAdd(&out[nh1 + r * N + row0 + cz * ng01 + b * ng0 + s], o);
-    }
-    lds_barrier();
   }
   // energy rows (element-owned)
-#pragma unroll
-  for (int cl = 0; cl < L1D; ++cl)
-#pragma unroll
-    for (int bl = 0; bl < L1D; ++bl)
-#pragma unroll
-      for (int al = 0; al < L1D; ++al) sO[ln][al + L1D * (bl + L1D * cl)] = sBL[px][al] * sBL[py][bl] * TL[cl];
-  lds_barrier();
-  if (pz < E) {
-    for (int t = pr; t < NLD; t += LPE) {
-      T o = 0;
-#pragma unroll
-      for (int q = 0; q < LPE; ++q) o += sO[pz * LPE + q][t];
-      out[2 * nh1 + (ebase + pz) * NLD + t] = o;
-    }
-  }
-  }
+  const T o = energy_sums3<T>(TL, sBL[px], sBL[py], px, py);
+  if (py < 2 && pz < E) st32(out, 2 * nh1 + (ebase + pz) * NLD + (px & 1) + 2 * (py + 2 * (px >> 1)), o);
 }
 
 // ---- host side ---------------------------------------------------------------------------

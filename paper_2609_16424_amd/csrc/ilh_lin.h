@@ -354,14 +354,81 @@ template <int C>
 __device__ __forceinline__ float dpp_of(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), C, 0xF, 0xF, true));
 }
+template <int C>
+__device__ __forceinline__ double dpp_of(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), C, 0xF, 0xF, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), C, 0xF, 0xF, true));
+}
 // sums over the four lanes of a quad, and over the four quads of a row of 16 lanes, in every lane
-__device__ __forceinline__ float quad_sum(float v) {
+template <typename T>
+__device__ __forceinline__ T quad_sum(T v) {
   v += dpp_of<0xB1>(v);  // quad_perm [1,0,3,2]
   return v + dpp_of<0x4E>(v);  // quad_perm [2,3,0,1]
 }
-__device__ __forceinline__ float quads_sum(float v) {
+template <typename T>
+__device__ __forceinline__ T quads_sum(T v) {
   v += dpp_of<0x124>(v);  // row_ror:4
   return v + dpp_of<0x128>(v);  // row_ror:8
+}
+__device__ __forceinline__ float lane_get(int byte_lane, float v) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(byte_lane, __float_as_int(v)));
+}
+__device__ __forceinline__ double lane_get(int byte_lane, double v) {
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(byte_lane, __double2hiint(v)),
+                          __builtin_amdgcn_ds_bpermute(byte_lane, __double2loint(v)));
+}
+// (the three formed in every lane, then selected: not sunk into branches on the lane)
+template <typename T>
+__device__ __forceinline__ T lane_pick(int i, T v0, T v1, T v2) {
+  asm volatile("" : "+v"(v0), "+v"(v1), "+v"(v2));
+  const T t = i == 1 ? v1 : v2;
+  return i == 0 ? v0 : t;
+}
+
+// Node sums of the 3D Q2 strips, one component.  An element's 4 x 4 quadrature columns are the 16 lanes of
+// a row (px fastest), so the sums over (q_x, q_y) of the factored contributions By_b (Gx_a Tx + Bx_a Tz) +
+// Gy_b Bx_a Ty are quad and row adds of the vector unit: lane (a, b) of the element ends with the sums of
+// node (a, b) of each layer in v, lane (0, b) with those of the node column that it shares with the
+// element before added (takes; from: 4 x that element's lane (2, b)).  Through LDS these sums and
+// their indices were a third to two fifths of the kernels' vector instructions.
+template <typename T>
+__device__ __forceinline__ void node_sums3(const T (&Tx)[3], const T (&Ty)[3], const T (&Tz)[3], const T (&Bx)[3],
+                                           const T (&Gx)[3], const T (&By)[3], const T (&Gy)[3], int px, int py,
+                                           int from, bool takes, T (&v)[3]) {
+  T left[3];
+#pragma unroll
+  for (int cz = 0; cz < 3; ++cz) {
+    T q1[3], q2[3], o[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      q1[a] = quad_sum(Gx[a] * Tx[cz] + Bx[a] * Tz[cz]);
+      q2[a] = quad_sum(Bx[a] * Ty[cz]);
+    }
+    const T s1 = lane_pick(px, q1[0], q1[1], q1[2]), s2 = lane_pick(px, q2[0], q2[1], q2[2]);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) o[b] = quads_sum(By[b] * s1 + Gy[b] * s2);
+    v[cz] = lane_pick(py, o[0], o[1], o[2]);
+  }
+#pragma unroll
+  for (int cz = 0; cz < 3; ++cz) left[cz] = lane_get(from, v[cz]);
+#pragma unroll
+  for (int cz = 0; cz < 3; ++cz) v[cz] = takes ? v[cz] + left[cz] : v[cz];
+}
+
+// Energy rows of the same strips: lane (al + 2 cl, bl) of the element returns entry (al, bl, cl), from the
+// lane's layer sums TL and its L2 values (bx at q_x, by at q_y); lanes py >= 2 return nothing of use.
+template <typename T>
+__device__ __forceinline__ T energy_sums3(const T (&TL)[2], const T* bx, const T* by, int px, int py) {
+  T w[2][2], o[2];
+#pragma unroll
+  for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+    for (int a2 = 0; a2 < 2; ++a2) w[c2][a2] = quad_sum(bx[a2] * TL[c2]);
+  const T w1 = lane_pick(px, w[0][0], w[0][1], w[1][0]);
+  const T wl = px == 3 ? w[1][1] : w1;
+#pragma unroll
+  for (int b2 = 0; b2 < 2; ++b2) o[b2] = quads_sum(by[b2] * wl);
+  return py == 0 ? o[0] : o[1];
 }
 
 // Work-group -> tile map for a chip of 8 XCDs, each with its own L2: work-groups are handed to

@@ -333,13 +333,13 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 // ---- 3D, Q2Q1 (no TG source): the lane map of the 3D linearised kernels ---------------------
 // One wave = EPW elements of one element row (fixed y, z), lane (z, qy, qx) = quadrature column
 // (qx, qy) of element z walking its Q1D points in z.  The lane's position contractions wait in LDS
-// during the walk (where the output columns go after it).  Each velocity component's sums over the
-// strip's columns go through LDS and take one atomic per node and strip.
-// Bound by FP64 arithmetic (about 3000 vector instructions a wave); one wavefront per SIMD left half
-// of the cycles idle, so registers (212, 252 with viscosity) and LDS (20 KB a wave) are laid out for
-// two, and the viscosity switch is fixed at compile time.  72^3 Q2Q1: 1250 us with one wavefront,
-// the contractions in registers and one atomic per node and element, 800 us now; 57x44x39 with
-// viscosity 430 and 331 us.
+// during the walk.  Each velocity component's sums over the strip's columns (node_sums3) take one
+// atomic per node and strip.
+// Bound by FP64 arithmetic (about 2900 vector instructions a wave, 3500 with the sums through LDS); one
+// wavefront per SIMD left half of the cycles idle, so registers (212, 252 with viscosity) and LDS
+// (20 KB a wave) are laid out for two, and the viscosity switch is fixed at compile time.  72^3 Q2Q1:
+// 1250 us with one wavefront, the contractions in registers, sums through LDS and one atomic per node
+// and element; 800 us with two wavefronts, 633 us now.
 template <int D1D, int Q1D, int VISC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_res3d(const KParams P_, const Tab2<double, D1D, Q1D> tb, const double* __restrict__ u,
@@ -349,16 +349,13 @@ k_res3d(const KParams P_, const Tab2<double, D1D, Q1D> tb, const double* __restr
   constexpr int K = D1D - 1, L1D = K, NLD = L1D * L1D * L1D;
   constexpr int LPE = Q1D * Q1D, EPW = 64 / LPE;
   constexpr int NS = K * EPW + 1;
-  constexpr int NND = D1D * D1D * D1D;
-  constexpr int NOP = (NND > NLD ? NND : NLD) | 1;
   constexpr int NNE = 3 * D1D * D1D * NS, RG = (NNE + 63) / 64;  // node entries (c, cz, b, s)
   constexpr int NLS = EPW * NLD, RL = (NLS + 63) / 64;
 
   __shared__ double sW[9][D1D][D1D][NS];  // w_x (3), w_v (3), k_v (3)
   __shared__ double sE[2][NLS];           // w_e, k_e
-  constexpr int NPC = 9 * D1D, NU = NPC > NOP ? NPC : NOP;
-  __shared__ double sU[64 * NU];  // (lane, position contraction), then the output columns (lane, node)
-  auto sO = reinterpret_cast<double(*)[NOP]>(sU);
+  constexpr int NPC = 9 * D1D;
+  __shared__ double sU[64 * NPC];  // (lane, position contraction)
   __shared__ double sBG[2][Q1D][D1D];
   __shared__ double sBL[Q1D][L1D];
 
@@ -576,10 +573,9 @@ k_res3d(const KParams P_, const Tab2<double, D1D, Q1D> tb, const double* __restr
   int ln = threadIdx.x;
   asm volatile("" : "+v"(ln));
   const int pz = ln / LPE, pq = ln - pz * LPE, py = pq / Q1D, px = pq - py * Q1D;
-  // velocity rows, one component at a time: each lane's column contributions to its element's
-  // nodes (factored: out(a,b) = By_b (Gx_a Tx + Bx_a Tz) + Gy_b Bx_a Ty per z-layer) go to LDS; one
-  // thread per node of the strip sums the columns of the (one or two) elements holding it and issues
-  // one atomic add (constrained rows were written by their owner above)
+  // velocity rows: node sums (node_sums3), one atomic per node and strip (constrained rows were written
+  // by their owner above)
+  static_assert(D1D == 3 && Q1D == 4, "one row of 16 lanes per element");
   {
     double Bx[D1D], Gx[D1D], By[D1D], Gy[D1D];
 #pragma unroll
@@ -589,75 +585,29 @@ k_res3d(const KParams P_, const Tab2<double, D1D, Q1D> tb, const double* __restr
       By[a] = sBG[0][py][a];
       Gy[a] = sBG[1][py][a];
     }
-#pragma unroll 1
+    const uint32_t I = K * (ex0 + pz) + px, J = K * ey + py;
+    const bool cI = I == 0 || I == ng0 - 1, cJ = J == 0 || J == ng1 - 1;
+    const bool node = px < D1D && py < D1D && pz < E && !(px == K && pz + 1 < E);
+    const uint32_t off = row0 + (uint32_t)(K * pz + px) + (uint32_t)py * ng0;
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
+      double v[D1D];
+      node_sums3<double>(Tx[c], Ty[c], Tz[c], Bx, Gx, By, Gy, px, py, 4 * (ln - (LPE - K)), px == 0 && pz > 0, v);
 #pragma unroll
       for (int cz = 0; cz < D1D; ++cz) {
-        double tx = 0, ty = 0, tz = 0;
-#pragma unroll
-        for (int cq = 0; cq < 3; ++cq)
-          if (cq == c) {
-            tx = Tx[cq][cz];
-            ty = Ty[cq][cz];
-            tz = Tz[cq][cz];
-          }
-#pragma unroll
-        for (int a = 0; a < D1D; ++a) {
-          const double q1 = Gx[a] * tx + Bx[a] * tz, q2 = Bx[a] * ty;
-#pragma unroll
-          for (int b = 0; b < D1D; ++b) sO[ln][(cz * D1D + b) * D1D + a] = By[b] * q1 + Gy[b] * q2;
-        }
+        const uint32_t Kz = K * ez + cz;
+        const bool cons = c == 0 ? cI : (c == 1 ? cJ : Kz == 0 || Kz == ng2 - 1);
+        if (node && !cons) atomic_add32(r, nh1 + c * N + cz * ng01 + off, v[cz]);
       }
-      lds_barrier();
-      for (int i = ln; i < D1D * D1D * NS; i += 64) {
-        const int s = i % NS, t = i / NS, b = t % D1D, cz = t / D1D;
-        if (s >= ns) continue;
-        const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
-        const uint32_t idx = c == 0 ? I : (c == 1 ? J : Kz), ngc = c == 0 ? ng0 : (c == 1 ? ng1 : ng2);
-        if (idx == 0 || idx == ngc - 1) continue;
-        const int zz = s / K, a = s - K * zz;
-        double o = 0;
-        if (zz < E) {
-#pragma unroll
-          for (int q = 0; q < LPE; ++q) o += sO[zz * LPE + q][(cz * D1D + b) * D1D + a];
-        }
-        if (a == 0 && zz > 0) {
-#pragma unroll
-          for (int q = 0; q < LPE; ++q) o += sO[(zz - 1) * LPE + q][(cz * D1D + b) * D1D + K];
-        }
-        unsafeAtomicAdd(&r[nh1 + c * N + row0 + cz * ng01 + b * ng0 + s], o);
-      }
-      lds_barrier();
     }
   }
   // energy rows (element-owned)
-  {
-    double BLx[L1D], BLy[L1D];
-#pragma unroll
-    for (int a = 0; a < L1D; ++a) {
-      BLx[a] = sBL[px][a];
-      BLy[a] = sBL[py][a];
-    }
-#pragma unroll
-    for (int cl = 0; cl < L1D; ++cl)
-#pragma unroll
-      for (int bl = 0; bl < L1D; ++bl)
-#pragma unroll
-        for (int al = 0; al < L1D; ++al) sO[ln][al + L1D * (bl + L1D * cl)] = BLx[al] * BLy[bl] * TL[cl];
-  }
-  lds_barrier();
+  const double o = energy_sums3<double>(TL, sBL[px], sBL[py], px, py);
+  if (py < 2 && pz < E) st32(r, 2 * nh1 + (ebase + pz) * NLD + (px & 1) + 2 * (py + 2 * (px >> 1)), o);
   if (dmin) {  // the work-group's smallest det J of the stage positions w_x
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) dm = nan_min(dm, __shfl_xor(dm, o, 64));
+    for (int q = 32; q > 0; q >>= 1) dm = nan_min(dm, __shfl_xor(dm, q, 64));
     if (ln == 0) dmin[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = dm;
-  }
-  if (pz < E) {
-    for (int t = pq; t < NLD; t += LPE) {
-      double o = 0;
-#pragma unroll
-      for (int q = 0; q < LPE; ++q) o += sO[pz * LPE + q][t];
-      r[2 * nh1 + (ebase + pz) * NLD + t] = o;
-    }
   }
 }
 

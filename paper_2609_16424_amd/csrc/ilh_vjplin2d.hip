@@ -301,7 +301,8 @@ __global__ void __launch_bounds__(64) k_vjp2d_q(const KParams P, const Tab2<T, D
 // quadrature column and walks q_z, as in the 3D forward kernels; the coefficients are read in
 // the layout k_lin3d stores them.  FP64 keeps the lane's contractions in LDS during the walk and asks
 // for the next coefficients when the point's results are formed, so that two wavefronts fit a SIMD
-// (57x44x39 with viscosity: 815 us with one, 440 us with two; without viscosity 579 and 379 us).
+// (57x44x39 with viscosity: 815 us with one, 440 with two, 382 with the node sums in the vector unit;
+// without viscosity 579, 379 and 302 us; FP32 259 and 205, 217 and 187 us).
 template <int D1D, int Q1D, typename T, int VISC>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_vjp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ y, const T* __restrict__ qd,
@@ -311,16 +312,12 @@ k_vjp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ y, 
   constexpr int NS = K * EPW + 1;
   constexpr int NQD = LinLayout<3, VISC, 0>::NQD;
   constexpr int NF = 6;  // y_x0 y_x1 y_x2, y~_v0 y~_v1 y~_v2 (constrained velocity rows zeroed)
-  constexpr int NND = D1D * D1D * D1D;
-  constexpr int NOP = (NND > NLD ? NND : NLD) | 1;
 
   __shared__ T sS[NF][D1D][D1D][NS];
   __shared__ T sE[EPW * NLD];
-  // during the column walk in FP64 the lane's contractions; after it the output columns (lane, node)
-  constexpr bool PLDS = sizeof(T) == 8;
-  constexpr int NPC = 9 * D1D, NU = PLDS && NPC > NOP ? NPC : NOP;
-  __shared__ T sU[64 * NU];
-  auto sO = reinterpret_cast<T(*)[NOP]>(sU);
+  constexpr bool PLDS = sizeof(T) == 8;  // the lane's contractions wait in LDS during the column walk
+  constexpr int NPC = 9 * D1D;
+  __shared__ T sU[PLDS ? 64 * NPC : 1];
   __shared__ T sBG[2][Q1D][D1D];
   __shared__ T sBL[Q1D][L1D];
 
@@ -510,85 +507,48 @@ k_vjp3d_q(const KParams P, const Tab2<T, D1D, Q1D> tb, const T* __restrict__ y, 
   int ln = threadIdx.x;
   asm volatile("" : "+v"(ln));
   const int pz = ln / LPE, pq = ln - pz * LPE, py = pq / Q1D, px = pq - py * Q1D;
-  // H1 rows (position part, then velocity part), one component at a time: factored expansion of
-  // each lane's column sums into sO, node sums over the (one or two) elements of the strip
-  // holding the node, the owner's identity terms, one atomic per node and strip
+  // H1 rows (position part, then velocity part): node sums (node_sums3), the owner's identity terms, one
+  // atomic per node and strip
+  static_assert(D1D == 3 && Q1D == 4, "one row of 16 lanes per element");
   const T Bxl[D1D] = {sBG[0][px][0], sBG[0][px][1], sBG[0][px][2]};
   const T Gxl[D1D] = {sBG[1][px][0], sBG[1][px][1], sBG[1][px][2]};
   const T Byl[D1D] = {sBG[0][py][0], sBG[0][py][1], sBG[0][py][2]};
   const T Gyl[D1D] = {sBG[1][py][0], sBG[1][py][1], sBG[1][py][2]};
   const bool last_x = (ex0 + E == nx), last_y = (ey == ny - 1), last_z = (ez == P.n[2] - 1);
-#pragma unroll 1
+  const uint32_t I = K * (ex0 + pz) + px, J = K * ey + py;
+  const bool cI = I == 0 || I == ng0 - 1, cJ = J == 0 || J == ng1 - 1;
+  const bool node = px < D1D && py < D1D && pz < E && !(px == K && pz + 1 < E);
+  const uint32_t sl = K * pz + px, off = row0 + sl + (uint32_t)py * ng0;
+  const bool own_xy = (sl < (uint32_t)(K * E) || last_x) && (py < K || last_y);
+#pragma unroll
   for (int pr = 0; pr < 6; ++pr) {
     const int part = pr / 3, r = pr % 3;
-    if (pz < E) {
+    T v[D1D];
+    if (part == 0)
+      node_sums3<T>(Xx[r], Xy[r], Xz[r], Bxl, Gxl, Byl, Gyl, px, py, 4 * (ln - (LPE - K)), px == 0 && pz > 0, v);
+    else
+      node_sums3<T>(Vx[r], Vy[r], Vz[r], Bxl, Gxl, Byl, Gyl, px, py, 4 * (ln - (LPE - K)), px == 0 && pz > 0, v);
+    if (!node) continue;
 #pragma unroll
-      for (int cz = 0; cz < D1D; ++cz) {
-        T tx = 0, ty = 0, tzv = 0;
-#pragma unroll
-        for (int rq = 0; rq < 3; ++rq)
-          if (rq == r) {
-            tx = part == 0 ? Xx[rq][cz] : Vx[rq][cz];
-            ty = part == 0 ? Xy[rq][cz] : Vy[rq][cz];
-            tzv = part == 0 ? Xz[rq][cz] : Vz[rq][cz];
-          }
-#pragma unroll
-        for (int a = 0; a < D1D; ++a) {
-          const T q1 = Gxl[a] * tx + Bxl[a] * tzv, q2 = Bxl[a] * ty;
-#pragma unroll
-          for (int b = 0; b < D1D; ++b) sO[ln][(cz * D1D + b) * D1D + a] = Byl[b] * q1 + Gyl[b] * q2;
-        }
-      }
-    }
-    lds_barrier();
-    for (int i = ln; i < D1D * D1D * NS; i += 64) {
-      const int s = i % NS, t = i / NS, b = t % D1D, cz = t / D1D;
-      if (s >= ns) continue;
-      const int zz = s / K, a = s - K * zz;
-      T o = 0;
-      if (zz < E) {
-#pragma unroll
-        for (int q = 0; q < LPE; ++q) o += sO[zz * LPE + q][(cz * D1D + b) * D1D + a];
-      }
-      if (a == 0 && zz > 0) {
-#pragma unroll
-        for (int q = 0; q < LPE; ++q) o += sO[(zz - 1) * LPE + q][(cz * D1D + b) * D1D + K];
-      }
-      const uint32_t gi = r * N + row0 + cz * ng01 + b * ng0 + s;
-      const bool own = (s < K * E || last_x) && (b < K || last_y) && (cz < K || last_z);
-      if (own) {
-        const T yx = sS[r][cz][b][s];
+    for (int cz = 0; cz < D1D; ++cz) {
+      const uint32_t Kz = K * ez + cz, gi = r * N + cz * ng01 + off;
+      T o = v[cz];
+      if (own_xy && (cz < K || last_z)) {
+        const T yx = sS[r][cz][py][sl];
         if (part == 0) {
           o += yx;
         } else {
           o -= tau * yx;
-          const uint32_t I = K * ex0 + s, J = K * ey + b, Kz = K * ez + cz;
-          const uint32_t idx = r == 0 ? I : (r == 1 ? J : Kz), ngr = r == 0 ? ng0 : (r == 1 ? ng1 : ng2);
-          if (idx == 0 || idx == ngr - 1) o += y[nh1 + gi];
+          const bool cons = r == 0 ? cI : (r == 1 ? cJ : Kz == 0 || Kz == ng2 - 1);
+          if (cons) o += ld32(y, nh1 + gi);
         }
       }
-      unsafeAtomicAdd(&out[part * nh1 + gi], o);
+      atomic_add32(out, part * nh1 + gi, o);
     }
-    lds_barrier();
   }
   // energy rows (element-owned)
-  if (pz < E) {
-#pragma unroll
-    for (int cl = 0; cl < L1D; ++cl)
-#pragma unroll
-      for (int bl = 0; bl < L1D; ++bl)
-#pragma unroll
-        for (int al = 0; al < L1D; ++al) sO[ln][al + L1D * (bl + L1D * cl)] = sBL[px][al] * sBL[py][bl] * TL[cl];
-  }
-  lds_barrier();
-  if (pz < E) {
-    for (int t = pq; t < NLD; t += LPE) {
-      T o = 0;
-#pragma unroll
-      for (int q = 0; q < LPE; ++q) o += sO[pz * LPE + q][t];
-      out[2 * nh1 + (ebase + pz) * NLD + t] = o;
-    }
-  }
+  const T o = energy_sums3<T>(TL, sBL[px], sBL[py], px, py);
+  if (py < 2 && pz < E) st32(out, 2 * nh1 + (ebase + pz) * NLD + (px & 1) + 2 * (py + 2 * (px >> 1)), o);
 }
 
 // ---- host side ---------------------------------------------------------------------------
