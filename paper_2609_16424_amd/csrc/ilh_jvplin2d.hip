@@ -91,6 +91,9 @@ __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double
   }
 #pragma unroll
   for (int a = 0; a < L1D; ++a) BLq[a] = sBLt[qx][a];
+  // Orders 1 and 4: positions relative to the element's first node (see the residual's strip kernel)
+  constexpr bool REL = K == 1 || K == 4;
+  const double x0[2] = {REL ? sS[0][0][s0] : 0.0, REL ? sS[1][0][s0] : 0.0};
   double AB[4][D1D], AG[4][D1D];
 #pragma unroll
   for (int f = 0; f < 4; ++f)
@@ -99,7 +102,7 @@ __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double
       double ab = 0, ag = 0;
 #pragma unroll
       for (int a = 0; a < D1D; ++a) {
-        const double xv = sS[f][b][s0 + a];
+        const double xv = REL && f < 2 ? sS[f][b][s0 + a] - x0[f & 1] : sS[f][b][s0 + a];
         ab += Bq[a] * xv;
         ag += Gq[a] * xv;
       }
@@ -142,7 +145,7 @@ __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double
     double cf[NQD];
     lin_coefs<2, VISC>(P, gam, mq, dJ0, J, Gv, eq, cf);
     if constexpr (SRC != 0) {
-      double xq0 = 0, xq1 = 0;
+      double xq0 = x0[0], xq1 = x0[1];
 #pragma unroll
       for (int b = 0; b < D1D; ++b) {
         xq0 += tb.B[qy][b] * AB[0][b];

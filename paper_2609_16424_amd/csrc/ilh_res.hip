@@ -151,6 +151,11 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
     }
 #pragma unroll
     for (int a = 0; a < L1D; ++a) BLq[a] = sBLt[qx][a];
+    // Orders 1 and 4: positions enter relative to the element's first node, so that the differences J is
+    // made of are formed without rounding at the domain's extent (as in the element kernels, which
+    // these orders ran on before)
+    constexpr bool REL = K == 1 || K == 4;
+    const double x0[2] = {REL ? sW[0][0][s0] : 0.0, REL ? sW[1][0][s0] : 0.0};
     // xi-contractions of the lane's column: w_x and w_v (value and derivative), k_v (value)
     double AB[4][D1D], AG[4][D1D], AK[2][D1D];
 #pragma unroll
@@ -160,7 +165,7 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
         double ab = 0, ag = 0;
 #pragma unroll
         for (int a = 0; a < D1D; ++a) {
-          const double xv = sW[f][b][s0 + a];
+          const double xv = REL && f < 2 ? sW[f][b][s0 + a] - x0[f & 1] : sW[f][b][s0 + a];
           ab += Bq[a] * xv;
           ag += Gq[a] * xv;
         }
@@ -228,7 +233,8 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
       double S[2][2], sq;
       qp_force<2, double>(P, gam, mq, dJ0, J, Gv, eq, S, sq);
       double cl = mq * ke - sq;
-      if constexpr (SRC != 0) cl -= mq * tg_source_c(xq[0], xq[1], gam);
+      if constexpr (SRC != 0)
+        cl -= mq * (REL ? tg_source_c(xq[0] + x0[0], xq[1] + x0[1], gam) : tg_source_c(xq[0], xq[1], gam));
 #pragma unroll
       for (int b = 0; b < D1D; ++b) {
         const double By = tb.B[qy][b], Gy = tb.G[qy][b];
