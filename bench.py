@@ -49,10 +49,10 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_SOURCES = ("paper_2609_16424_amd/csrc/ilh_jvplin2d.hip", "paper_2609_16424_amd/csrc/ilh_lin.h",
                    "paper_2609_16424_amd/csrc/ilh_pointwise.h", "paper_2609_16424_amd/csrc/ilh_internal.h")
 TRAFFIC_SOURCE_END = {"paper_2609_16424_amd/csrc/ilh_internal.h": b"struct ilh_ctx {"}
-TRAFFIC_RECORD = {"sha256": "27386b64d2e5349a588d80bf98687b40352c5154e35d5c37b3c61c3dacac98fb",
+TRAFFIC_RECORD = {"sha256": "10ff5d988e5ea8db7a01c24995d79ac166eb8d4505df4ac84ce9dd40d88da621",
                   "variant": "lin", "n": 128, "order": 3,
-                  "fetch_kib": 16609.3, "fetch_scale": 262144.0 / 131080.04,
-                  "write_kib": 3704.6, "write_scale": 262144.0 / 262144.0}
+                  "fetch_kib": 16609.2, "fetch_scale": 262144.0 / 131081.33,
+                  "write_kib": 3704.4, "write_scale": 262144.0 / 262144.0}
 
 
 def sources_sha256():
@@ -71,7 +71,7 @@ def sources_sha256():
 # VALU instructions per launch of the same kernel (rocprofv3 --pmc SQ_INSTS_VALU, same sources):
 # the issue peak of wave64 FP32 (unpacked) / FP64 VALU instructions is 1024 SIMDs x 2.4 GHz / 4.
 VALU_RECORD = {"sha256": TRAFFIC_RECORD["sha256"], "variant": "lin", "n": 128, "order": 3,
-               "instructions": 2137047.3}
+               "instructions": 2137682.5}
 VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4
 
 
