@@ -119,7 +119,7 @@ struct ilh_ctx {
   double* kry = nullptr;        // V [(m+1)][nblock], Z [m][nblock]
   float* gscr = nullptr;        // learned-guess features and activations, training scratch (allocated on first use)
   int64_t gscr_len = 0;
-  double* gres = nullptr;       // learned-guess judge: residuals of the learned and the plain iterate [2][nblock]
+  double* gres = nullptr;       // learned guess: residuals of the learned and the plain iterate [2][nblock]
   double* pgb = nullptr;        // plain-guess fallback: candidate and residual [2][nblock] (first use)
   double* pdv = nullptr;        // probed diagonal of the velocity block [nh1]
   double* peinv = nullptr;      // inverted probed energy blocks [Ne][Nl][Nl]

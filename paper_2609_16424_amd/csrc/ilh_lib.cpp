@@ -2316,7 +2316,7 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
   if (c->dim != 2 || pl < 2 * ND + NLd) return fail(c, ILH_EINVAL, "prediction stride too small");
   if ((st = guess_assemble(c, out, pl, m->kvscale, m->kescale, m->osc, base, u, tau, k, rl + c->nh1, rb + c->nh1)))
     return st;
-  // judge: residual norms of the learned and the plain iterate, formed and read together
+  // residual norms of the learned and the plain iterate, formed and read together
   if ((st = residual_pair(c, k, rl, base, rb, u, tau))) return st;
   const double tag = (c->est_tag += 1.0);
   double nl, nb;
