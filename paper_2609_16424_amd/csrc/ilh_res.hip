@@ -27,8 +27,10 @@ __device__ __forceinline__ double tg_source_c(double x, double y, double gam) {
   return 0.78539816339744830962 * (c3x * cy - cx * c3y) / (gam - 1.0);
 }
 
-template <int D1D, int Q1D, int SRC>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D1D == 5 ? 1 : 2)))
+// W waves share a strip, each takes Q1D / W of its quadrature rows (W = 2 on meshes whose strips would
+// leave SIMDs idle: a launch is then one wave's chain; 8 x 8 Q2Q1 9.0 -> 7.0 us, 16 x 16 Q3Q2 11.5 -> 9.4).
+template <int D1D, int Q1D, int SRC, int W>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D1D == 5 ? 1 : 2)))
 k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restrict__ u,
         const double* __restrict__ kk1, double tau, double* __restrict__ r1, double* __restrict__ dmin1,
         const double* __restrict__ kk2, double* __restrict__ r2) {
@@ -37,27 +39,29 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
   constexpr int NS = K * EPW + 1;
   constexpr int NVO = 2 * D1D * D1D;
   constexpr int NOP = NVO | 1;
-  constexpr int NNE = 2 * D1D * NS, RG = (NNE + 63) / 64;  // node entries (c, b, s) of the strip
-  constexpr int NLS = EPW * NLD, RL = (NLS + 63) / 64;
+  constexpr int NT = 64 * W, QW = Q1D / W;
+  static_assert(Q1D % W == 0, "the quadrature rows split evenly over the waves");
+  constexpr int NNE = 2 * D1D * NS, RG = (NNE + NT - 1) / NT;  // node entries (c, b, s) of the strip
+  constexpr int NLS = EPW * NLD, RL = (NLS + NT - 1) / NT;
 
   // The gathered strips are read by the xi-contractions only, the per-lane contributions are
   // written after the quadrature rows: one LDS block serves both (the wave's LDS operations
   // complete in program order), which keeps a C2-sized grid resident in one round.
   union StripLds {
     struct {
-      double W[6][D1D][NS];  // w_x (2), w_v (2), k_v (2)
+      double X[6][D1D][NS];  // w_x (2), w_v (2), k_v (2)
       double E[2][NLS];      // w_e, k_e
     } in;
-    double O[64][NOP];  // per-lane contributions (velocity, then energy)
+    double O[NT][NOP];  // per-lane contributions (velocity, then energy)
   };
   __shared__ StripLds sm;
-  auto& sW = sm.in.W;
+  auto& sW = sm.in.X;
   auto& sE = sm.in.E;
   auto& sO = sm.O;
   __shared__ double sBG[2][Q1D][D1D];
   __shared__ double sBLt[Q1D][L1D];
 
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, hw = W == 1 ? 0 : tid / 64, lane = tid - 64 * hw;
   // grid.z = 2: a second residual, R(kk2) into r2, at the same u and tau, by a second set of
   // work-groups (one launch for the two; the XCD map spreads the combined set)
   const uint32_t nt = gridDim.x * gridDim.y;
@@ -80,18 +84,18 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
   const int z = lane / Q1D, qx = lane - z * Q1D;
   const bool active = z < E;
 
-  for (int i = lane; i < Q1D * D1D; i += 64) {
+  for (int i = tid; i < Q1D * D1D; i += NT) {
     sBG[0][i / D1D][i % D1D] = tb.B[i / D1D][i % D1D];
     sBG[1][i / D1D][i % D1D] = tb.G[i / D1D][i % D1D];
   }
-  for (int i = lane; i < Q1D * L1D; i += 64) sBLt[i / L1D][i % L1D] = tb.BL[i / L1D][i % L1D];
+  for (int i = tid; i < Q1D * L1D; i += NT) sBLt[i / L1D][i % L1D] = tb.BL[i / L1D][i % L1D];
 
   // gathers: every lane reads u_x, k_x, u_v, k_v of its node entries (indices clamped in range,
   // so all loads are in flight together), and the energy DOFs of the strip's elements
   double gx[RG], gk[RG], gv[RG], gkv[RG];
 #pragma unroll
   for (int q = 0; q < RG; ++q) {
-    const int i = min(lane + 64 * q, NNE - 1), s = min(i % NS, ns - 1), t = i / NS, b = t % D1D, c = t / D1D;
+    const int i = min(tid + NT * q, NNE - 1), s = min(i % NS, ns - 1), t = i / NS, b = t % D1D, c = t / D1D;
     const uint32_t gi = c * N + row0 + (uint32_t)b * ng0 + s;
     gx[q] = ld32(u, gi);
     gk[q] = ld32(kk, gi);
@@ -101,7 +105,7 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
   double ge[RL], gke[RL];
 #pragma unroll
   for (int q = 0; q < RL; ++q) {
-    const uint32_t i = 2 * nh1 + ebase * NLD + min(lane + 64 * q, E * NLD - 1);
+    const uint32_t i = 2 * nh1 + ebase * NLD + min(tid + NT * q, E * NLD - 1);
     ge[q] = ld32(u, i);
     gke[q] = ld32(kk, i);
   }
@@ -110,7 +114,7 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
   const double dJ0 = P.j0e[ebase + (active ? z : 0)];
 #pragma unroll
   for (int q = 0; q < RG; ++q) {
-    const int i = lane + 64 * q;
+    const int i = tid + NT * q;
     if (i >= NNE) continue;
     const int s = i % NS, t = i / NS, b = t % D1D, c = t / D1D;
     const double wv = gv[q] + tau * gkv[q];
@@ -129,7 +133,7 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
   }
 #pragma unroll
   for (int q = 0; q < RL; ++q) {
-    const int i = lane + 64 * q;
+    const int i = tid + NT * q;
     if (i < NLS) {
       sE[0][i] = ge[q] + tau * gke[q];
       sE[1][i] = gke[q];
@@ -141,8 +145,9 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
 #pragma unroll
   for (int bl = 0; bl < L1D; ++bl) TL[bl] = 0.0;
   double dm = 1e300;  // the lane's smallest det J (dmin set)
-  if (active) {
-    const int s0 = K * z;
+  {
+    // lanes past the strip walk along on its last element: their columns feed no output
+    const int zc = min(z, E - 1), s0 = K * zc;
     double Bq[D1D], Gq[D1D], BLq[L1D];
 #pragma unroll
     for (int a = 0; a < D1D; ++a) {
@@ -187,8 +192,8 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
       double a1 = 0, a2 = 0;
 #pragma unroll
       for (int al = 0; al < L1D; ++al) {
-        a1 += BLq[al] * sE[0][z * NLD + al + L1D * bl];
-        a2 += BLq[al] * sE[1][z * NLD + al + L1D * bl];
+        a1 += BLq[al] * sE[0][zc * NLD + al + L1D * bl];
+        a2 += BLq[al] * sE[1][zc * NLD + al + L1D * bl];
       }
       ALw[bl] = a1;
       ALk[bl] = a2;
@@ -200,7 +205,7 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
       for (int b = 0; b < D1D; ++b) T0[c][b] = T1[c][b] = 0.0;
     const double wx = tb.W[qx] * rj_l;
 #pragma unroll 1
-    for (int qy = 0; qy < Q1D; ++qy) {
+    for (int qy = hw * QW; qy < (hw + 1) * QW; ++qy) {
       double J[2][2], Gv[2][2], kv[2], xq[2];
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -229,7 +234,7 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
         ke += tb.BL[qy][bl] * ALk[bl];
       }
       const double mq = wx * tb.W[qy];
-      if (dmin) dm = nan_min(dm, J[0][0] * J[1][1] - J[0][1] * J[1][0]);
+      if (dmin && active) dm = nan_min(dm, J[0][0] * J[1][1] - J[0][1] * J[1][0]);
       double S[2][2], sq;
       qp_force<2, double>(P, gam, mq, dJ0, J, Gv, eq, S, sq);
       double cl = mq * ke - sq;
@@ -252,20 +257,33 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
       Gq[a] = sBG[1][qx][a];
     }
     asm volatile("" ::: "memory");  // sO overlays the strips read above: keep the order
+    if constexpr (W > 1) lds_barrier();
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int b = 0; b < D1D; ++b)
 #pragma unroll
         for (int a = 0; a < D1D; ++a)
-          sO[lane][c * D1D * D1D + b * D1D + a] = Gq[a] * T0[c][b] + Bq[a] * T1[c][b];
+          sO[tid][c * D1D * D1D + b * D1D + a] = Gq[a] * T0[c][b] + Bq[a] * T1[c][b];
   }
   vm_drained();  // every load is consumed; the position-row stores were issued long before
   lds_barrier();
   if (dmin) {  // the work-group's smallest det J of the stage positions w_x
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) dm = nan_min(dm, __shfl_xor(dm, o, 64));
-    if (lane == 0) dmin[tile] = dm;
+    if constexpr (W == 1) {
+      if (lane == 0) dmin[tile] = dm;
+    } else {
+      __shared__ double sd[W];
+      if (lane == 0) sd[hw] = dm;
+      lds_barrier();
+      if (tid == 0) {
+        double m = sd[0];
+#pragma unroll
+        for (int w = 1; w < W; ++w) m = nan_min(m, sd[w]);
+        dmin[tile] = m;
+      }
+    }
   }
 
   // velocity rows that are not constrained: the Q1D columns of the (one or two) elements of the
@@ -273,65 +291,71 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
   // gs of the rows (component g, node row p): per-lane LDS bases plus per-pass constants, all
   // LDS reads issued before the first sum.
   {
-    constexpr int GS = NS <= 32 ? 32 : 64, NG = 64 / GS, PN = 2 * D1D / NG;
-    int tn = lane % GS, gn = lane / GS;
+    constexpr int GS = NS <= 32 ? 32 : 64, NG = NT / GS, PN = 2 * D1D / NG;
+    static_assert(2 * D1D % NG == 0, "the node rows split evenly over the node groups");
+    // node group gn takes the entries (component, row) = (en & 1, en / 2), en = gn + NG p
+    int tn = tid % GS, gn = tid / GS;
     asm volatile("" : "+v"(tn), "+v"(gn));
-    const int lc = NG == 1 ? 0 : gn;
+    const int lc = gn & 1, lb = gn >> 1;  // (NG = 1: the component alternates with p)
     const int zz = tn / K, a = tn - K * zz;
     const bool left = zz < E, shared = a == 0 && zz > 0;
-    const int oR = min(zz, E - 1) * Q1D * NOP + lc * D1D * D1D + a;
-    int oL = max(zz - 1, 0) * Q1D * NOP + lc * D1D * D1D + K;
+    const int oR = min(zz, E - 1) * Q1D * NOP + lc * D1D * D1D + lb * D1D + a;
+    int oL = max(zz - 1, 0) * Q1D * NOP + lc * D1D * D1D + lb * D1D + K;
     asm volatile("" : "+v"(oL));
     const double* const sOf = &sO[0][0];
     double fv[PN];
 #pragma unroll
     for (int p = 0; p < PN; ++p) {
-      const int cp = NG == 1 ? (p & 1) : 0, bp = NG == 1 ? (p >> 1) : p;
+      const int cp = NG == 1 ? (p & 1) : 0, bp = (NG * p) >> 1;
       const int po = cp * D1D * D1D + bp * D1D;
-      double f0 = sOf[oR + po], f1 = sOf[oL + po];
+      double f0 = 0.0, f1 = 0.0;
 #pragma unroll
-      for (int q = 1; q < Q1D; ++q) {
-        f0 += sOf[oR + po + q * NOP];
-        f1 += sOf[oL + po + q * NOP];
-      }
+      for (int w = 0; w < W; ++w)
+#pragma unroll
+        for (int q = 0; q < Q1D; ++q) {
+          f0 += sOf[oR + po + (64 * w + q) * NOP];
+          f1 += sOf[oL + po + (64 * w + q) * NOP];
+        }
       fv[p] = (left ? f0 : 0.0) + (shared ? f1 : 0.0);
     }
     const uint32_t I = K * ex0 + tn;
-    const bool cI = lc == 0 && (I == 0 || I == ng0 - 1), isv = lc != 0;
-    const uint32_t gb = nh1 + (uint32_t)lc * N + row0 + tn;
+    const bool cI = I == 0 || I == ng0 - 1;
+    const uint32_t gb = nh1 + (uint32_t)lc * N + row0 + (uint32_t)lb * ng0 + tn;
     if (tn < ns) {
 #pragma unroll
       for (int p = 0; p < PN; ++p) {
-        const int cp = NG == 1 ? (p & 1) : 0, bp = NG == 1 ? (p >> 1) : p;
-        const uint32_t J = K * ey + bp;
-        const bool consJ = J == 0 || J == ng1 - 1;
-        const bool cons = NG == 1 ? (cp == 0 ? (I == 0 || I == ng0 - 1) : consJ) : (cI || (isv && consJ));
+        const int cp = NG == 1 ? (p & 1) : 0, bp = (NG * p) >> 1;
+        const uint32_t J = K * ey + lb + bp;
+        const bool cJ = J == 0 || J == ng1 - 1;
+        const bool cons = (lc + cp) == 0 ? cI : cJ;
         if (!cons) atomic_add32(r, gb + (uint32_t)cp * N + (uint32_t)bp * ng0, fv[p]);
       }
     }
   }
   // energy rows (element-owned): the column sums go through sO once the velocity is done
   lds_barrier();
-  if (active) {
+  {
 #pragma unroll
     for (int bl = 0; bl < L1D; ++bl)
 #pragma unroll
-      for (int al = 0; al < L1D; ++al) sO[lane][bl * L1D + al] = sBLt[qx][al] * TL[bl];
+      for (int al = 0; al < L1D; ++al) sO[tid][bl * L1D + al] = sBLt[qx][al] * TL[bl];
   }
   lds_barrier();
-  constexpr int NE = (NLS + 63) / 64;
+  constexpr int NE = (NLS + NT - 1) / NT;
   double ev[NE];
 #pragma unroll
   for (int it = 0; it < NE; ++it) {
-    const int i = min(lane + 64 * it, E * NLD - 1), zz = i / NLD, t = i % NLD;
-    double o = sO[zz * Q1D][t];
+    const int i = min(tid + NT * it, E * NLD - 1), zz = i / NLD, t = i % NLD;
+    double o = 0.0;
 #pragma unroll
-    for (int q = 1; q < Q1D; ++q) o += sO[zz * Q1D + q][t];
+    for (int w = 0; w < W; ++w)
+#pragma unroll
+      for (int q = 0; q < Q1D; ++q) o += sO[64 * w + zz * Q1D + q][t];
     ev[it] = o;
   }
 #pragma unroll
   for (int it = 0; it < NE; ++it) {
-    const int i = lane + 64 * it;
+    const int i = tid + NT * it;
     if (i < E * NLD) st32(r, 2 * nh1 + ebase * NLD + i, ev[it]);
   }
 }
@@ -626,6 +650,12 @@ bool res3d_available(const ilh_ctx* c) {
   return c->dim == 3 && c->k == 2 && !c->kp.tg_source && c->nblock < (int64_t(1) << 28) && !c->general;
 }
 
+// Strips up to which two waves share one (orders 1 to 3; at order 4 the LDS of two would leave one
+// work-group per compute unit): 160 strips of Q3 take 11.7 us with one wave and 9.6 with two, 576 13.0 and
+// 12.6, 1,152 17.1 and 18.7, 1,664 18.4 and 24.0, where the repeated contractions cost more than the
+// shorter chain saves.
+static constexpr int64_t RES2D_SPLIT = 640;
+
 template <int K, int SRC>
 static void res_t(ilh_ctx* c, const double* k, const double* u, double tau, double* r, double* dmin,
                   const double* k2, double* r2) {
@@ -640,7 +670,13 @@ static void res_t(ilh_ctx* c, const double* k, const double* u, double tau, doub
     tb.W[q] = c->h_w1[q];
   }
   const dim3 grid((c->n[0] + EPW - 1) / EPW, c->n[1], k2 ? 2 : 1);
-  klaunch(c, k_res2d<D1D, Q1D, SRC>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
+  if constexpr (K <= 3) {
+    if ((int64_t)grid.x * grid.y * grid.z <= RES2D_SPLIT) {
+      klaunch(c, k_res2d<D1D, Q1D, SRC, 2>, grid, dim3(128), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
+      return;
+    }
+  }
+  klaunch(c, k_res2d<D1D, Q1D, SRC, 1>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
 }
 
 int res3d_groups(const ilh_ctx* c) {
