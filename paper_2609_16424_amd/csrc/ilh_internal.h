@@ -126,6 +126,7 @@ struct ilh_ctx {
   double* rkw = nullptr;        // explicit RK2-average workspace [4 nblock] (allocated on first use)
   bool rkw_zero = false;        // its zero block is filled and the velocity rows of its residual are zero
   double rj0_one = 0.0;         // rho0 |J0| when every element has the same (affine initial mesh), else 0
+  double* tm_all = nullptr;     // the allocation that holds the next two (first use)
   double* tm_w[3][2] = {};      // 1D inverse mass bands: per direction, without and with held ends (first use)
   int tm_bw[3][2] = {};         // and their half bandwidths
   double* tm_tmp = nullptr;     // [2][nh1] vectors between the passes of the direct mass solve

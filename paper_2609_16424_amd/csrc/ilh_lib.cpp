@@ -340,10 +340,7 @@ void ilh_destroy(ilh_ctx* c) {
     if (p) (void)hipFree(p);
   for (void* p : c->qd)
     if (p) (void)hipFree(p);
-  for (auto& w : c->tm_w)
-    for (double* p : w)
-      if (p) (void)hipFree(p);
-  if (c->tm_tmp) (void)hipFree(c->tm_tmp);
+  if (c->tm_all) (void)hipFree(c->tm_all);
   for (hipEvent_t e : c->tev) (void)hipEventDestroy(e);
   if (c->nwords) (void)hipFree(c->nwords);
   for (hipGraphExec_t e : c->gexec)

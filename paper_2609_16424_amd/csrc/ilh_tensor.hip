@@ -119,6 +119,8 @@ static int tensor_setup(ilh_ctx* c) {
     std::vector<double> w;
   };
   std::vector<Inv> invs;  // directions of one extent and the same held ends share theirs
+  std::vector<double> P;  // all weights: one allocation and one copy (each of them costs tenths of a millisecond)
+  size_t at_d[3][2] = {};
   for (int d = 0; d < c->dim; ++d)
     for (int held = 0; held < 2; ++held) {
       const int ends = held ? (c->kp.walls >> (2 * d)) & 3 : 0;
@@ -133,20 +135,23 @@ static int tensor_setup(ilh_ctx* c) {
       const std::vector<double>& W = invs[at].w;
       const int bw = invs[at].bw;
       const int n1 = c->ng[d], nb = 2 * bw + 1, tiles = (n1 + 15) / 16, nt = (16 + 2 * bw + 3) / 4;
-      std::vector<double> P((size_t)tiles * nt * 64, 0.0);
+      const size_t p0 = P.size();
+      at_d[d][held] = p0;
+      P.resize(p0 + (size_t)tiles * nt * 64, 0.0);
       for (int b = 0; b < tiles; ++b)
         for (int t = 0; t < nt; ++t)
           for (int l = 0; l < 64; ++l) {
             const int i = 16 * b + l % 16, col = 16 * b - bw + 4 * t + l / 16, o = col - i + bw;
             if (i < n1 && col >= 0 && col < n1 && o >= 0 && o < nb)
-              P[((size_t)b * nt + t) * 64 + l] = scale * W[(size_t)i * nb + o];
+              P[p0 + ((size_t)b * nt + t) * 64 + l] = scale * W[(size_t)i * nb + o];
           }
-      double*& dst = c->tm_w[d][held];
-      if (!dst) ILH_HIP(c, hipMalloc((void**)&dst, P.size() * sizeof(double)));
-      ILH_HIP(c, hipMemcpy(dst, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice));
       c->tm_bw[d][held] = bw;
     }
-  if (!c->tm_tmp) ILH_HIP(c, hipMalloc((void**)&c->tm_tmp, 2 * (size_t)c->nh1 * sizeof(double)));
+  if (!c->tm_all) ILH_HIP(c, hipMalloc((void**)&c->tm_all, (P.size() + 2 * (size_t)c->nh1) * sizeof(double)));
+  ILH_HIP(c, hipMemcpy(c->tm_all, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice));
+  for (int d = 0; d < c->dim; ++d)
+    for (int held = 0; held < 2; ++held) c->tm_w[d][held] = c->tm_all + at_d[d][held];
+  c->tm_tmp = c->tm_all + P.size();
   c->tm_ok = true;
   return ILH_OK;
 }
