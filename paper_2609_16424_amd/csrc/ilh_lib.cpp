@@ -4,7 +4,6 @@
 
 #include <algorithm>
 #include <atomic>
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -13,6 +12,7 @@
 #include <vector>
 
 #include "ilh_internal.h"
+#include "ilh_wait.h"
 
 // Static scratch of ilh_jvp_noalloc: one array per GPU, held until the process ends.  Host code
 // never uses the name `scratch` as an address (on the host it is only a stand-in for the symbol):
@@ -220,6 +220,12 @@ static int ensure_hest(ilh_ctx* c) {
     ILH_HIP(c, hipHostGetDevicePointer((void**)&c->hest_dev, c->hest, 0));
   }
   return ILH_OK;
+}
+
+// the state of the context's stream as wait_records asks for it
+static int stream_state(ilh_ctx* c, hipError_t* e) {
+  *e = hipStreamQuery(c->stream);
+  return *e == hipSuccess ? 1 : *e == hipErrorNotReady ? 0 : -1;
 }
 
 int ensure_gscr(ilh_ctx* c, int64_t need) {
@@ -1682,49 +1688,33 @@ struct Solver {
       bool dev_end = false;  // the step's end flag is set on the device
       // read step jj's estimate; true when the cycle ends after it
       auto check = [&](int jj, bool& end) -> int {
-        // wait for the tag the step's reduction stores after its estimate; the stream running
-        // dry without it (every enqueued kernel done) is an error, so the wait always ends
+        // wait for the tag the step's reduction stores with its estimate, or for the mark of a step that
+        // was given up; the stream running dry with neither (every enqueued kernel done) is an error, so
+        // the wait always ends
         const volatile double* est = c->hest;
-        const auto t0 = std::chrono::steady_clock::now();
-        auto asked = t0;
-        auto arrived = [&]() { return est[4 * jj + 1] == tag && est[4 * jj + 3] == tag; };
-        for (unsigned spins = 1; !arrived(); ++spins) {
-          __builtin_ia32_pause();
-          if (est[HEST_ABORT + 1] == tag) {
-            given_up = true;
-            return ILH_OK;
-          }
-          if ((spins & 1023) == 0) {
-            const auto now = std::chrono::steady_clock::now();
-            if (now - asked < std::chrono::milliseconds(1)) continue;
-            asked = now;  // (a query costs the stream a marker: not within an ordinary wait)
-            const hipError_t q = hipStreamQuery(c->stream);
-            if (q != hipSuccess && q != hipErrorNotReady) ILH_HIP(c, q);
-            if (q == hipSuccess && !arrived()) {
-              // the stream is done: the tag must arrive (host-mapped stores can trail the
-              // completion the stream reports); give it 10 ms before calling it missing
-              const auto td = std::chrono::steady_clock::now();
-              while (!arrived() && std::chrono::steady_clock::now() - td < std::chrono::milliseconds(10))
-                __builtin_ia32_pause();
-            }
-            if (q == hipSuccess && !arrived()) {
-              // the device's view: cycle-end flag, target, and the previous column's estimate
-              double dv[HDEV_LEN];
-              (void)hipMemcpy(dv, hd, sizeof(dv), hipMemcpyDeviceToHost);
-              const int pj = jj > 0 ? jj - 1 : 0;
-              char msg[512];
-              std::snprintf(msg, sizeof msg,
-                            "FGMRES: a finished step left no residual estimate (column %d, tag %.17g, found %.17g, "
-                            "columns read %d, end flag %g; column %d: host %.17g %.17g tag %.17g, device %.17g "
-                            "%.17g; target host %.17g device %.17g)",
-                            jj, tag, (double)est[4 * jj + 1], total, dv[HDEV_LGSE], pj, (double)est[4 * pj],
-                            (double)est[4 * pj + 2], (double)est[4 * pj + 1], dv[352 + 2 * pj], dv[353 + 2 * pj],
-                            target, dv[252]);
-              return fail(c, ILH_EHIP, msg);
-            }
-            if (std::chrono::steady_clock::now() - t0 > std::chrono::seconds(120))
-              return fail(c, ILH_EHIP, "FGMRES: timed out waiting for a residual estimate");
-          }
+        hipError_t qe = hipSuccess;
+        const Waited wt = wait_records([&] { return est[4 * jj + 1] == tag && est[4 * jj + 3] == tag; },
+                                       [&] { return est[HEST_ABORT + 1] == tag; }, [&] { return stream_state(c, &qe); });
+        if (wt == Waited::GivenUp) {
+          given_up = true;
+          return ILH_OK;
+        }
+        if (wt == Waited::Failed) ILH_HIP(c, qe);
+        if (wt == Waited::TimedOut) return fail(c, ILH_EHIP, "FGMRES: timed out waiting for a residual estimate");
+        if (wt == Waited::Missing) {
+          // the device's view: cycle-end flag, target, and the previous column's estimate
+          double dv[HDEV_LEN];
+          (void)hipMemcpy(dv, hd, sizeof(dv), hipMemcpyDeviceToHost);
+          const int pj = jj > 0 ? jj - 1 : 0;
+          char msg[512];
+          std::snprintf(msg, sizeof msg,
+                        "FGMRES: a finished step left no residual estimate (column %d, tag %.17g, found %.17g, "
+                        "columns read %d, end flag %g; column %d: host %.17g %.17g tag %.17g, device %.17g "
+                        "%.17g; target host %.17g device %.17g)",
+                        jj, tag, (double)est[4 * jj + 1], total, dv[HDEV_LGSE], pj, (double)est[4 * pj],
+                        (double)est[4 * pj + 2], (double)est[4 * pj + 1], dv[352 + 2 * pj], dv[353 + 2 * pj],
+                        target, dv[252]);
+          return fail(c, ILH_EHIP, msg);
         }
         std::atomic_thread_fence(std::memory_order_acquire);
         const double res = est[4 * jj], hn = est[4 * jj + 2];
@@ -1853,25 +1843,12 @@ struct Solver {
 // arrive, when the stream runs dry without them, or after two minutes
 static int read_norms(ilh_ctx* c, double tag, double* a, double* b) {
   const volatile double* rec = c->hest + HEST_PAIR;
-  auto arrived = [&]() { return rec[1] == tag && rec[3] == tag; };
-  const auto t0 = std::chrono::steady_clock::now();
-  auto asked = t0;
-  for (unsigned spins = 1; !arrived(); ++spins) {
-    __builtin_ia32_pause();
-    if ((spins & 1023) != 0) continue;
-    const auto now = std::chrono::steady_clock::now();
-    if (now - asked < std::chrono::milliseconds(1)) continue;
-    asked = now;  // (a query costs the stream a marker: not within an ordinary wait)
-    const hipError_t q = hipStreamQuery(c->stream);
-    if (q != hipSuccess && q != hipErrorNotReady) ILH_HIP(c, q);
-    if (q == hipSuccess) {
-      // (host-mapped stores can trail the completion the stream reports)
-      while (!arrived() && std::chrono::steady_clock::now() - now < std::chrono::milliseconds(10))
-        __builtin_ia32_pause();
-      if (!arrived()) return fail(c, ILH_EHIP, "a finished reduction left no residual norms");
-    }
-    if (now - t0 > std::chrono::seconds(120)) return fail(c, ILH_EHIP, "timed out waiting for residual norms");
-  }
+  hipError_t qe = hipSuccess;
+  const Waited wt = wait_records([&] { return rec[1] == tag && rec[3] == tag; }, [] { return false; },
+                                 [&] { return stream_state(c, &qe); });
+  if (wt == Waited::Failed) ILH_HIP(c, qe);
+  if (wt == Waited::Missing) return fail(c, ILH_EHIP, "a finished reduction left no residual norms");
+  if (wt == Waited::TimedOut) return fail(c, ILH_EHIP, "timed out waiting for residual norms");
   std::atomic_thread_fence(std::memory_order_acquire);
   *a = rec[0];
   *b = rec[2];
