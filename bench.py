@@ -47,7 +47,8 @@ HBM_PEAK_GBS = 8000.0
 # part the device code sees (kernel parameters, tables, wall test: everything before the host-side
 # context struct, whose later declarations do not change the kernel).
 TRAFFIC_SOURCES = ("paper_2609_16424_amd/csrc/ilh_jvplin2d.hip", "paper_2609_16424_amd/csrc/ilh_lin.h",
-                   "paper_2609_16424_amd/csrc/ilh_pointwise.h", "paper_2609_16424_amd/csrc/ilh_internal.h")
+                   "paper_2609_16424_amd/csrc/ilh_pointwise.h", "paper_2609_16424_amd/csrc/ilh_strip.h",
+                   "paper_2609_16424_amd/csrc/ilh_internal.h")
 TRAFFIC_SOURCE_END = {"paper_2609_16424_amd/csrc/ilh_internal.h": b"struct ilh_ctx {"}
 TRAFFIC_RECORD = {"sha256": "10ff5d988e5ea8db7a01c24995d79ac166eb8d4505df4ac84ce9dd40d88da621",
                   "variant": "lin", "n": 128, "order": 3,

@@ -18,6 +18,7 @@
 
 #include "ilh_internal.h"
 #include "ilh_lin.h"
+#include "ilh_strip.h"
 #include "ilh_pointwise.h"
 
 namespace ilh {
@@ -435,10 +436,11 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(VIS
     asm volatile("" : "+v"(tn), "+v"(gn));
     // pass p of group g: component c = lc + cp(p), node row b = lb + bp(p)
     const int lc = NG == 1 ? 0 : (gn & 1), lb = NG <= 2 ? 0 : (gn >> 1);
+    static_assert(strip_last_row(K, Q1D, GS, W, EPW) < 64 * W, "the node phase reads rows that the lanes wrote");
     const int zz = tn / K, a = tn - K * zz, sc = min(tn, ns - 1);
     const bool left = zz < E, shared = a == 0 && zz > 0;
-    const int oR = min(zz, E - 1) * Q1D * NOP + lc * D1D * D1D + lb * D1D + a;
-    int oL = max(zz - 1, 0) * Q1D * NOP + lc * D1D * D1D + lb * D1D + K;
+    const int oR = strip_element(tn, K, E) * Q1D * NOP + lc * D1D * D1D + lb * D1D + a;
+    int oL = strip_left(tn, K, E) * Q1D * NOP + lc * D1D * D1D + lb * D1D + K;
     asm volatile("" : "+v"(oL));  // its own base (not oR minus a constant): immediate LDS offsets
     const int oS = (lc * D1D + lb) * GS + sc;
     const T* const sOf = &sO[0][0][0];

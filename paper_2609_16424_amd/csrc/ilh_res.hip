@@ -15,6 +15,7 @@
 
 #include "ilh_internal.h"
 #include "ilh_lin.h"
+#include "ilh_strip.h"
 #include "ilh_pointwise.h"
 
 namespace ilh {
@@ -297,10 +298,11 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
     int tn = tid % GS, gn = tid / GS;
     asm volatile("" : "+v"(tn), "+v"(gn));
     const int lc = gn & 1, lb = gn >> 1;  // (NG = 1: the component alternates with p)
+    static_assert(strip_last_row(K, Q1D, GS, W, EPW) < 64 * W, "the node phase reads rows that the lanes wrote");
     const int zz = tn / K, a = tn - K * zz;
     const bool left = zz < E, shared = a == 0 && zz > 0;
-    const int oR = min(zz, E - 1) * Q1D * NOP + lc * D1D * D1D + lb * D1D + a;
-    int oL = max(zz - 1, 0) * Q1D * NOP + lc * D1D * D1D + lb * D1D + K;
+    const int oR = strip_element(tn, K, E) * Q1D * NOP + lc * D1D * D1D + lb * D1D + a;
+    int oL = strip_left(tn, K, E) * Q1D * NOP + lc * D1D * D1D + lb * D1D + K;
     asm volatile("" : "+v"(oL));
     const double* const sOf = &sO[0][0];
     double fv[PN];

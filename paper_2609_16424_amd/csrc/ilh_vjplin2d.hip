@@ -17,6 +17,7 @@
 
 #include "ilh_internal.h"
 #include "ilh_lin.h"
+#include "ilh_strip.h"
 
 namespace ilh {
 
@@ -197,10 +198,11 @@ __global__ void __launch_bounds__(64) k_vjp2d_q(const KParams P, const Tab2<T, D
   int tn = lane % GS, gn = lane / GS;
   asm volatile("" : "+v"(tn), "+v"(gn));
   const int lc = NG == 1 ? 0 : gn;
+  static_assert(strip_last_row(K, Q1D, GS, 1, EPW) < 64 * 1, "the node phase reads rows that the lanes wrote");
   const int zz = tn / K, a = tn - K * zz, sc = min(tn, ns - 1);
   const bool left = zz < E, shared = a == 0 && zz > 0;
-  const int oR = min(zz, E - 1) * Q1D * NOP + lc * D1D * D1D + a;
-  int oL = max(zz - 1, 0) * Q1D * NOP + lc * D1D * D1D + K;
+  const int oR = strip_element(tn, K, E) * Q1D * NOP + lc * D1D * D1D + a;
+  int oL = strip_left(tn, K, E) * Q1D * NOP + lc * D1D * D1D + K;
   asm volatile("" : "+v"(oL));
   const int oS = lc * D1D * NS + sc;
   const uint32_t I = K * ex0 + tn;
