@@ -424,11 +424,19 @@ int ilh_set_apply_waves(ilh_ctx* ctx, int waves);
  * it, where the basis vectors fit the registers of one work-group per compute unit (up to 16 to 22
  * basis vectors), else as three launches.  us bounds the time the work-groups wait for one another
  * (default 5,000 microseconds): a step whose work-groups could not all be placed in that time
- * (other work holds the device) is given up, the launches behind it return at once, the solver repeats
- * the cycle with the three launches and the context keeps to them.  us < 0 takes the three
- * launches from the start; us = 0 gives every such step up (the fallback's test).  The result does
- * not depend on it beyond the order of FP additions.  us above 1e6 or NaN: ILH_EINVAL. */
+ * (other work holds the device) is given up, the launches behind it return at once and the solver
+ * repeats the cycle with the three launches.  The rest of that linear solve keeps them, and so do the
+ * next 1, 2, 4, ... 256 linear solves while attempts go on being given up; the setting stays as it is.
+ * us < 0 takes the three launches from the start; us = 0 gives every such step up (the fallback's
+ * test).  The result does not depend on it beyond the order of FP additions.  A call starts the
+ * attempts afresh.  us above 1e6 or NaN: ILH_EINVAL. */
 int ilh_set_step_wait(ilh_ctx* ctx, double us);
+/* How often the context took a launch whose work-groups meet, and how often one was given up, since its
+ * creation (counts: host, ILH_MEETING_COUNTS entries): [0] one-launch Arnoldi steps enqueued (those
+ * behind the end of a cycle return at once), [1] FGMRES cycles repeated after a given-up step, [2]
+ * one-launch residual norms, [3] those formed again after they were given up. */
+#define ILH_MEETING_COUNTS 4
+int ilh_meeting_counts(ilh_ctx* ctx, int64_t* counts);
 int ilh_timing_enable(ilh_ctx* ctx, int on);
 int ilh_timing_read(ilh_ctx* ctx, double* ms, int64_t* launches);
 

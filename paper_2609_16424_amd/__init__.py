@@ -338,6 +338,12 @@ class Hydro:
         another; negative: three launches instead."""
         self._check(self.lib.ilh_set_step_wait(self.ctx, float(us)))
 
+    def meeting_counts(self):
+        """Launches whose work-groups meet, and those given up, since the context's creation."""
+        n = (C.c_int64 * 4)()
+        self._check(self.lib.ilh_meeting_counts(self.ctx, n))
+        return dict(zip(("steps", "cycles_given_up", "norms", "norms_given_up"), n))
+
     def timing(self, on=True):
         self._check(self.lib.ilh_timing_enable(self.ctx, int(bool(on))))
 

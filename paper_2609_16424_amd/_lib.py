@@ -96,6 +96,7 @@ SIGNATURES = {
     "ilh_set_apply_rows": (I, [P, I]),
     "ilh_set_apply_waves": (I, [P, I]),
     "ilh_set_step_wait": (I, [P, D]),
+    "ilh_meeting_counts": (I, [P, P]),
     "ilh_vjp_lin": (I, [P, I, P, P]),
     "ilh_vjp": (I, [P, I, P, P, D, P, P]),
     "ilh_rk2avg_step": (I, [P, P, D]),

@@ -145,6 +145,9 @@ struct ilh_ctx {
   double est_tag = 0.0;         // tag of the current FGMRES cycle (host counter)
   int gs_cus = 0;                // compute units of the device (bounds the work-groups that meet in a launch)
   double gs_wait_us = 5000.0;    // longest wait of those work-groups; < 0: three launches instead; 0: always given up
+  int gs_pause = 0;              // linear solves still to take the three launches after a given-up step
+  int gs_backoff = 0;            // and how many the last one that was given up asked for
+  int64_t meet[ILH_MEETING_COUNTS] = {};  // launches whose work-groups meet, and those given up (ilh_meeting_counts)
   double* gmd = nullptr;        // device Givens state of FGMRES: H [64][64], cs, sn [64], g [65]
   hipStream_t capstream = nullptr;         // stream the Arnoldi-step graphs are captured on
   std::vector<hipGraphExec_t> gexec;       // captured Arnoldi step per basis index

@@ -1671,7 +1671,9 @@ struct Solver {
     const double* rhs = b;
     double* rbuf = c->nwt + 3 * n;  // tmp vector
     int total = 0;
-    pairs = lagged() ? lgs_step_pairs(c, F32) : 0;
+    const bool paused = lagged() && c->gs_pause > 0;  // after a given-up step: this solve keeps the three launches
+    if (paused) --c->gs_pause;
+    pairs = lagged() && !paused ? lgs_step_pairs(c, F32) : 0;
     const bool use_graph = graphable();
     if (use_graph && !c->qd_ok[0]) {  // the linearisation stays outside the captured steps
       if ((st = launch_lin2d(c, 32))) return st;
@@ -1756,6 +1758,7 @@ struct Solver {
               if ((st = lag_step(next, m, L))) return st;
               rec[next] = Rec{skippable, skip_slot, skip_gen};
             }
+            if (pairs > 0 && next <= lgs_step_max_j(pairs, F32)) ++c->meet[0];
             ++next;
           }
           if ((st = check(col, end))) return st;
@@ -1779,10 +1782,13 @@ struct Solver {
         }
       }
       if (given_up) {
-        // the work-groups of a one-launch step could not meet in time (other work held the device):
-        // the launches behind it returned at once, x is as the cycle found it, and the cycle is
-        // repeated with the three launches, which this context then keeps
-        c->gs_wait_us = -1.0;
+        // the work-groups of a one-launch step could not meet in time (other work held the device): the
+        // launches behind it returned at once, x is as the cycle found it, and the cycle is repeated
+        // with the three launches.  The rest of this solve keeps them, and so do the next 1, 2, 4, ... 256
+        // while attempts go on failing: a wait of 5 ms in 256 solves is at most a few per cent of them.
+        ++c->meet[1];
+        c->gs_backoff = std::min(c->gs_backoff > 0 ? 2 * c->gs_backoff : 1, 256);
+        c->gs_pause = c->gs_backoff;
         pairs = 0;
         total = total0;
         jvp_calls = calls0;
@@ -1834,6 +1840,7 @@ struct Solver {
       rhs = rbuf;
       beta2_part = c->red;
     }
+    if (pairs > 0) c->gs_backoff = 0;
     *its = total;
     return ILH_OK;
   }
@@ -2118,6 +2125,15 @@ int ilh_set_step_wait(ilh_ctx* c, double us) {
   if (!c) return ILH_EINVAL;
   if (!(us <= 1e6)) return fail(c, ILH_EINVAL, "step wait must be at most one second");
   c->gs_wait_us = us;
+  c->gs_pause = c->gs_backoff = 0;
+  return ILH_OK;
+  ILH_CATCH(c)
+}
+
+int ilh_meeting_counts(ilh_ctx* c, int64_t* counts) {
+  ILH_TRY
+  if (!c || !counts) return ILH_EINVAL;
+  for (int i = 0; i < ILH_MEETING_COUNTS; ++i) counts[i] = c->meet[i];
   return ILH_OK;
   ILH_CATCH(c)
 }
