@@ -427,9 +427,11 @@ int ilh_set_apply_waves(ilh_ctx* ctx, int waves);
  * (other work holds the device) is given up, the launches behind it return at once and the solver
  * repeats the cycle with the three launches.  The rest of that linear solve keeps them, and so do the
  * next 1, 2, 4, ... 256 linear solves while attempts go on being given up; the setting stays as it is.
- * us < 0 takes the three launches from the start; us = 0 gives every such step up (the fallback's
- * test).  The result does not depend on it beyond the order of FP additions.  A call starts the
- * attempts afresh.  us above 1e6 or NaN: ILH_EINVAL. */
+ * The residual norms of a Newton iteration and of the learned guess are one launch with a meeting too,
+ * under the same bound; norms that were given up are formed again by two launches without one.
+ * us < 0 takes the launches without a meeting from the start; us = 0 gives every meeting up (the
+ * fallbacks' test).  The result does not depend on it beyond the order of FP additions.  A call starts
+ * the attempts afresh.  us above 1e6 or NaN: ILH_EINVAL. */
 int ilh_set_step_wait(ilh_ctx* ctx, double us);
 /* How often the context took a launch whose work-groups meet, and how often one was given up, since its
  * creation (counts: host, ILH_MEETING_COUNTS entries): [0] one-launch Arnoldi steps enqueued (those

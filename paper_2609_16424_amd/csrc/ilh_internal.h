@@ -140,7 +140,7 @@ struct ilh_ctx {
   double* gsp = nullptr;        // partial sums of the lagged Gram-Schmidt dot sweep [132][1024]
   double* hdev = nullptr;       // [HDEV_LEN] device scalars of the Arnoldi step
   double* hest = nullptr;       // pinned, coherent: per Arnoldi column j the records {|g_j+1|, tag} and
-                                // {h_j+1,j, tag} at [4j, 4j + 4); [256, 258) a pair of norms
+                                // {h_j+1,j, tag} at [4j, 4j + 4); then HEST_PAIR and HEST_ABORT
   double* hest_dev = nullptr;   // its device (mapped) address
   double est_tag = 0.0;         // tag of the current FGMRES cycle (host counter)
   int gs_cus = 0;                // compute units of the device (bounds the work-groups that meet in a launch)
@@ -165,6 +165,7 @@ struct ilh_ctx {
   int64_t tgen = 0;  // flushes so far (a pending slot index is valid within one generation)
   hipEvent_t xev0 = nullptr, xev1 = nullptr;  // open single-kernel slot, taken by the next klaunch
   unsigned long long* nwords = nullptr;  // partial sums of launch_norms (first use; empty between launches)
+  bool norms_open = false;               // the last launch of it has not been read: the words may not be empty
   double tms[ILH_TIMING_CLASSES] = {};
   int64_t tcnt[ILH_TIMING_CLASSES] = {};
   std::string err;
@@ -265,9 +266,17 @@ int launch_jacobi(ilh_ctx* c, const double* r, double* z);   // z = r / Mdiag
 int dot_host(ilh_ctx* c, const double* x, const double* y, int64_t n, double* out);
 // device-side dot into d_out (no sync)
 int dot_dev(ilh_ctx* c, const double* x, const double* y, int64_t n, double* d_out);
-// (ilh_ops.hip) the records {value, tag} of |x|^2 and |x2|^2, or of the minimum of mins and |x|^2
-int launch_norms(ilh_ctx* c, const double* x, const double* x2, int64_t n, const double* mins, int nm, double* rec,
-                 double tag);
+// (ilh_ops.hip) the records {value, tag} of |x|^2 and |x2|^2, or of the minimum of mins and |x|^2, at
+// rec (mapped host memory); a launch that was given up stores -tag in the first record's place
+struct Norms {
+  const double* x;
+  const double* x2;  // nullable
+  int64_t n;
+  const double* mins;  // nm of them
+  int nm;
+  double tag;
+};
+int launch_norms(ilh_ctx* c, const Norms& q, double* rec, bool two);
 // out = k1 or 2 k1 - k2 (nhist 1 or 2), position block u_v + tau out_v when tau > 0
 int launch_extrap(ilh_ctx* c, double* out, const double* u, const double* k1, const double* k2, int nhist,
                   double tau);
@@ -288,7 +297,7 @@ constexpr int HDEV_LGSE = 770;
 constexpr int HDEV_LEN = 776;
 // hest[HEST_ABORT, +2): {step, tag} of a cycle whose one-launch step was given up
 constexpr int HEST_ABORT = 260;
-// hest[HEST_PAIR, +4): the two records {value, tag} of launch_norms
+// hest[HEST_PAIR, +4): the two records {value, tag} of launch_norms (first tag negated: given up)
 constexpr int HEST_PAIR = 256;
 // y = H(0:n, 0:n)^-1 g
 int launch_trisolve(ilh_ctx* c, const double* G, int m, int n, double* y);

@@ -1846,17 +1846,35 @@ struct Solver {
   }
 };
 
-// The two values of launch_norms with this tag, read from mapped host memory: the wait ends when the tags
-// arrive, when the stream runs dry without them, or after two minutes
-static int read_norms(ilh_ctx* c, double tag, double* a, double* b) {
+// |x|^2 and |x2|^2 (or the minimum of mins and |x|^2) enqueued, with a tag of their own: one launch whose
+// work-groups meet, unless the context's wait forbids it or the last such launch was never read
+static int ask_norms(ilh_ctx* c, Norms* q) {
+  q->tag = (c->est_tag += 1.0);
+  const bool two = c->gs_wait_us < 0.0 || c->norms_open;
+  if (!two) ++c->meet[2];
+  c->norms_open = true;
+  return launch_norms(c, *q, c->hest_dev + HEST_PAIR, two);
+}
+
+// Their values, read from mapped host memory: the wait ends when the tags arrive, when the stream runs
+// dry without them, or after two minutes.  Norms that were given up are formed again in two launches.
+static int read_norms(ilh_ctx* c, Norms q, double* a, double* b) {
   const volatile double* rec = c->hest + HEST_PAIR;
   hipError_t qe = hipSuccess;
-  const Waited wt = wait_records([&] { return rec[1] == tag && rec[3] == tag; }, [] { return false; },
-                                 [&] { return stream_state(c, &qe); });
-  if (wt == Waited::Failed) ILH_HIP(c, qe);
-  if (wt == Waited::Missing) return fail(c, ILH_EHIP, "a finished reduction left no residual norms");
-  if (wt == Waited::TimedOut) return fail(c, ILH_EHIP, "timed out waiting for residual norms");
+  int st;
+  for (int tries = 0;; ++tries) {
+    const Waited wt = wait_records([&] { return rec[1] == q.tag && rec[3] == q.tag; },
+                                   [&] { return rec[1] == -q.tag; }, [&] { return stream_state(c, &qe); });
+    if (wt == Waited::Arrived) break;
+    if (wt == Waited::Failed) ILH_HIP(c, qe);
+    if (wt == Waited::TimedOut) return fail(c, ILH_EHIP, "timed out waiting for residual norms");
+    if (wt == Waited::Missing || tries > 0) return fail(c, ILH_EHIP, "a finished reduction left no residual norms");
+    ++c->meet[3];
+    q.tag = (c->est_tag += 1.0);
+    if ((st = launch_norms(c, q, c->hest_dev + HEST_PAIR, true))) return st;
+  }
   std::atomic_thread_fence(std::memory_order_acquire);
+  c->norms_open = false;
   *a = rec[0];
   *b = rec[2];
   return ILH_OK;
@@ -1909,22 +1927,21 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
   double* rt = c->nwt + 7 * n;
   Solver<TV> S{c, o, tau};
   double* dsc = dev_pair(c);
-  double tag = 0.0;  // of the norms asked for last
+  Norms asked{};  // the norms asked for last
   auto norms = [&](const double* x, const double* x2, const double* mins, int nm) {
-    return launch_norms(c, x, x2, n, mins, nm, c->hest_dev + HEST_PAIR, tag = (c->est_tag += 1.0));
+    asked = Norms{x, x2, n, mins, nm, 0.0};
+    return ask_norms(c, &asked);
   };
   // Norms are read while the stream already runs the linearisation at the iterate that the next Newton
   // step takes in the common case (kspec: the first iterate, or a trial that a full step leaves); a
   // rejected iterate or a met tolerance discards that linearisation (the next one overwrites it).
   const double* k_lin = nullptr;  // the iterate the stream has been linearised at
   auto read_ahead = [&](const double* kspec, double* a, double* b) -> int {
-    int s1;
     k_lin = nullptr;
-    if (kspec) {
-      if ((s1 = linearize_now(c, kspec, u, tau, o->jvp_prec))) return s1;
-      k_lin = kspec;
-    }
-    return read_norms(c, tag, a, b);
+    const int s1 = kspec ? linearize_now(c, kspec, u, tau, o->jvp_prec) : ILH_OK;
+    const int s2 = read_norms(c, asked, a, b);  // (also after a failure: the context's next norms use the same words)
+    if (!s1) k_lin = kspec;
+    return s1 ? s1 : s2;
   };
   if (!c->zero_ok) {
     if ((st = launch_fill(c, zero, 0.0, n))) return st;
@@ -2308,10 +2325,10 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
     return st;
   // residual norms of the learned and the plain iterate, formed and read together
   if ((st = residual_pair(c, k, rl, base, rb, u, tau))) return st;
-  const double tag = (c->est_tag += 1.0);
+  Norms q{rl, rb, c->nblock, nullptr, 0, 0.0};
   double nl, nb;
-  if ((st = launch_norms(c, rl, rb, c->nblock, nullptr, 0, c->hest_dev + HEST_PAIR, tag))) return st;
-  if ((st = read_norms(c, tag, &nl, &nb))) return st;
+  if ((st = ask_norms(c, &q))) return st;
+  if ((st = read_norms(c, q, &nl, &nb))) return st;
   nl = std::sqrt(nl);
   nb = std::sqrt(nb);
   const bool use = std::isfinite(nl) && (nl < nb || !std::isfinite(nb));

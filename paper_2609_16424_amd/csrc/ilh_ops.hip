@@ -232,13 +232,16 @@ int dot_dev(ilh_ctx* c, const double* x, const double* y, int64_t n, double* d_o
 // {value, tag} in mapped host memory: rec[0 .. 2) the first or the minimum, rec[2 .. 4) the second (or the
 // first again).  nb work-groups a vector leave their partial sums in `words` (agent-scope stores; GS_EMPTY
 // before), the last work-group reads them until none is empty, empties them again and adds them in one
-// order; it is dispatched after the others, so it never keeps them from running.  One launch and no
-// synchronisation: the host reads the tag.  (Partial sums, a final launch and a stream
-// synchronisation took some 10 us more of every Newton iteration.)
+// order.  One launch and no synchronisation: the host reads the tag.  (Partial sums, a final launch
+// and a stream synchronisation took some 10 us more of every Newton iteration.)
+// The last group never keeps the others from running (it is one of several hundred places on the chip),
+// but its wait is bounded all the same: after `limit` ticks of the 100 MHz clock it stores the tag
+// negated, and the host asks for the same norms in two launches (first and last: the groups' and the last
+// group's share of the grid), which meet nowhere.
 __global__ void __launch_bounds__(TPB) k_norms(const double* x, const double* x2, int64_t n, int nb,
                                                unsigned long long* words, const double* mins, int nm, double* rec,
-                                               double tag) {
-  const int ns = x2 ? 2 * nb : nb, b = blockIdx.x;
+                                               double tag, int b0, int never, uint64_t limit) {
+  const int ns = x2 ? 2 * nb : nb, b = (int)blockIdx.x + b0;
   if (b < ns) {
     const bool second = b >= nb;
     const double* v = second ? x2 : x;
@@ -252,21 +255,30 @@ __global__ void __launch_bounds__(TPB) k_norms(const double* x, const double* x2
   }
   double m = 1e300, s[2] = {0.0, 0.0};
   for (int i = threadIdx.x; i < nm; i += TPB) m = nan_min(m, mins[i]);
+  const uint64_t t0 = wall_clock64();
+  bool late = never != 0;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {  // nb <= TPB: one word a thread and sum
-    if ((int)threadIdx.x >= nb || q * nb >= ns) continue;
+    if (late || (int)threadIdx.x >= nb || q * nb >= ns) continue;
     unsigned long long* w = &words[q * nb + threadIdx.x];
     unsigned long long u;
     do u = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (u == GS_EMPTY);
+    while (u == GS_EMPTY && !(late = wall_clock64() - t0 > limit));
     __hip_atomic_store(w, GS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     s[q] = __longlong_as_double((long long)u);
+  }
+  double2* r = reinterpret_cast<double2*>(rec);
+  if (__syncthreads_or(late)) {
+    if (threadIdx.x == 0) {
+      r[0] = make_double2(0.0, -tag);
+      __threadfence_system();
+    }
+    return;
   }
   if (nm > 0) m = block_min<TPB>(m);
   s[0] = block_sum<TPB>(s[0]);
   if (x2) s[1] = block_sum<TPB>(s[1]);
   if (threadIdx.x == 0) {
-    double2* r = reinterpret_cast<double2*>(rec);
     r[0] = make_double2(nm > 0 ? m : s[0], tag);
     r[1] = make_double2(x2 ? s[1] : s[0], tag);
     __threadfence_system();
@@ -278,15 +290,27 @@ __global__ void k_empty(unsigned long long* w, int n) {
   if (i < n) w[i] = GS_EMPTY;
 }
 
-int launch_norms(ilh_ctx* c, const double* x, const double* x2, int64_t n, const double* mins, int nm, double* rec,
-                 double tag) {
-  const int nb = (int)std::min<int64_t>(TPB, std::max<int64_t>(1, (n + 4 * TPB - 1) / (4 * TPB)));
+// two: in two launches, which need no empty words (the first stores all that the second reads, and that
+// one leaves them empty, whatever a launch that was given up or never read left there)
+int launch_norms(ilh_ctx* c, const Norms& q, double* rec, bool two) {
+  const int nb = (int)std::min<int64_t>(TPB, std::max<int64_t>(1, (q.n + 4 * TPB - 1) / (4 * TPB)));
+  const int ns = (q.x2 ? 2 : 1) * nb;
   if (!c->nwords) {
     ILH_HIP(c, hipMalloc((void**)&c->nwords, 2 * TPB * sizeof(unsigned long long)));
     hipLaunchKernelGGL(k_empty, dim3(2), dim3(TPB), 0, c->stream, c->nwords, 2 * TPB);
   }
-  hipLaunchKernelGGL(k_norms, dim3((x2 ? 2 : 1) * nb + 1), dim3(TPB), 0, c->stream, x, x2, n, nb, c->nwords, mins, nm,
-                     rec, tag);
+  auto launch = [&](int groups, int b0, int never, uint64_t limit) {
+    hipLaunchKernelGGL(k_norms, dim3(groups), dim3(TPB), 0, c->stream, q.x, q.x2, q.n, nb, c->nwords, q.mins, q.nm, rec,
+                       q.tag, b0, never, limit);
+  };
+  if (two) {
+    launch(ns, 0, 0, 0);
+    launch(1, ns, 0, ~0ull);
+  } else {
+    // (beside the context's bound, the time that the vectors themselves take at a hundredth of the card's rate)
+    const double us = c->gs_wait_us + (q.x2 ? 2 : 1) * (double)q.n * 1e-4;
+    launch(ns + 1, 0, c->gs_wait_us == 0.0 ? 1 : 0, (uint64_t)(us * 100.0));
+  }
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
 }

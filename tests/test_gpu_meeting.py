@@ -2,7 +2,9 @@
 Arnoldi step is taken and not given up where the basis fits the chip, at every edge of the rule (one
 element; two and three node pairs per thread; cycles longer than the launch holds; captured
 steps), and not taken for vectors too wide for it; a given-up step costs its own linear solve
-and then 1, 2, 4, ... later ones, after which the launch is tried again, and the caller's setting stays."""
+and then 1, 2, 4, ... later ones, after which the launch is tried again, and the caller's setting stays.
+The residual norms likewise: one launch by default, two without a meeting where it is given up or not
+wanted, with the same iterations and values."""
 import pytest
 
 import paper_2609_16424_amd as ilh
@@ -60,3 +62,39 @@ def test_setting_survives_a_given_up_step():
     G.implicit_step(u, dt, opts=opts)
     b = G.meeting_counts()
     assert b["steps"] > a["steps"] and b["cycles_given_up"] == a["cycles_given_up"]
+
+
+@pytest.mark.parametrize("case", ["one_element", "q2_f32", "q2_3d", "two_pairs_f64"])
+def test_norms_are_formed_again_when_given_up(case):
+    problem, n, k, kw, fac = CASES[case]
+    runs = []
+    for wait in (-1.0, 0.0, 5000.0):
+        G = ilh.Hydro(problem, n, k)
+        G.set_step_wait(wait)
+        u = G.init_state()
+        dt = fac * G.dt_estimate(u, 0.5)
+        st = [G.implicit_step(u, dt, opts=ilh.newton_options(tol=1e-10, **kw))[1] for _ in range(2)]
+        runs.append((to_np(u), st, G.meeting_counts()))
+    (a, sa, ca), (b, sb, cb), (c, sc, cc) = runs
+    assert ca["norms"] == 0 and ca["norms_given_up"] == 0
+    assert cb["norms"] > 0 and cb["norms_given_up"] == cb["norms"]
+    assert cc["norms"] == cb["norms"] and cc["norms_given_up"] == 0
+    for x, y, z in zip(sa, sb, sc):
+        assert x["newton"] == y["newton"] == z["newton"]
+        # the first residuals are of the same states: the sums differ by rounding only
+        assert abs(x["res_init"] - y["res_init"]) <= 1e-12 * x["res_init"]
+    assert rel(b, a) <= 1e-9 and rel(c, a) <= 1e-9
+
+
+def test_guess_norms_are_formed_again_when_given_up():
+    from test_gpu_mlp_fused import _guess, _state
+    outs = []
+    for wait in (-1.0, 0.0, 5000.0):
+        G = ilh.Hydro("tg2d", (13, 11), 3)
+        G.set_step_wait(wait)
+        u, _ = _state(G, 5)
+        g, used = _guess(G, (128, 64), True, True, seed=7).guess(u, [0.5 * u], 0.01)
+        outs.append((to_np(g), used, G.meeting_counts()))
+    (a, na, ca), (b, nb, cb), (c, nc, cc) = outs
+    assert ca["norms"] == 0 and cb["norms_given_up"] == cb["norms"] == cc["norms"] > 0 and cc["norms_given_up"] == 0
+    assert na == nb == nc and (a == b).all() and (a == c).all()
