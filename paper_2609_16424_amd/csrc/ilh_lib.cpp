@@ -1590,7 +1590,10 @@ struct Solver {
     mix((uint64_t)c->nblock);
     mix((uint64_t)lagged());
     mix((uint64_t)pairs);
-    mix((uint64_t)(int64_t)c->gs_wait_us);
+    uint64_t wait;  // its bits: fractions of a microsecond are other captured launches
+    static_assert(sizeof(wait) == sizeof(c->gs_wait_us), "");
+    std::memcpy(&wait, &c->gs_wait_us, sizeof(wait));
+    mix(wait);
     return k;
   }
 
@@ -1599,8 +1602,14 @@ struct Solver {
   int graph_for(int j, int m, int L, hipGraphExec_t* out) {
     const uint64_t key = graph_key(m);
     if (key != c->gkey) {
-      for (hipGraphExec_t e : c->gexec)
+      bool any = false;
+      for (hipGraphExec_t e : c->gexec) any = any || e;
+      // (replays can still be under way: those of a cycle that was given up, or behind its end)
+      if (any) ILH_HIP(c, hipStreamSynchronize(c->stream));
+      for (hipGraphExec_t& e : c->gexec) {
         if (e) (void)hipGraphExecDestroy(e);
+        e = nullptr;
+      }
       c->gexec.assign(128, nullptr);
       c->gkey = key;
     }
