@@ -6,13 +6,18 @@
 // the 1D matrix of direction c loses those end rows and the others none.  Its inverse is the tensor
 // product of the 1D inverses.  A 1D inverse is dense, but its entries fall off exponentially (the 1D
 // condition number is 4 to 16): beyond 29 to 68 nodes (k = 1 to 4) they are below 1e-17 of the largest,
-// less than the rounding of the result.  So the solve is one banded product along each direction,
-// exact to rounding, where conjugate gradients took some 20 iterations of nine launches.
+// less than the rounding of the result.  So the solve is one banded product along each direction, where
+// conjugate gradients took some 20 iterations of nine launches.
+//
+// Rounding.  A plain sum over the band rounds some 60 times next to its largest terms (4e-16 to 5e-16 of
+// the solution, twice what conjugate gradients leave).  So the columns left and right of a tile's
+// own ones are summed from the ends of the band inwards, each of the four or five multiplies over its own
+// columns starts from zero, and those sums are added with their rounding errors carried along.
 //
 // The product along a direction is a band matrix times the matrix of all lines, so it runs on the FP64
 // matrix instructions: a wave makes a tile of 16 nodes by 16 lines from (16 + 2 bw) / 4 multiplies of
 // 16x16x4, its weights packed in the operand's lane order.  What bounds it: on small meshes the
-// launches and the round trips to memory (all of a tile's operands are requested 16 multiplies ahead;
+// launches and the round trips to memory (the operands of TM_U multiplies are in flight together;
 // a first form with one lane per node, weights and lines through the caches and LDS, took 13 us a pass at
 // 49 x 49 nodes against 5 and 8 now), on large ones the multiplies, about 2 (16 + 2 bw) flop per node and
 // direction against 16 bytes moved.
@@ -27,15 +32,19 @@
 namespace ilh {
 
 static constexpr int TM_W = 4;   // waves per work-group
-static constexpr int TM_U = 16;  // multiplies whose operands are in flight together
+static constexpr int TM_U = 24;  // multiplies whose operands are in flight together (half from each end): 16 x 16 Q3Q2
+                                 // steps 68.5 us with 24, 72.2 with 16, 73.1 with 32; 96 x 90 133, 126 and 130
+static constexpr int TM_M = 5;   // multiplies that hold a column of the tile's own rows: 4, or 5 where the
+                                 // band starts between two multiples of 4
 
 // The 1D inverse mass matrix on the n k + 1 nodes of a direction as rows of 2 bw + 1 band entries (row
 // i, offset o: column i + o - bw); with lo / hi, the end node is held (its row and column zero).
-// Banded Cholesky (half bandwidth k) in extended precision, so that the weights are the inverse's
-// entries rounded once, then the columns by substitution over a window wide enough that what it leaves
-// out is below 1e-25: those near the low end, which the middle repeats and, where both ends are
-// alike, the high end mirrors.  (Every column near both ends, over 160 nodes, took 2 ms a direction.)
-static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool hi, int* bw_out) {
+// Banded Cholesky (half bandwidth k) in extended precision, and the entries kept so, for weights that are
+// rounded once; then the columns by substitution over a window wide enough that what it leaves out is
+// below 1e-25, from the diagonal down (the inverse is symmetric): those near the two ends, the middle
+// repeats them.  (The high end is not the mirror of the low one: the rounded quadrature points
+// are not symmetric, which put 4e-16 into the solution at k = 4.)
+static std::vector<long double> inverse_band(const ilh_ctx* c, int n, bool lo, bool hi, int* bw_out) {
   const int k = c->k, n1 = n * k + 1, D1D = k + 1, Q1D = 2 * k;
   std::vector<long double> m(D1D * D1D, 0.0L), A((size_t)n1 * D1D, 0.0L);  // A[i][k + j - i], j <= i
   for (int a = 0; a < D1D; ++a)
@@ -59,19 +68,14 @@ static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool h
       A[(size_t)i * D1D + k + j - i] = j == i ? std::sqrt(s) : s / A[(size_t)j * D1D + k];
     }
   const int win = 100;
-  std::vector<double> B((size_t)n1 * (2 * win + 1), 0.0);
+  std::vector<long double> B((size_t)n1 * (2 * win + 1), 0.0L);
   std::vector<long double> y(n1, 0.0L);
+  auto at = [&](int i, int j) -> long double& { return B[(size_t)i * (2 * win + 1) + win + j - i]; };
   const int far = win;  // beyond it from both ends the columns repeat with the elements' period k
   for (int j = 0; j < n1; ++j) {
-    const int i0 = std::max(0, j - win), i1 = std::min(n1 - 1, j + win);
+    const int i1 = std::min(n1 - 1, j + win);
     if (j >= far + k && j < n1 - far) {
-      for (int i = i0; i <= i1; ++i)
-        B[(size_t)i * (2 * win + 1) + win + j - i] = B[(size_t)(i - k) * (2 * win + 1) + win + j - i];
-      continue;
-    }
-    if (lo == hi && j > n1 - 1 - j) {
-      for (int i = i0; i <= i1; ++i)
-        B[(size_t)i * (2 * win + 1) + win + j - i] = B[(size_t)(n1 - 1 - i) * (2 * win + 1) + win + i - j];
+      for (int i = j; i <= i1; ++i) at(i, j) = at(j, i) = at(i - k, j - k);
       continue;
     }
     for (int i = j; i <= i1; ++i) {
@@ -79,21 +83,21 @@ static std::vector<double> inverse_band(const ilh_ctx* c, int n, bool lo, bool h
       for (int p = std::max(j, i - k); p < i; ++p) s -= A[(size_t)i * D1D + k + p - i] * y[p];
       y[i] = s / A[(size_t)i * D1D + k];
     }
-    for (int i = i1; i >= i0; --i) {
-      long double s = i >= j ? y[i] : 0.0L;
+    for (int i = i1; i >= j; --i) {
+      long double s = y[i];
       for (int p = i + 1; p <= std::min(i1, i + k); ++p) s -= A[(size_t)p * D1D + k + i - p] * y[p];
       y[i] = s / A[(size_t)i * D1D + k];
     }
     const bool held = (lo && j == 0) || (hi && j == n1 - 1);
-    for (int i = i0; i <= i1; ++i) B[(size_t)i * (2 * win + 1) + win + j - i] = held ? 0.0 : (double)y[i];
+    for (int i = j; i <= i1; ++i) at(i, j) = at(j, i) = held ? 0.0L : y[i];
   }
-  double top = 0.0;
-  for (double v : B) top = std::max(top, std::fabs(v));
+  long double top = 0.0L;
+  for (long double v : B) top = std::max(top, std::fabs(v));
   int bw = 0;
   for (int i = 0; i < n1; ++i)
     for (int o = 0; o <= 2 * win; ++o)
-      if (std::fabs(B[(size_t)i * (2 * win + 1) + o]) > 1e-18 * top) bw = std::max(bw, std::abs(o - win));
-  std::vector<double> W((size_t)n1 * (2 * bw + 1));
+      if (std::fabs(B[(size_t)i * (2 * win + 1) + o]) > 1e-18L * top) bw = std::max(bw, std::abs(o - win));
+  std::vector<long double> W((size_t)n1 * (2 * bw + 1));
   for (int i = 0; i < n1; ++i)
     for (int o = 0; o <= 2 * bw; ++o) W[(size_t)i * (2 * bw + 1) + o] = B[(size_t)i * (2 * win + 1) + win - bw + o];
   *bw_out = bw;
@@ -116,7 +120,7 @@ static int tensor_setup(ilh_ctx* c) {
   if (c->tm_ok) return ILH_OK;
   struct Inv {
     int n, ends, bw;
-    std::vector<double> w;
+    std::vector<long double> w;
   };
   std::vector<Inv> invs;  // directions of one extent and the same held ends share theirs
   std::vector<double> P;  // all weights: one allocation and one copy (each of them costs tenths of a millisecond)
@@ -124,7 +128,7 @@ static int tensor_setup(ilh_ctx* c) {
   for (int d = 0; d < c->dim; ++d)
     for (int held = 0; held < 2; ++held) {
       const int ends = held ? (c->kp.walls >> (2 * d)) & 3 : 0;
-      const double scale = d == 0 ? 1.0 / c->rj0_one : 1.0;
+      const long double scale = d == 0 ? 1.0L / c->rj0_one : 1.0L;
       size_t at = 0;
       while (at < invs.size() && (invs[at].n != c->n[d] || invs[at].ends != ends)) ++at;
       if (at == invs.size()) {
@@ -132,7 +136,7 @@ static int tensor_setup(ilh_ctx* c) {
         v.w = inverse_band(c, c->n[d], (ends & 1) != 0, (ends & 2) != 0, &v.bw);
         invs.push_back(std::move(v));
       }
-      const std::vector<double>& W = invs[at].w;
+      const std::vector<long double>& W = invs[at].w;
       const int bw = invs[at].bw;
       const int n1 = c->ng[d], nb = 2 * bw + 1, tiles = (n1 + 15) / 16, nt = (16 + 2 * bw + 3) / 4;
       const size_t p0 = P.size();
@@ -143,7 +147,7 @@ static int tensor_setup(ilh_ctx* c) {
           for (int l = 0; l < 64; ++l) {
             const int i = 16 * b + l % 16, col = 16 * b - bw + 4 * t + l / 16, o = col - i + bw;
             if (i < n1 && col >= 0 && col < n1 && o >= 0 && o < nb)
-              P[p0 + ((size_t)b * nt + t) * 64 + l] = scale * W[(size_t)i * nb + o];
+              P[p0 + ((size_t)b * nt + t) * 64 + l] = (double)(scale * W[(size_t)i * nb + o]);
           }
       c->tm_bw[d][held] = bw;
     }
@@ -193,19 +197,65 @@ __global__ void __launch_bounds__(64 * TM_W) k_tensor(const double* __restrict__
   const int64_t base = c * N + (FIRST ? line * n1 : (int64_t)ot * n1 * lines + line);
   const double* w = tw.w[c] + (int64_t)tile * nt * 64 + lane;
   const int r0 = i0 - bw + lk;
-  d4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (int t0 = 0; t0 < nt; t0 += TM_U) {
+  auto wt = [&](int t) { return w[t * 64]; };
+  auto xt = [&](int t) { return in[base + (int64_t)min(max(r0 + 4 * t, 0), n1 - 1) * sn]; };
+  // the multiplies over the tile's own columns, then those left of them (nl) and right of them (nr)
+  const int nl = bw / 4, mid = (bw + 15) / 4 - nl + 1, nr = nt - nl - mid;
+  double am[TM_M], bm[TM_M];
+#pragma unroll
+  for (int q = 0; q < TM_M; ++q) {
+    const int t = nl + min(q, mid - 1);
+    am[q] = wt(t);
+    bm[q] = xt(t);
+  }
+  d4 lo = {0.0, 0.0, 0.0, 0.0}, hi = lo, acc, err;
+  for (int t0 = 0; t0 < max(nl, nr); t0 += TM_U / 2) {
     double a[TM_U], b[TM_U];
 #pragma unroll
     for (int q = 0; q < TM_U; ++q) {
-      const int t = min(t0 + q, nt - 1);
-      a[q] = w[t * 64];
-      b[q] = in[base + (int64_t)min(max(r0 + 4 * t, 0), n1 - 1) * sn];
+      const int t = t0 + q / 2, tt = q % 2 == 0 ? min(t, nt - 1) : max(nt - 1 - t, 0);
+      a[q] = wt(tt);
+      b[q] = xt(tt);
     }
 #pragma unroll
-    for (int q = 0; q < TM_U; ++q)
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(t0 + q < nt ? a[q] : 0.0, b[q], acc, 0, 0, 0);
+    for (int q = 0; q < TM_U; ++q) {
+      const int t = t0 + q / 2;
+      if (q % 2 == 0)
+        lo = __builtin_amdgcn_mfma_f64_16x16x4f64(t < nl ? a[q] : 0.0, b[q], lo, 0, 0, 0);
+      else
+        hi = __builtin_amdgcn_mfma_f64_16x16x4f64(t < nr ? a[q] : 0.0, b[q], hi, 0, 0, 0);
+    }
   }
+  // s + e += x, the rounding error of the sum kept in e
+  auto add = [](double& s, double& e, double x) {
+    const double n = s + x, t = n - s;
+    e += (s - (n - t)) + (x - t);
+    s = n;
+  };
+  acc = lo;
+  err = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    double v = acc[r], e = 0.0;
+    add(v, e, hi[r]);
+    acc[r] = v;
+    err[r] = e;
+  }
+#pragma unroll
+  for (int q = 0; q < TM_M; ++q) {
+    if (q >= mid) break;
+    const d4 zero = {0.0, 0.0, 0.0, 0.0}, x = __builtin_amdgcn_mfma_f64_16x16x4f64(am[q], bm[q], zero, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      double v = acc[r], e = err[r];
+      add(v, e, x[r]);
+      acc[r] = v;
+      err[r] = e;
+    }
+  }
+  // (an infinite sum has no rounding error: inf - inf)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) acc[r] += err[r] == err[r] ? err[r] : 0.0;
   if (!have) return;
   // grid index of the line along direction c of the last pass (c below the pass's direction)
   const uint32_t l32 = (uint32_t)line, ng0 = P.ng[0];
