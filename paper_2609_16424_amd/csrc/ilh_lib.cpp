@@ -794,12 +794,14 @@ int ilh_force_jvp(ilh_ctx* c, int prec, const double* w, const void* dw, void* d
 
 // The stage residual; the kernels accumulate the velocity rows of r, so they start from zero:
 // zeroed here unless the caller has zeroed them already (zero_v false)
-static int residual_into(ilh_ctx* c, const double* k, const double* u, double tau, double* r, bool zero_v) {
+// (rel: see launch_res2d)
+static int residual_into(ilh_ctx* c, const double* k, const double* u, double tau, double* r, bool zero_v,
+                         bool rel = false) {
   int st = zero_v ? launch_fill(c, r + c->nh1, 0.0, c->nh1) : ILH_OK;
   if (st) return st;
   const int slot = tstart_k(c, 1);
   if (c->jvp_variant != 1 && res2d_available(c)) {
-    st = launch_res2d(c, k, u, tau, r);
+    st = launch_res2d(c, k, u, tau, r, nullptr, nullptr, nullptr, rel);
   } else if (c->jvp_variant != 1 && res3d_available(c)) {
     st = launch_res3d(c, k, u, tau, r);
   } else {
@@ -1138,7 +1140,7 @@ int ilh_rk2avg_step(ilh_ctx* c, double* u, double dt) {
   // vm = v + dt/2 a(w), xo = x + dx vm and, with vo, vo = v + dt a(w)
   auto velocity = [&](const double* w, double* vm, double* xo, double dx, double* vo) -> int {
     int s1;
-    if ((s1 = residual_into(c, zero, w, 0.0, f, false))) return s1;
+    if ((s1 = residual_into(c, zero, w, 0.0, f, false, true))) return s1;
     if (direct) {
       MassOut mo;
       mo.b = mo.zero = f + nh1;

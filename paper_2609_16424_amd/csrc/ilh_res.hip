@@ -30,7 +30,7 @@ __device__ __forceinline__ double tg_source_c(double x, double y, double gam) {
 
 // W waves share a strip, each takes Q1D / W of its quadrature rows (W = 2 on meshes whose strips would
 // leave SIMDs idle: a launch is then one wave's chain; 8 x 8 Q2Q1 9.0 -> 7.0 us, 16 x 16 Q3Q2 11.5 -> 9.4).
-template <int D1D, int Q1D, int SRC, int W>
+template <int D1D, int Q1D, int SRC, int W, bool REL>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(D1D == 5 ? 1 : 2)))
 k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restrict__ u,
         const double* __restrict__ kk1, double tau, double* __restrict__ r1, double* __restrict__ dmin1,
@@ -157,10 +157,8 @@ k_res2d(const KParams P, const Tab2<double, D1D, Q1D> tb, const double* __restri
     }
 #pragma unroll
     for (int a = 0; a < L1D; ++a) BLq[a] = sBLt[qx][a];
-    // Orders 1 and 4: positions enter relative to the element's first node, so that the differences J is
-    // made of are formed without rounding at the domain's extent (as in the element kernels, which
-    // these orders ran on before)
-    constexpr bool REL = K == 1 || K == 4;
+    // REL: positions enter relative to the element's first node, so that the differences J is made of are
+    // formed without rounding at the domain's extent (as in the element kernels)
     const double x0[2] = {REL ? sW[0][0][s0] : 0.0, REL ? sW[1][0][s0] : 0.0};
     // xi-contractions of the lane's column: w_x and w_v (value and derivative), k_v (value)
     double AB[4][D1D], AG[4][D1D], AK[2][D1D];
@@ -658,7 +656,7 @@ bool res3d_available(const ilh_ctx* c) {
 // shorter chain saves.
 static constexpr int64_t RES2D_SPLIT = 640;
 
-template <int K, int SRC>
+template <int K, int SRC, bool REL>
 static void res_t(ilh_ctx* c, const double* k, const double* u, double tau, double* r, double* dmin,
                   const double* k2, double* r2) {
   constexpr int D1D = K + 1, Q1D = 2 * K, EPW = 64 / Q1D;
@@ -674,11 +672,11 @@ static void res_t(ilh_ctx* c, const double* k, const double* u, double tau, doub
   const dim3 grid((c->n[0] + EPW - 1) / EPW, c->n[1], k2 ? 2 : 1);
   if constexpr (K <= 3) {
     if ((int64_t)grid.x * grid.y * grid.z <= RES2D_SPLIT) {
-      klaunch(c, k_res2d<D1D, Q1D, SRC, 2>, grid, dim3(128), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
+      klaunch(c, k_res2d<D1D, Q1D, SRC, 2, REL>, grid, dim3(128), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
       return;
     }
   }
-  klaunch(c, k_res2d<D1D, Q1D, SRC, 1>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
+  klaunch(c, k_res2d<D1D, Q1D, SRC, 1, REL>, grid, dim3(64), 0, c->kp, tb, u, k, tau, r, dmin, k2, r2);
 }
 
 int res3d_groups(const ilh_ctx* c) {
@@ -713,22 +711,30 @@ int res2d_groups(const ilh_ctx* c) {
   return ((c->n[0] + EPW - 1) / EPW) * c->n[1];
 }
 
-// r = R(k; u, tau); the velocity rows of r must be zero on entry
+// r = R(k; u, tau); the velocity rows of r must be zero on entry.  Positions are taken relative to their
+// element where the caller asks for it (rel: the explicit step, whose forces came from the element
+// kernels, which do so) and at orders 1 and 4, which ran on those kernels altogether: with absolute
+// positions the velocity of an explicit step was 2.6 times as far from the 64-bit one (24 x 17 Q3Q2
+// Taylor-Green 1.7e-14 against 6.4e-15).  The implicit residual of orders 2 and 3 keeps absolute positions.
 int launch_res2d(ilh_ctx* c, const double* k, const double* u, double tau, double* r, double* dmin, const double* k2,
-                 double* r2) {
+                 double* r2, bool rel) {
   if (!res2d_available(c)) return ILH_EINVAL;
   if ((k2 == nullptr) != (r2 == nullptr) || (r2 && (r2 == r || dmin)))
     return fail(c, ILH_EINVAL, "residual pair: both or neither of k2, r2; distinct outputs; no det J");
-  const int code = 2 * c->k + (c->kp.tg_source ? 1 : 0);
+  const int code = 2 * c->k + (c->kp.tg_source ? 1 : 0) + (rel && (c->k == 2 || c->k == 3) ? 16 : 0);
   switch (code) {
-    case 2: res_t<1, 0>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 3: res_t<1, 1>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 4: res_t<2, 0>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 5: res_t<2, 1>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 6: res_t<3, 0>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 7: res_t<3, 1>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 8: res_t<4, 0>(c, k, u, tau, r, dmin, k2, r2); break;
-    case 9: res_t<4, 1>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 2: res_t<1, 0, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 3: res_t<1, 1, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 4: res_t<2, 0, false>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 5: res_t<2, 1, false>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 6: res_t<3, 0, false>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 7: res_t<3, 1, false>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 8: res_t<4, 0, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 9: res_t<4, 1, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 20: res_t<2, 0, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 21: res_t<2, 1, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 22: res_t<3, 0, true>(c, k, u, tau, r, dmin, k2, r2); break;
+    case 23: res_t<3, 1, true>(c, k, u, tau, r, dmin, k2, r2); break;
     default: return ILH_EINVAL;
   }
   ILH_HIP(c, hipGetLastError());
