@@ -511,7 +511,8 @@ int ilh_mlp_forward(ilh_ctx* ctx, int nl, const int* widths /*host*/, const uint
 
 /* Gradients of the loss 0.5/batch sum_{rows, cols < w_nl} (y - t)^2 (t [batch][P(w_nl)]):
  * dW (float, layout of W) and db (float), both overwritten.  work: float
- * [2 * batch * 128] scratch.  loss (host, nullable) receives the loss (synchronises). */
+ * [2 * batch * 128] scratch, the call's only one: it allocates nothing and may be captured without loss.
+ * loss (host, nullable) receives the loss (synchronises). */
 int ilh_mlp_backward(ilh_ctx* ctx, int nl, const int* widths /*host*/, const uint16_t* WT,
                      const float* x, const float* zs, const float* acts, const float* target,
                      int batch, float* dW, float* db, float* work, double* loss);

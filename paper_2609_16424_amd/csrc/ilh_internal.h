@@ -117,7 +117,7 @@ struct ilh_ctx {
   // Krylov / Newton workspace (allocated on first use)
   int kry_m = 0;
   double* kry = nullptr;        // V [(m+1)][nblock], Z [m][nblock]
-  float* gscr = nullptr;        // learned-guess features and activations, training scratch (allocated on first use)
+  float* gscr = nullptr;        // learned-guess features and activations (allocated on first use)
   int64_t gscr_len = 0;
   double* gres = nullptr;       // learned guess: residuals of the learned and the plain iterate [2][nblock]
   double* pgb = nullptr;        // plain-guess fallback: candidate and residual [2][nblock] (first use)

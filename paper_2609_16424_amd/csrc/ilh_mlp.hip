@@ -68,6 +68,11 @@ struct MlpNet {
   int64_t ao[ML_MAXL];           // offset of the layer's [batch][np] block in zs, acts and the data gradients
   int qo[ML_MAXL + 1];           // first 64 x 64 block of the layer in the weight-gradient grid
   int wtot, btot;
+  // (gradients, not WHOLE) the layers l0 .. l1 of one pair of launches, the offsets of their data
+  // gradients in dzb, and the columns of their bias sums
+  int l0, l1;
+  int64_t zo[ML_MAXL];
+  int bcols;
 };
 
 // 16-byte loads that assume the alignment of one element only (global memory takes them)
@@ -143,21 +148,29 @@ __global__ void __launch_bounds__(ML_T) k_mlp_fwd(const MlpNet F, const uint16_t
 }
 
 // Loss gradient dZ_last = (Y - T) mask / batch, then dZ_{l-1} = (bf(dZ_l) W_l) gelu'(Z_{l-1}) down to
-// layer 0, 16 rows at a time: to dzb in BF16 (the operand the weight gradients take), the column sums
-// of the FP32 values over the work-group's rows to dbp[work-group][btot], the loss sum to part.  Also
-// clears dW for the launch that follows.
+// layer l0, 16 rows at a time: to dzb in BF16 (the operand the weight gradients take), the column sums
+// of the FP32 values over the work-group's rows to db (the first work-group's) and dbp[work-group -
+// 1][bcols], the loss sum to part (nullable).  Also clears dW for the launch that follows.  A group of layers
+// below the last one starts from the data gradients of layer l1 + 1 that an earlier launch left in dzb.
+// WHOLE: all layers, with the offsets of the activations (4,096 rows: 14.8 us, with a group's offsets 15.2;
+// the weight gradients 10.1 and 11.3).
+template <bool WHOLE>
 __global__ void __launch_bounds__(ML_T) k_mlp_bwd(const MlpNet F, const uint16_t* __restrict__ WT,
                                                   const float* __restrict__ zs, const float* __restrict__ acts,
                                                   const float* __restrict__ target, int batch, int nvalid,
                                                   uint16_t* __restrict__ dzb, float* __restrict__ dbp,
-                                                  float* __restrict__ dW, double* __restrict__ part) {
+                                                  float* __restrict__ dW, float* __restrict__ db,
+                                                  double* __restrict__ part) {
   __shared__ __attribute__((aligned(16))) uint16_t sD[2][16][ML_LD];
   __shared__ float sB[ML_MAXL * 128];
   __shared__ double sL[ML_T / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 15, kb = (lane >> 4) * 8;
   const int rl0 = (lane >> 4) * 4, n = wave * 16 + ln;
-  for (int i = blockIdx.x * ML_T + tid; i < F.wtot; i += gridDim.x * ML_T) dW[i] = 0.0f;
-  for (int i = tid; i < F.btot; i += ML_T) sB[i] = 0.0f;
+  const int l0 = WHOLE ? 0 : F.l0, b0 = WHOLE ? 0 : F.bo[F.l0], bcols = WHOLE ? F.btot : F.bcols;
+  const bool from_loss = WHOLE || F.l1 == F.nl - 1;
+  if (from_loss)
+    for (int i = blockIdx.x * ML_T + tid; i < F.wtot; i += gridDim.x * ML_T) dW[i] = 0.0f;
+  for (int i = tid; i < bcols; i += ML_T) sB[i] = 0.0f;
   __syncthreads();
   double loss = 0.0;
   const int ntiles = (batch + 15) / 16;
@@ -169,17 +182,24 @@ __global__ void __launch_bounds__(ML_T) k_mlp_bwd(const MlpNet F, const uint16_t
     for (int j = 0; j < 4; ++j) {
       const uint16_t h = f2bf(v[j]);
       sD[buf][rl0 + j][n] = h;
-      if (row0 + rl0 + j < batch) dzb[F.ao[l] + (int64_t)(row0 + rl0 + j) * NP + n] = h;
+      if (row0 + rl0 + j < batch) dzb[(WHOLE ? F.ao[l] : F.zo[l]) + (int64_t)(row0 + rl0 + j) * NP + n] = h;
       s += v[j];
     }
     s += __shfl_xor(s, 16, 64);
     s += __shfl_xor(s, 32, 64);
-    if (lane < 16) sB[F.bo[l] + n] += s;  // (the column belongs to this wave alone)
+    if (lane < 16) sB[F.bo[l] - b0 + n] += s;  // (the column belongs to this wave alone)
   };
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int row0 = tile * 16;
     int cur = 0;
-    {
+    if (!from_loss) {
+      const int l = F.l1 + 1, NP = F.np[l], r = tid / 32, c = 4 * (tid % 32);
+      if (c < NP) {
+        const uint16_t* p = dzb + F.zo[l] + (int64_t)min(row0 + r, batch - 1) * NP + c;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sD[0][r][c + j] = row0 + r < batch ? p[j] : (uint16_t)0;
+      }
+    } else {
       const int l = F.nl - 1, NP = F.np[l];
       if (wave < NP / 16) {
         float v[4];
@@ -194,7 +214,7 @@ __global__ void __launch_bounds__(ML_T) k_mlp_bwd(const MlpNet F, const uint16_t
         put(l, 0, row0, v);
       }
     }
-    for (int l = F.nl - 1; l > 0; --l) {
+    for (int l = WHOLE ? F.nl - 1 : min(F.l1 + 1, F.nl - 1); l > l0; --l) {
       const int KP = F.kp[l], NP = F.np[l], ns = NP / 32;
       bf16x8 w[4];
       float gz[4];
@@ -217,7 +237,9 @@ __global__ void __launch_bounds__(ML_T) k_mlp_bwd(const MlpNet F, const uint16_t
     }
     __syncthreads();  // the next tile writes the first LDS tile again
   }
-  for (int i = tid; i < F.btot; i += ML_T) dbp[(int64_t)blockIdx.x * F.btot + i] = sB[i];
+  float* bp = blockIdx.x == 0 ? db + b0 : dbp + (int64_t)(blockIdx.x - 1) * bcols;
+  for (int i = tid; i < bcols; i += ML_T) bp[i] = sB[i];
+  if (!from_loss || !part) return;
   for (int o = 32; o > 0; o >>= 1) loss += __shfl_down(loss, o, 64);
   if (lane == 0) sL[wave] = loss;
   __syncthreads();
@@ -244,15 +266,17 @@ __device__ __forceinline__ void transpose8(const u32x4 (&v)[8], u32x4 (&t)[8]) {
 // transposed (a thread loads 8 rows x 8 columns in 16-byte pieces and stores 8 columns), from where a
 // lane reads its 8 consecutive rows in one piece.  The first row of groups also sums the bias gradients
 // and the loss from the parts of the launch before.
+template <bool WHOLE>
 __global__ void __launch_bounds__(256) k_mlp_wgrad(const MlpNet F, const uint16_t* __restrict__ dzb,
                                                    const float* __restrict__ x, const float* __restrict__ acts,
                                                    int batch, float* __restrict__ dW, const float* __restrict__ dbp,
-                                                   const double* __restrict__ part, int nparts, float* __restrict__ db,
+                                                   const double* __restrict__ part, int nparts, float* db,
                                                    double* loss) {
   __shared__ __attribute__((aligned(16))) uint16_t sZ[64][MW_LD], sX[64][MW_LD];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ln = lane & 15, kb = (lane >> 4) * 8;
-  int l = 0;
-  while (l + 1 < F.nl && (int)blockIdx.y >= F.qo[l + 1]) ++l;
+  const int l0 = WHOLE ? 0 : F.l0, l1 = WHOLE ? F.nl - 1 : F.l1, bcols = WHOLE ? F.btot : F.bcols;
+  int l = l0;
+  while (l < l1 && (int)blockIdx.y >= F.qo[l + 1]) ++l;
   const int KP = F.kp[l], NP = F.np[l], qk = (KP + 63) / 64, qi = blockIdx.y - F.qo[l];
   const int n0 = 64 * (qi / qk), k0 = 64 * (qi % qk), nn = min(64, NP - n0), kk = min(64, KP - k0);
   const int b0 = blockIdx.x * MW_ROWS, rb = (t / 8) * 8, cb = (t % 8) * 8;
@@ -263,7 +287,7 @@ __global__ void __launch_bounds__(256) k_mlp_wgrad(const MlpNet F, const uint16_
     for (int i = 0; i < 8; ++i) {
       const int row = b0 + rb + i;
       v[i] = u32x4{0, 0, 0, 0};
-      if (row < batch) v[i] = *reinterpret_cast<const u32x4u*>(dzb + F.ao[l] + (int64_t)row * NP + n0 + cb);
+      if (row < batch) v[i] = *reinterpret_cast<const u32x4u*>(dzb + (WHOLE ? F.ao[l] : F.zo[l]) + (int64_t)row * NP + n0 + cb);
     }
     transpose8(v, o);
 #pragma unroll
@@ -320,13 +344,15 @@ __global__ void __launch_bounds__(256) k_mlp_wgrad(const MlpNet F, const uint16_
     const int col = t & 63;
     float s = 0.0f;
     if (col < nn) {
-      const float* p = dbp + F.bo[l] + n0 + col;
-      for (int b = wave; b < nparts; b += 4 * 16) {  // 16 loads in flight
+      // part 0 waits in db itself: these columns of it are read here only, before the sums replace them
+      if (wave == 0) s = db[F.bo[l] + n0 + col];
+      const float* p = dbp + F.bo[l] - (WHOLE ? 0 : F.bo[l0]) + n0 + col;
+      for (int b = wave; b < nparts - 1; b += 4 * 16) {  // 16 loads in flight
         float v[16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) v[q] = p[(int64_t)min(b + 4 * q, nparts - 1) * F.btot];
+        for (int q = 0; q < 16; ++q) v[q] = p[(int64_t)min(b + 4 * q, nparts - 2) * bcols];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) s += b + 4 * q < nparts ? v[q] : 0.0f;
+        for (int q = 0; q < 16; ++q) s += b + 4 * q < nparts - 1 ? v[q] : 0.0f;
       }
     }
     sF[t] = s;
@@ -663,21 +689,44 @@ int ilh_mlp_backward(ilh_ctx* c, int nl, const int* widths, const uint16_t* WT, 
   if (!c || !widths || !WT || !x || !zs || !acts || !target || !dW || !db || !work || batch <= 0) return ILH_EINVAL;
   int st = check_widths(c, nl, widths);
   if (st) return st;
-  const MlpNet F = make_net(nl, widths, batch);
+  MlpNet F = make_net(nl, widths, batch);
   for (int l = 0; l < nl; ++l)
     if (!layer_shape(F.kp[l], F.np[l]))
       return fail(c, ILH_EINVAL, "unsupported MLP layer width (padded widths 32..128)");
-  // scratch: the loss parts, the bias-gradient parts and the BF16 data gradients of every layer
+  // The caller's work holds 1,024 bytes a row: the BF16 data gradients and the bias sums of all layers (a
+  // part for every 16 rows, the first one in db) where the padded outputs are some 450 or fewer, else of
+  // two layers at a time, the lower one's gradients left for the next pair in one of two slots.
   const int nparts = std::min((batch + 15) / 16, ML_MAXB);
-  const int64_t need = 2 * (int64_t)ML_MAXB + (int64_t)ML_MAXB * F.btot + ((int64_t)batch * F.btot + 1) / 2;
-  if ((st = ensure_gscr(c, need))) return st;
-  double* part = reinterpret_cast<double*>(c->gscr);
-  float* dbp = c->gscr + 2 * ML_MAXB;
-  uint16_t* dzb = reinterpret_cast<uint16_t*>(dbp + (int64_t)ML_MAXB * F.btot);
-  hipLaunchKernelGGL(k_mlp_bwd, dim3(nparts), dim3(ML_T), 0, c->stream, F, WT, zs, acts, target, batch, widths[nl], dzb,
-                     dbp, dW, part);
-  hipLaunchKernelGGL(k_mlp_wgrad, dim3((batch + MW_ROWS - 1) / MW_ROWS, F.qo[nl]), dim3(256), 0, c->stream, F, dzb, x,
-                     acts, batch, dW, dbp, part, nparts, db, loss ? c->red_host + 2 : nullptr);
+  const int64_t room = (int64_t)batch * 1024;
+  uint16_t* dzb = reinterpret_cast<uint16_t*>(work);
+  const bool whole = 2 * (int64_t)batch * F.btot + 4 * (int64_t)(nparts - 1) * F.btot <= room;
+  int slot = 0;
+  for (int hi = nl - 1; hi >= 0; hi = F.l0 - 1) {
+    F.l1 = hi;
+    F.l0 = whole ? 0 : std::max(hi - 1, 0);
+    float* dbp;
+    if (whole) {
+      dbp = reinterpret_cast<float*>(dzb + (int64_t)batch * F.btot);
+    } else {
+      F.zo[hi] = 256 * (int64_t)batch;
+      F.zo[F.l0] = 128 * (int64_t)slot * batch;
+      slot ^= 1;
+      dbp = reinterpret_cast<float*>(dzb + 384 * (int64_t)batch);
+    }
+    F.bcols = 0;
+    F.qo[F.l0] = 0;
+    for (int l = F.l0; l <= hi; ++l) {
+      F.bcols += F.np[l];
+      F.qo[l + 1] = F.qo[l] + ((F.np[l] + 63) / 64) * ((F.kp[l] + 63) / 64);
+    }
+    double* out = loss && hi == nl - 1 ? c->red_host + 2 : nullptr;
+    auto bwd = whole ? k_mlp_bwd<true> : k_mlp_bwd<false>;
+    auto wgrad = whole ? k_mlp_wgrad<true> : k_mlp_wgrad<false>;
+    hipLaunchKernelGGL(bwd, dim3(nparts), dim3(ML_T), 0, c->stream, F, WT, zs, acts, target, batch, widths[nl], dzb,
+                       dbp, dW, db, loss ? c->red : nullptr);
+    hipLaunchKernelGGL(wgrad, dim3((batch + MW_ROWS - 1) / MW_ROWS, F.qo[hi + 1]), dim3(256), 0, c->stream, F, dzb, x,
+                       acts, batch, dW, dbp, c->red, nparts, db, out);
+  }
   ILH_HIP(c, hipGetLastError());
   if (loss) {  // (the last launch writes it to the pinned host buffer)
     ILH_HIP(c, hipStreamSynchronize(c->stream));
