@@ -114,6 +114,7 @@ struct ilh_ctx {
   float* ws32 = nullptr;
   int64_t ws32_len = 0;
   double* pcgbuf = nullptr;     // [4 nh1 + 16] PCG vectors and device scalars
+  bool lin_none = false;    // no room for the tangent coefficients of orders 1 and 4: element kernels instead
   // Krylov / Newton workspace (allocated on first use)
   int kry_m = 0;
   double* kry = nullptr;        // V [(m+1)][nblock], Z [m][nblock]

@@ -539,7 +539,7 @@ static Tab2<T, D1D, Q1D> make_tab2(const ilh_ctx* c) {
 // (and 18.5 for the linearisation; 256 VGPRs and 38 KB of LDS a wave, so one wave per SIMD).
 // 32-bit element offsets into the block vectors (byte offsets below 4 GiB in FP64)
 static bool lin2d_supported(const ilh_ctx* c) {
-  return c->dim == 2 && c->nblock < (int64_t(1) << 29) && !c->general;
+  return c->dim == 2 && c->nblock < (int64_t(1) << 29) && !c->general && !c->lin_none;
 }
 
 static dim3 lin2d_grid(const ilh_ctx* c) {

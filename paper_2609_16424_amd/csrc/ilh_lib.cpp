@@ -864,9 +864,23 @@ int ilh_linearize(ilh_ctx* c, const double* k, const double* u, double tau) {
   ILH_CATCH(c)
 }
 
+// Room for the tangent coefficients of precision prec.  Where the device has none (8 KB an element at
+// order 4 with viscosity in FP64), 2D orders 1 and 4 take the element kernels from then on, which
+// need no coefficients; the other strip kernels have no such stand-in and report the failure.
+static int lin_room(ilh_ctx* c, int prec) {
+  const int p = prec == 64 ? 1 : 0;
+  if (c->jvp_variant != 0 || c->qd[p] || (c->k != 1 && c->k != 4) || !lin2d_available(c)) return ILH_OK;
+  if (hipMalloc(&c->qd[p], (size_t)lin2d_coef_bytes(c, prec)) == hipSuccess) return ILH_OK;
+  (void)hipGetLastError();
+  c->qd[p] = nullptr;
+  c->lin_none = true;
+  return launch_cast_d2f(c, c->w32, c->w64, c->nblock);  // (what ilh_linearize leaves for them)
+}
+
 // The linearised action on an output whose velocity rows the caller has zeroed
 static int jvp_lin_zeroed(ilh_ctx* c, int prec, const void* dk, void* jdk) {
   int st;
+  if ((st = lin_room(c, prec))) return st;
   if (c->jvp_variant == 0 && (lin2d_available(c) || lin3d_available(c))) {
     const bool d3 = c->dim == 3;
     const int p = prec == 64 ? 1 : 0;
@@ -1226,6 +1240,7 @@ static int build_probe_prec(ilh_ctx* c, int mode) {
   int st;
   if (!c->pdv && (st = dalloc(c, &c->pdv, (size_t)c->nh1))) return st;
   if (!c->peinv && (st = dalloc(c, &c->peinv, (size_t)c->Ne * c->Nl * c->Nl))) return st;
+  if ((st = lin_room(c, 32))) return st;
   if (c->jvp_variant == 0 && lin2d_available(c)) {
     if (!c->qd_ok[0]) {
       const int ls = tstart_k(c, 5);
@@ -1919,6 +1934,7 @@ static int stage_solve_t(ilh_ctx* c, const double* u, double tau, const double* 
   if (!c->nwt && (st = dalloc(c, &c->nwt, 8 * (size_t)n))) return st;
   if (!c->hdev && (st = dalloc(c, &c->hdev, HDEV_LEN))) return st;
   if ((st = ensure_hest(c))) return st;
+  if ((st = lin_room(c, o->jvp_prec))) return st;
   if (!c->gmd && (st = dalloc(c, &c->gmd, 64 * 64 + 3 * 65))) return st;
   if (!c->gs_cus) {
     int dev = 0, cus = 0;
