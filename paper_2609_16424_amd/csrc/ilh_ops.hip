@@ -195,7 +195,7 @@ __device__ __forceinline__ double block_min(double v) {
   return r;
 }
 
-// partial sums of x . y, one per block; grid.y = 2: the blocks of row 1 take x2 . y2 into part2
+// partial sums of x . y, one per block
 __global__ void __launch_bounds__(TPB) k_dot_part(const double* x, const double* y, int64_t n, double* part) {
   double acc = 0;
   for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) acc += x[i] * y[i];
@@ -228,6 +228,32 @@ int dot_dev(ilh_ctx* c, const double* x, const double* y, int64_t n, double* d_o
   return ILH_OK;
 }
 
+// Sum over the entries that work-group b of nb takes of a vector of n: f(i, u) returns the sum over the
+// entries i[0 .. u), whose loads are in flight together.  One load at a time left a 378 MB vector
+// (1024^2 Q3Q2) at half of the card's copy rate.
+static constexpr int SUM_U = 4;
+static constexpr int NORM_GROUPS = 1024;  // most work-groups of a vector's sum
+template <typename F>
+__device__ __forceinline__ double strided_sum(int b, int nb, int64_t n, F&& f) {
+  const int64_t step = (int64_t)nb * TPB;
+  double acc = 0.0;
+  int64_t i0 = (int64_t)b * TPB + threadIdx.x;
+  for (; i0 + (SUM_U - 1) * step < n; i0 += SUM_U * step) {
+    int64_t i[SUM_U];
+#pragma unroll
+    for (int q = 0; q < SUM_U; ++q) i[q] = i0 + q * step;
+    acc += f(i, SUM_U);
+  }
+  for (; i0 < n; i0 += step) {
+    int64_t i[SUM_U] = {i0};
+    acc += f(i, 1);
+  }
+  return acc;
+}
+static int sum_groups(int64_t n) {
+  return (int)std::min<int64_t>(NORM_GROUPS, std::max<int64_t>(1, (n + SUM_U * TPB - 1) / (SUM_U * TPB)));
+}
+
 // |x|^2 and, where x2 is set, |x2|^2, or the minimum of mins[0 .. nm) and |x|^2, as two records
 // {value, tag} in mapped host memory: rec[0 .. 2) the first or the minimum, rec[2 .. 4) the second (or the
 // first again).  nb work-groups a vector leave their partial sums in `words` (agent-scope stores; GS_EMPTY
@@ -245,10 +271,14 @@ __global__ void __launch_bounds__(TPB) k_norms(const double* x, const double* x2
   if (b < ns) {
     const bool second = b >= nb;
     const double* v = second ? x2 : x;
-    double acc = 0;
-    for (int64_t i = (int64_t)(second ? b - nb : b) * TPB + threadIdx.x; i < n; i += (int64_t)nb * TPB)
-      acc += v[i] * v[i];
-    acc = block_sum<TPB>(acc);
+    const double acc = block_sum<TPB>(strided_sum(second ? b - nb : b, nb, n, [&](const int64_t (&i)[SUM_U], int u) {
+      double x[SUM_U], a = 0.0;
+#pragma unroll
+      for (int q = 0; q < SUM_U; ++q) x[q] = q < u ? v[i[q]] : 0.0;
+#pragma unroll
+      for (int q = 0; q < SUM_U; ++q) a += x[q] * x[q];
+      return a;
+    }));
     if (threadIdx.x == 0)
       __hip_atomic_store(&words[b], gs_bits(acc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
@@ -258,14 +288,29 @@ __global__ void __launch_bounds__(TPB) k_norms(const double* x, const double* x2
   const uint64_t t0 = wall_clock64();
   bool late = never != 0;
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {  // nb <= TPB: one word a thread and sum
-    if (late || (int)threadIdx.x >= nb || q * nb >= ns) continue;
-    unsigned long long* w = &words[q * nb + threadIdx.x];
-    unsigned long long u;
-    do u = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    while (u == GS_EMPTY && !(late = wall_clock64() - t0 > limit));
-    __hip_atomic_store(w, GS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s[q] = __longlong_as_double((long long)u);
+  for (int q = 0; q < 2; ++q) {
+    if (late || q * nb >= ns) continue;
+    // the thread's words (nb <= NORM_GROUPS), all loads of a round in flight together
+    unsigned long long* w = words + q * nb + threadIdx.x;
+    unsigned long long u[NORM_GROUPS / TPB];
+    bool wait = true;
+#pragma unroll
+    for (int i = 0; i < NORM_GROUPS / TPB; ++i) u[i] = (int)threadIdx.x + i * TPB < nb ? GS_EMPTY : 0ull;
+    while (wait && !late) {
+#pragma unroll
+      for (int i = 0; i < NORM_GROUPS / TPB; ++i)
+        if (u[i] == GS_EMPTY) u[i] = __hip_atomic_load(w + i * TPB, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      wait = false;
+#pragma unroll
+      for (int i = 0; i < NORM_GROUPS / TPB; ++i) wait = wait || u[i] == GS_EMPTY;
+      if (wait) late = wall_clock64() - t0 > limit;
+    }
+#pragma unroll
+    for (int i = 0; i < NORM_GROUPS / TPB; ++i) {
+      if ((int)threadIdx.x + i * TPB < nb)
+        __hip_atomic_store(w + i * TPB, GS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s[q] += __longlong_as_double((long long)u[i]);
+    }
   }
   double2* r = reinterpret_cast<double2*>(rec);
   if (__syncthreads_or(late)) {
@@ -293,11 +338,11 @@ __global__ void k_empty(unsigned long long* w, int n) {
 // two: in two launches, which need no empty words (the first stores all that the second reads, and that
 // one leaves them empty, whatever a launch that was given up or never read left there)
 int launch_norms(ilh_ctx* c, const Norms& q, double* rec, bool two) {
-  const int nb = (int)std::min<int64_t>(TPB, std::max<int64_t>(1, (q.n + 4 * TPB - 1) / (4 * TPB)));
+  const int nb = sum_groups(q.n);
   const int ns = (q.x2 ? 2 : 1) * nb;
   if (!c->nwords) {
-    ILH_HIP(c, hipMalloc((void**)&c->nwords, 2 * TPB * sizeof(unsigned long long)));
-    hipLaunchKernelGGL(k_empty, dim3(2), dim3(TPB), 0, c->stream, c->nwords, 2 * TPB);
+    ILH_HIP(c, hipMalloc((void**)&c->nwords, 2 * NORM_GROUPS * sizeof(unsigned long long)));
+    hipLaunchKernelGGL(k_empty, dim3(2 * NORM_GROUPS / TPB), dim3(TPB), 0, c->stream, c->nwords, 2 * NORM_GROUPS);
   }
   auto launch = [&](int groups, int b0, int never, uint64_t limit) {
     hipLaunchKernelGGL(k_norms, dim3(groups), dim3(TPB), 0, c->stream, q.x, q.x2, q.n, nb, c->nwords, q.mins, q.nm, rec,
@@ -1703,18 +1748,26 @@ template int launch_precond_probe<float>(ilh_ctx*, const float*, float*, float*,
 // ------------------------------------------------------------------ start of an FGMRES cycle
 // r = b - r and the partial sums of |r|^2 (r holds J x on entry)
 __global__ void __launch_bounds__(TPB) k_restart_residual(double* r, const double* b, int64_t n, double* part) {
-  double acc = 0;
-  for (int64_t i = blockIdx.x * (int64_t)TPB + threadIdx.x; i < n; i += (int64_t)gridDim.x * TPB) {
-    const double v = b[i] - r[i];
-    r[i] = v;
-    acc += v * v;
-  }
-  acc = block_sum<TPB>(acc);
+  const double acc = block_sum<TPB>(strided_sum(blockIdx.x, gridDim.x, n, [&](const int64_t (&i)[SUM_U], int u) {
+    double x[SUM_U], y[SUM_U], a = 0.0;
+#pragma unroll
+    for (int q = 0; q < SUM_U; ++q) {
+      x[q] = q < u ? b[i[q]] : 0.0;
+      y[q] = q < u ? r[i[q]] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < SUM_U; ++q) {
+      const double v = x[q] - y[q];
+      if (q < u) r[i[q]] = v;
+      a += v * v;
+    }
+    return a;
+  }));
   if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
 int launch_restart_residual(ilh_ctx* c, double* r, const double* b, int64_t n, double* part, int* np) {
-  *np = (int)std::min<int64_t>(TPB, std::max<int64_t>(1, (n + 4 * TPB - 1) / (4 * TPB)));
+  *np = sum_groups(n);
   hipLaunchKernelGGL(k_restart_residual, dim3(*np), dim3(TPB), 0, c->stream, r, b, n, part);
   ILH_HIP(c, hipGetLastError());
   return ILH_OK;
@@ -1735,7 +1788,10 @@ __global__ void __launch_bounds__(TPB) k_cycle_start(TV* __restrict__ V, const d
   __shared__ double beta_s;
   double beta = beta_h;
   if (np > 0) {
-    double acc = (int)threadIdx.x < np ? part[threadIdx.x] : 0.0;  // np <= TPB
+    double acc = 0.0;
+#pragma unroll
+    for (int q = 0; q < NORM_GROUPS / TPB; ++q)  // np <= NORM_GROUPS
+      acc += (int)threadIdx.x + q * TPB < np ? part[threadIdx.x + q * TPB] : 0.0;
     acc = block_sum<TPB>(acc);
     if (threadIdx.x == 0) beta_s = sqrt(acc);
     __syncthreads();
@@ -1783,7 +1839,7 @@ int launch_cycle_start(ilh_ctx* c, TV* V, const double* r, double beta, const do
                        const CycleStart& cs, double* gsp, int ngsp, int probe, int coupled, TV* z, float* z32,
                        TV* zero_v) {
   const int64_t n = c->nh1 + c->Ne * c->Nl;
-  if (np > TPB || ngsp > n) return fail(c, ILH_EINVAL, "cycle start: more partial sums than it reads or empties");
+  if (np > NORM_GROUPS || ngsp > n) return fail(c, ILH_EINVAL, "cycle start: more partial sums than it reads or empties");
   hipLaunchKernelGGL(k_cycle_start<TV>, dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, c->stream, V, r, beta,
                      part, np, h, cs, gsp, ngsp, probe ? c->pdv : c->Mdiag, probe ? c->peinv : c->MEinv,
                      probe ? (int64_t)c->Nl * c->Nl : c->me_stride, probe ? nullptr : c->me_scale, coupled, z, z32,
