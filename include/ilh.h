@@ -410,7 +410,9 @@ int ilh_set_kernel_variant(ilh_ctx* ctx, int variant);
  * chip and only nodes shared with other waves are added atomically.  rows = 0 (default) picks
  * the count from the mesh size: 1 on meshes whose one-row grid has few waves per SIMD, up to 8
  * on large meshes.  The result does not depend on it beyond the order of FP additions.
- * rows < 0: ILH_EINVAL. */
+ * (2D meshes of order 4 with at most 2,048 elements take single residuals, and those with at most 1,024
+ * single FP64 actions, on the element kernels; a split set here or with ilh_set_apply_waves keeps
+ * the strip kernels.)  rows < 0: ILH_EINVAL. */
 int ilh_set_apply_rows(ilh_ctx* ctx, int rows);
 /* Waves per strip of the 2D FP32 linearised Jacobian-action kernel: 1 (one wave takes every
  * quadrature row of its strip of elements) or 2 (the two waves of a work-group share the strip:

@@ -792,6 +792,17 @@ int ilh_force_jvp(ilh_ctx* c, int prec, const double* w, const void* dw, void* d
   ILH_CATCH(c)
 }
 
+// Small 2D meshes of order 4 keep single residuals and FP64 actions on the element kernels, whose work-groups
+// of one element fill a round of the chip's 256 compute units (eight residuals, four actions each) while
+// a strip launch is one wave's chain of eight quadrature rows: residual 12.5 us up to 2,048 elements
+// against 16.3 (20.5 with viscosity) on strips, 19.3 against 17.1 (20.8) just beyond; linearisation and
+// one FP64 action 17.7 us up to 1,024 elements against 24 (33.5), 24.6 against 24.3 (26.1 and 33.8) beyond.
+// FP32 actions and everything inside the solver stay on the strips (fewer launches, and a quarter of the
+// element kernels' FP32 error), and so does a context whose strip work split was set.
+static bool few_elements(const ilh_ctx* c, int per_cu) {
+  return c->dim == 2 && c->k == 4 && c->Ne <= (int64_t)per_cu * 256 && c->apply_rows == 0 && c->apply_waves == 0;
+}
+
 // The stage residual; the kernels accumulate the velocity rows of r, so they start from zero:
 // zeroed here unless the caller has zeroed them already (zero_v false)
 // (rel: see launch_res2d)
@@ -800,7 +811,7 @@ static int residual_into(ilh_ctx* c, const double* k, const double* u, double ta
   int st = zero_v ? launch_fill(c, r + c->nh1, 0.0, c->nh1) : ILH_OK;
   if (st) return st;
   const int slot = tstart_k(c, 1);
-  if (c->jvp_variant != 1 && res2d_available(c)) {
+  if (c->jvp_variant != 1 && res2d_available(c) && !few_elements(c, 8)) {
     st = launch_res2d(c, k, u, tau, r, nullptr, nullptr, nullptr, rel);
   } else if (c->jvp_variant != 1 && res3d_available(c)) {
     st = launch_res3d(c, k, u, tau, r);
@@ -880,8 +891,10 @@ static int lin_room(ilh_ctx* c, int prec) {
 // The linearised action on an output whose velocity rows the caller has zeroed
 static int jvp_lin_zeroed(ilh_ctx* c, int prec, const void* dk, void* jdk) {
   int st;
-  if ((st = lin_room(c, prec))) return st;
-  if (c->jvp_variant == 0 && (lin2d_available(c) || lin3d_available(c))) {
+  // (element kernels unless the coefficients are there already; in FP64 they need the state only)
+  const bool elem = prec == 64 && c->jvp_variant == 0 && lin2d_available(c) && few_elements(c, 4) && !c->qd_ok[1];
+  if (!elem && (st = lin_room(c, prec))) return st;
+  if (!elem && c->jvp_variant == 0 && (lin2d_available(c) || lin3d_available(c))) {
     const bool d3 = c->dim == 3;
     const int p = prec == 64 ? 1 : 0;
     if (!c->qd_ok[p]) {
