@@ -40,10 +40,9 @@ static constexpr int TM_M = 5;   // multiplies that hold a column of the tile's 
 // The 1D inverse mass matrix on the n k + 1 nodes of a direction as rows of 2 bw + 1 band entries (row
 // i, offset o: column i + o - bw); with lo / hi, the end node is held (its row and column zero).
 // Banded Cholesky (half bandwidth k) in extended precision, and the entries kept so, for weights that are
-// rounded once; then the columns by substitution over a window wide enough that what it leaves out is
-// below 1e-25, from the diagonal down (the inverse is symmetric): those near the two ends, the middle
-// repeats them.  (The high end is not the mirror of the low one: the rounded quadrature points
-// are not symmetric, which put 4e-16 into the solution at k = 4.)
+// rounded once; the rows of the inverse from the last one up, over a window wide enough that what it
+// leaves out is below 1e-25, the middle rows repeated.  (The low end is not the mirror of the high one:
+// the rounded quadrature points are not symmetric, which put 4e-16 into the solution at k = 4.)
 static std::vector<long double> inverse_band(const ilh_ctx* c, int n, bool lo, bool hi, int* bw_out) {
   const int k = c->k, n1 = n * k + 1, D1D = k + 1, Q1D = 2 * k;
   std::vector<long double> m(D1D * D1D, 0.0L), A((size_t)n1 * D1D, 0.0L);  // A[i][k + j - i], j <= i
@@ -67,39 +66,39 @@ static std::vector<long double> inverse_band(const ilh_ctx* c, int n, bool lo, b
         if (j - p <= k) s -= A[(size_t)i * D1D + k + p - i] * A[(size_t)j * D1D + k + p - j];
       A[(size_t)i * D1D + k + j - i] = j == i ? std::sqrt(s) : s / A[(size_t)j * D1D + k];
     }
-  const int win = 100;
-  std::vector<long double> B((size_t)n1 * (2 * win + 1), 0.0L);
-  std::vector<long double> y(n1, 0.0L);
-  auto at = [&](int i, int j) -> long double& { return B[(size_t)i * (2 * win + 1) + win + j - i]; };
-  const int far = win;  // beyond it from both ends the columns repeat with the elements' period k
-  for (int j = 0; j < n1; ++j) {
-    const int i1 = std::min(n1 - 1, j + win);
-    if (j >= far + k && j < n1 - far) {
-      for (int i = j; i <= i1; ++i) at(i, j) = at(j, i) = at(i - k, j - k);
+  // Rows of the inverse Z from the last one up, right of the diagonal (it is symmetric): with A = L L^T,
+  // L_ii Z_ij = [i = j] / L_ii - sum_{i < p <= i + k} L_pi Z_pj.  U[i][d] = Z_{i, i + d}.
+  const int win = 100, far = win;  // beyond `far` from both ends the rows repeat with the elements' period k
+  std::vector<long double> U((size_t)n1 * (win + 1), 0.0L);
+  long double top = 0.0L;
+  for (int i = n1 - 1; i >= 0; --i) {
+    long double* u = &U[(size_t)i * (win + 1)];
+    if (i >= far && i <= n1 - 1 - far - k) {
+      std::copy(u + (size_t)k * (win + 1), u + (size_t)(k + 1) * (win + 1), u);
       continue;
     }
-    for (int i = j; i <= i1; ++i) {
-      long double s = i == j ? 1.0L : 0.0L;
-      for (int p = std::max(j, i - k); p < i; ++p) s -= A[(size_t)i * D1D + k + p - i] * y[p];
-      y[i] = s / A[(size_t)i * D1D + k];
+    const int m = std::min(win, n1 - 1 - i), np = std::min(k, n1 - 1 - i);
+    const long double r = 1.0L / A[(size_t)i * D1D + k];
+    for (int q = 1; q <= np; ++q) {
+      const long double l = A[(size_t)(i + q) * D1D + k - q];
+      const long double* z = u + (size_t)q * (win + 1);  // row i + q
+      for (int d = q; d <= m; ++d) u[d] -= l * z[d - q];
+      for (int d = 1; d < q; ++d) u[d] -= l * U[(size_t)(i + d) * (win + 1) + q - d];
     }
-    for (int i = i1; i >= j; --i) {
-      long double s = y[i];
-      for (int p = i + 1; p <= std::min(i1, i + k); ++p) s -= A[(size_t)p * D1D + k + i - p] * y[p];
-      y[i] = s / A[(size_t)i * D1D + k];
-    }
-    const bool held = (lo && j == 0) || (hi && j == n1 - 1);
-    for (int i = j; i <= i1; ++i) at(i, j) = at(j, i) = held ? 0.0L : y[i];
+    for (int d = 1; d <= m; ++d) u[d] *= r;
+    long double s = r;
+    for (int q = 1; q <= np; ++q) s -= A[(size_t)(i + q) * D1D + k - q] * u[q];
+    u[0] = (lo && i == 0) || (hi && i == n1 - 1) ? 0.0L : s * r;
+    for (int d = 0; d <= m; ++d) top = std::max(top, std::fabs(u[d]));
   }
-  long double top = 0.0L;
-  for (long double v : B) top = std::max(top, std::fabs(v));
   int bw = 0;
   for (int i = 0; i < n1; ++i)
-    for (int o = 0; o <= 2 * win; ++o)
-      if (std::fabs(B[(size_t)i * (2 * win + 1) + o]) > 1e-18L * top) bw = std::max(bw, std::abs(o - win));
-  std::vector<long double> W((size_t)n1 * (2 * bw + 1));
+    for (int d = win; d > bw; --d)
+      if (std::fabs(U[(size_t)i * (win + 1) + d]) > 1e-18L * top) bw = d;
+  std::vector<long double> W((size_t)n1 * (2 * bw + 1), 0.0L);
   for (int i = 0; i < n1; ++i)
-    for (int o = 0; o <= 2 * bw; ++o) W[(size_t)i * (2 * bw + 1) + o] = B[(size_t)i * (2 * win + 1) + win - bw + o];
+    for (int d = 0; d <= std::min(bw, n1 - 1 - i); ++d)
+      W[(size_t)i * (2 * bw + 1) + bw + d] = W[(size_t)(i + d) * (2 * bw + 1) + bw - d] = U[(size_t)i * (win + 1) + d];
   *bw_out = bw;
   return W;
 }
@@ -136,19 +135,20 @@ static int tensor_setup(ilh_ctx* c) {
         v.w = inverse_band(c, c->n[d], (ends & 1) != 0, (ends & 2) != 0, &v.bw);
         invs.push_back(std::move(v));
       }
-      const std::vector<long double>& W = invs[at].w;
+      const std::vector<long double>& Wl = invs[at].w;
+      std::vector<double> W(Wl.size());  // the weights: scaled, then rounded once
+      for (size_t i = 0; i < W.size(); ++i) W[i] = (double)(scale * Wl[i]);
       const int bw = invs[at].bw;
       const int n1 = c->ng[d], nb = 2 * bw + 1, tiles = (n1 + 15) / 16, nt = (16 + 2 * bw + 3) / 4;
       const size_t p0 = P.size();
       at_d[d][held] = p0;
       P.resize(p0 + (size_t)tiles * nt * 64, 0.0);
-      for (int b = 0; b < tiles; ++b)
-        for (int t = 0; t < nt; ++t)
-          for (int l = 0; l < 64; ++l) {
-            const int i = 16 * b + l % 16, col = 16 * b - bw + 4 * t + l / 16, o = col - i + bw;
-            if (i < n1 && col >= 0 && col < n1 && o >= 0 && o < nb)
-              P[p0 + ((size_t)b * nt + t) * 64 + l] = (double)(scale * W[(size_t)i * nb + o]);
-          }
+      for (int i = 0; i < n1; ++i) {
+        double* row = &P[p0 + (size_t)(i / 16) * nt * 64 + i % 16];
+        const int c0 = 16 * (i / 16) - bw;  // first column of the tile's first multiply
+        for (int col = std::max(0, i - bw); col <= std::min(n1 - 1, i + bw); ++col)
+          row[((col - c0) / 4) * 64 + 16 * ((col - c0) % 4)] = W[(size_t)i * nb + col - i + bw];
+      }
       c->tm_bw[d][held] = bw;
     }
   if (!c->tm_all) ILH_HIP(c, hipMalloc((void**)&c->tm_all, (P.size() + 2 * (size_t)c->nh1) * sizeof(double)));

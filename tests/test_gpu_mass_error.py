@@ -90,6 +90,7 @@ def _inverse(A, held):
 @pytest.mark.parametrize("seed", [1, 2])
 def test_rate_error(n, k, seed):
     G = ilh.Hydro("uniform", n, k)
+    G.set_apply_rows(1)  # the strip kernels at every order
     d = len(n)
     u = to_np(G.init_state())
     u = to_dev(si.perturb_state(u, seed, G.nh1, 0.02 / (k * max(n)), 0.3, 0.1))
