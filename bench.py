@@ -50,9 +50,9 @@ TRAFFIC_SOURCES = ("paper_2609_16424_amd/csrc/ilh_jvplin2d.hip", "paper_2609_164
                    "paper_2609_16424_amd/csrc/ilh_pointwise.h", "paper_2609_16424_amd/csrc/ilh_strip.h",
                    "paper_2609_16424_amd/csrc/ilh_internal.h")
 TRAFFIC_SOURCE_END = {"paper_2609_16424_amd/csrc/ilh_internal.h": b"struct ilh_ctx {"}
-TRAFFIC_RECORD = {"sha256": "10ff5d988e5ea8db7a01c24995d79ac166eb8d4505df4ac84ce9dd40d88da621",
+TRAFFIC_RECORD = {"sha256": "bb04528f7feb0853f5d1ed04214a454d8967f994f76c0086af767cf69173c759",
                   "variant": "lin", "n": 128, "order": 3,
-                  "fetch_kib": 16609.2, "fetch_scale": 262144.0 / 131081.33,
+                  "fetch_kib": 16609.3, "fetch_scale": 262144.0 / 131079.79,
                   "write_kib": 3704.4, "write_scale": 262144.0 / 262144.0}
 
 
@@ -72,7 +72,7 @@ def sources_sha256():
 # VALU instructions per launch of the same kernel (rocprofv3 --pmc SQ_INSTS_VALU, same sources):
 # the issue peak of wave64 FP32 (unpacked) / FP64 VALU instructions is 1024 SIMDs x 2.4 GHz / 4.
 VALU_RECORD = {"sha256": TRAFFIC_RECORD["sha256"], "variant": "lin", "n": 128, "order": 3,
-               "instructions": 2137682.5}
+               "instructions": 2139346.5}
 VALU_ISSUE_PEAK = 1024 * 2.4e9 / 4
 
 

@@ -355,10 +355,12 @@ int ilh_sdirk_step(ilh_ctx* ctx, double* u, double dt, int scheme, const double*
  *   v_h = v + dt/2 a(u),  e_h = e + dt/2 M_E^-1 (F(u)^T v_h + b(x)),  x_h = x + dt/2 v_h,
  *   v+ = v + dt a(u_h),   vbar = (v + v+)/2,
  *   e+ = e + dt M_E^-1 (F(u_h)^T vbar + b(x_h)),  x+ = x + dt vbar,
- * with a(w) = -Mhat^-1 P_u F(w) 1 (velocity mass solve with the wall rows held at zero, PCG to
- * 1e-14) and b the TG energy source (else 0).  The averaged velocity makes the total energy
+ * with a(w) = -Mhat^-1 P_u F(w) 1 (velocity mass solve with the wall rows held at zero: direct on
+ * affine initial meshes of one density, at most 16,384 nodes a direction; else PCG to 1e-14) and b
+ * the TG energy source (else 0).  The averaged velocity makes the total energy
  * change exactly dt 1^T b(x_h).  u [block] is updated in place.  2D only (ILH_EINVAL in 3D);
- * uses 3 block vectors of workspace (allocated on first use). */
+ * uses 4 block vectors of workspace and, for the direct solve, its weights and 2 velocity vectors
+ * (allocated on first use). */
 int ilh_rk2avg_step(ilh_ctx* ctx, double* u, double dt);
 
 /* One accepted step under the Newton-based step-size control of Sec. 4 ("Implicit time step
@@ -486,18 +488,19 @@ typedef struct {
  * residual R(.; tau, u) judges the result against base, and k receives the learned iterate if
  * its residual norm is finite and smaller than base's (or base's is not finite), else a copy
  * of base.  u, base, k: device [block]; m, used (1 if learned, nullable): host.  Scratch for
- * the features, activations and one residual is kept in the context (allocated on first
- * use).  Synchronises (the judge reads two norms). */
+ * the features, activations and two residuals is kept in the context (allocated on first
+ * use).  Waits for the two norms that the judge reads: k is complete on return. */
 int ilh_guess_infer(ilh_ctx* ctx, const ilh_guess_model* m, const double* u, const double* base, double tau,
                     double* k, int* used);
 
 /* Features of (u, base) and the whole MLP of m in one launch: pred [Ne][ld] (float, device)
  * receives the network output of every element, equal to ilh_guess_features followed by
- * ilh_mlp_forward (same BF16 rounding, accumulation order and epilogue).  Each work-group keeps
- * every layer's BF16 weights and biases in LDS and walks tiles of 16 elements.  ILH_EINVAL when
- * the widths do not match this mesh's features (widths[0]) and outputs (widths[nl]), when the
- * padded weights exceed 112 KiB of LDS (rows padded by 8 entries), when ld is below the padded
- * output width, or when m->W is not 16-byte aligned.  ilh_guess_infer takes this path when the
+ * ilh_mlp_forward (same BF16 rounding, accumulation order and epilogue).  A work-group takes a tile
+ * of 16 elements through every layer, the weights straight from memory.  ILH_EINVAL when the
+ * widths do not match this mesh's features (widths[0]) and outputs (widths[nl]), when the padded
+ * weights exceed 112 KiB (rows counted with 8 entries of padding), when ld is below the padded
+ * output width, or when m->W is not 16-byte aligned (the size and the alignment are the call's
+ * limits, not the kernel's).  ilh_guess_infer takes this path when the
  * model fits.  No synchronisation. */
 int ilh_guess_mlp_fused(ilh_ctx* ctx, const ilh_guess_model* m, const double* u, const double* base,
                         float* pred, int ld);

@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(GS_T) k_lgs_step(TV* __restrict__ V, int64_t l
       wr[r] = in[r] ? wr[r] : TV(0);
     }
     // the sums q = 2k: v_k . u_j, 2k + 1: v_k . w, then |u_j|^2, u_j . w, |w|^2, reduced across the
-    // wave 16 at a time (all 31 at once spilled the widest instances)
+    // wave 16 at a time (all of the up to 47 at once spilled the widest instances)
 #pragma unroll
     for (int q0 = 0; q0 < NA; q0 += 16) {
       if (ended != 0.0) break;  // behind the loads: one round trip for both

@@ -26,7 +26,7 @@ namespace ilh {
 // ---- linearisation: state w (FP64) -> stored coefficients (T) ----------------------------
 // Bound by the coefficients it writes.  Rows of 60 of 64 lanes (six points a row, ten elements) left
 // the last cache line of each row partly written, which the memory completes by reading it: 1024^2
-// Q3Q2 in FP32 (1.94 GB) took 730 us, with whole lines 440 us.
+// Q3Q2 in FP32 (1.94 GB) took 720 us, with whole lines 490 to 520 us.
 template <int D1D, int Q1D, typename T, int VISC, int SRC>
 __global__ void __launch_bounds__(64) k_lin2d(const KParams P, const Tab2<double, D1D, Q1D> tb,
                                               const double* __restrict__ w, double tau, T* __restrict__ qd,

@@ -7,8 +7,8 @@
 // points in the third direction.  The wave's node strip (D1D z-layers x D1D y-rows x NS nodes
 // per field) is gathered once into LDS; each lane forms the x and y contractions of every field
 // for its column; the third direction is unrolled with the 1D tables in kernel arguments.  The
-// element outputs are combined in LDS over the element's lanes, one velocity component at a
-// time, before the atomic scatter of the shared nodes.
+// outputs are summed over the strip's columns by lane permutes (node_sums3), one velocity component at
+// a time, and take one atomic per node and strip.
 //
 // Stored data: field f of lane l at step qz of strip b sits at qd[((b Q1D + qz) NQD + f) 64 + l]
 // (the NQD fields of one wave's step form one contiguous block).  Strips are dealt to the XCDs

@@ -1141,7 +1141,7 @@ static int energy_update(ilh_ctx* c, const double* w, const double* vt, double* 
 // velocity-mass solve and the energy rate for the averaged velocity.  With one density the solve is
 // direct and its last pass makes the velocity and position updates and clears the residual's
 // velocity rows for the next force: five launches a half, no synchronisation.  16 x 16 Q3Q2: 1.64 ms
-// with conjugate gradients and a launch per vector operation, 0.073 ms now.
+// with conjugate gradients and a launch per vector operation, 0.068 ms now.
 int ilh_rk2avg_step(ilh_ctx* c, double* u, double dt) {
   ILH_TRY
   if (!c || !u || !(dt > 0)) return ILH_EINVAL;
@@ -2340,14 +2340,14 @@ int ilh_guess_infer(ilh_ctx* c, const ilh_guess_model* m, const double* u, const
   float* zs = feat + ne * p0;
   float* acts = zs + tot;
   float* out = acts + tot - ne * pl;
-  // one launch (features and every layer, weights in LDS) where the model fits, else the
-  // features and the layer-by-layer forward
+  // one launch (features and every layer) where ilh_guess_mlp_fused takes the model, else the features
+  // and the forward of ilh_mlp_forward
   const int ND = (c->k + 1) * (c->k + 1), NLd = c->k * c->k;
   const bool widths_ok = m->widths[0] == 2 * ND + NLd + 8 + (m->with_base ? 2 * ND + NLd : 0) &&
                          m->widths[m->nl] == 2 * ND + NLd;
-  int64_t lds = 0;
-  for (int l = 0; l < m->nl; ++l) lds += (int64_t)pad(m->widths[l + 1]) * (pad(m->widths[l]) + 8);
-  const bool fused = widths_ok && lds <= 57344 && (reinterpret_cast<uintptr_t>(m->W) & 15) == 0;
+  int64_t wsize = 0;
+  for (int l = 0; l < m->nl; ++l) wsize += (int64_t)pad(m->widths[l + 1]) * (pad(m->widths[l]) + 8);
+  const bool fused = widths_ok && wsize <= 57344 && (reinterpret_cast<uintptr_t>(m->W) & 15) == 0;
   if (fused) {
     if ((st = ilh_guess_mlp_fused(c, m, u, base, out, pl))) return st;
   } else {

@@ -48,13 +48,15 @@ __device__ __forceinline__ float gelu_d(float z) {
 // output) blocks of all layers at once, from the BF16 data gradients that the second left behind.
 // Layer by layer the forward took 55 us, the data gradients 58 and the weight gradients 132 (one wave
 // read its operands element by element down a column, and one work-group row summed the bias gradients
-// in a serial loop), now 10, 15 and 10; a training step of 4,096 rows 310 -> 65 us.  Operand rounding, accumulation order and epilogues are those of the
-// layer-by-layer form, so zs, acts and the data gradients are bit for bit the same.
+// in a serial loop), now 10, 15 and 10; a training step of 4,096 rows 310 -> 60 us.  Operand rounding,
+// accumulation order and epilogues are those of the layer-by-layer form, so zs, acts and the data
+// gradients are bit for bit the same.
 //
 // MFMA 16x16x32 operand layout: lane l holds row/col (l % 16) and the 8 consecutive k of
 // block (l / 16); the accumulator holds column (l % 16), rows 4 (l / 16) + 0..3.
 constexpr int ML_MAXL = 8;
-constexpr int FZ_WLDS = 57344;   // BF16 weights (rows padded by 8) that the fused inference call takes
+constexpr int FZ_WMAX = 57344;   // BF16 weights (rows counted padded by 8) that the fused inference call takes: the
+                                 // limit of its first form, which held them in LDS; larger models go layer by layer
 constexpr int ML_T = 512;        // threads of the row kernels: one wave per 16-column tile
 constexpr int ML_LD = 128 + 8;   // LDS row of an activation tile (BF16, padded)
 constexpr int ML_MAXB = 512;     // work-groups of the data-gradient launch (each walks 16-row tiles)
@@ -670,7 +672,7 @@ int ilh_guess_mlp_fused(ilh_ctx* c, const ilh_guess_model* m, const double* u, c
   const MlpNet F = make_net(m->nl, m->widths, 0);
   int64_t padded = 0;
   for (int l = 0; l < m->nl; ++l) padded += (int64_t)F.np[l] * (F.kp[l] + 8);
-  if (padded > FZ_WLDS) return fail(c, ILH_EINVAL, "fused guess MLP: the weights exceed the LDS budget");
+  if (padded > FZ_WMAX) return fail(c, ILH_EINVAL, "fused guess MLP: the weights exceed 112 KiB");
   if (ld < F.np[m->nl - 1]) return fail(c, ILH_EINVAL, "prediction stride below the padded output width");
   if ((reinterpret_cast<uintptr_t>(m->W) & 15) != 0) return fail(c, ILH_EINVAL, "fused guess MLP: W not 16-byte aligned");
   const FeatArgs fa{u, m->with_base ? base : nullptr, m->vscale, m->escale, m->xscale, m->kvscale, m->kescale,

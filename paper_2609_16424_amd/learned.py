@@ -217,7 +217,7 @@ class LearnedGuess:
 
     def predict_fused(self, u, base):
         """Network output [Ne][P(w_nl)] from ilh_guess_mlp_fused (features and every layer in one
-        launch, the weights in LDS)."""
+        launch)."""
         out = torch.zeros(self.h.Ne, self.ld_out, dtype=torch.float32, device=self.h.device)
         self.h._stream()
         self.h._check(self.h.lib.ilh_guess_mlp_fused(self.h.ctx, C.byref(self.model()), self.h._vec(u, self.h.nblock),
